@@ -390,7 +390,7 @@ bool geo3(const Candidate& c, const int64_t n[3], int tb, Geo3& g) {
 }
 
 // Default fused depth and lane width per family.
-int default_vx2(int dtype) { return dtype == kF64 ? 2 : (dtype == kF32 ? 4 : 8); }
+int default_vx2(int dtype) { return dtype == kF64 ? 2 : 4; }
 
 void build_candidates(st_plan_s* p) {
     p->cands.clear();

@@ -10,18 +10,31 @@
 //
 // Work decomposition.  A wave owns an x strip of W = 64*VX columns: lane L
 // holds columns X0 + L*VX .. X0 + L*VX + VX-1 of every row it touches, loaded
-// with one coalesced 16-byte access per lane.  The wave walks the rows of one
-// y chunk from top to bottom.  Pipeline level l (l = 0 .. tb-1) keeps the
-// last 2R+1 rows of step l in registers; each new row of step l lets level
-// l+1 produce the row R above it, so step tb leaves the wave R*tb rows behind
-// the loads and is stored straight away.  x neighbours come from the lane's
-// own registers or, across the lane boundary, from lane +-1 by DPP; y
-// neighbours are other queue slots; nothing goes through LDS.  The R columns
-// just outside the strip (step 0 only) are fetched by lanes 0..R-1 (left) and
+// with one coalesced access of up to 16 bytes per lane.  The wave walks the
+// rows of one y chunk from top to bottom.  The canonical point order takes the
+// rows of a pattern from top to bottom, so pipeline level l (l = 0 .. tb-1)
+// keeps partial sums: when row y of step l arrives, its terms finish row y - R
+// of step l+1 (which goes on to level l+1 at once), extend the sums of the R -
+// 1 rows between, and begin row y's own sum; the level holds its last R rows
+// and those R sums.  Step tb leaves the wave R*tb rows behind the loads and is
+// stored straight away.  x neighbours come from the lane's own registers or,
+// across the lane boundary, from lane +-1 by DPP, once per row and step (a box
+// keeps them with the row); nothing goes through LDS.  The R columns just
+// outside the strip (step 0 only) are fetched by lanes 0..R-1 (left) and
 // 32..32+R-1 (right) with the row and reach the DPP "old" operand of lanes 0
 // and 63 through readlane.
 //
-// Loads.  Rows are prefetched 2R+1 rows ahead with buffer loads through a
+// What bounds it.  Eight fused steps: the vector ALU; four: HBM and the ALU
+// about alike.  Against a queue of 2R+1 rows per level, whose boxes shift all
+// their rows again at every step, the loop of the FP32 9-point box at eight
+// steps is 93 % multiply/FMA instead of 81 % (288 of 308 instructions a row),
+// that of the FP64 25-point box 80 % instead of 54 %: 8192^2, 64 steps, zero
+// rule: 9-point FP32 1910 -> 1432 us, FP64 3340 -> 2555; 25-point FP64 8480 ->
+// 5900, FP32 4800 -> 3620; 5-point stars, where a queue shifts a row only once
+// too, +-3 %.  bfloat16 rows take 4 columns a lane (8-byte accesses): with 8
+// the registers leave one or two waves per SIMD (5-point 8192^2 1990 -> 1160).
+//
+// Loads.  Rows are prefetched 2 to 4 rows ahead with buffer loads through a
 // descriptor whose range is the row; under the zero rule a row outside the
 // grid gets an empty range and a ghost column a 32-bit offset past the row's
 // end, so ghost cells load as 0 -- no masks, no clamped indices, and no
@@ -153,8 +166,11 @@ struct Kern {
     // Row y (wrapped already when periodic): an empty range outside the grid.
     template <bool FAST>
     static __device__ __forceinline__ void load_row(const Ctx& c, int32_t y, TC (&v)[VX], TC& xv) {
+        // selects on the row index, not on the address: a row of the pipeline
+        // stays one basic block (split in two, the compiler moves the partial
+        // sums behind the split and holds every level's row there: 30 VGPRs)
         const bool out = ghost(y, c.ny);
-        const TS* base = out ? c.src : c.src + static_cast<int64_t>(y) * c.nx;
+        const TS* base = c.src + static_cast<int64_t>(out ? 0 : y) * c.nx;
         const __amdgpu_buffer_rsrc_t r =
             __builtin_amdgcn_make_buffer_rsrc(const_cast<TS*>(base), 0, out ? 0 : c.row_bytes, kRsrcWord3);
         if constexpr (FAST) {
@@ -200,53 +216,76 @@ struct Kern {
         return idx < 0 ? lft[R + idx] : (idx >= VX ? rgt[idx - VX] : v[idx]);
     }
 
-    // One output row of step l+1 from the queue of step l.  J is the slot of
-    // the newest row; the row dy away from the centre is slot (J - R + dy) mod
-    // Q.  Canonical point order: centre, then (dy, dx) lexicographic.
-    template <int J, bool LEVEL0>
-    static __device__ __forceinline__ void compute(const Ctx& c, const TC (&q)[Q][VX], const TC (&xq)[Q],
-                                                   TC (&out)[VX]) {
-        constexpr int CEN = (J - R + Q) % Q;
-        if constexpr (CLS == kStar) {
-            TC lft[R], rgt[R];
-            side<LEVEL0>(q[CEN], xq[CEN], lft, rgt);
+    // What a level keeps between rows: its last R rows (boxes: with their
+    // columns across the lane boundary) and the partial sums of the R rows of
+    // the next level that still wait for rows below them.  The slots of the
+    // rows rotate (slot J mod R+1 holds the newest), so nothing is copied.
+    struct Level {
+        TC row[R + 1][VX];
+        TC lft[CLS == kBox ? R + 1 : 1][R], rgt[CLS == kBox ? R + 1 : 1][R];
+        TC part[R][VX];  // part[j]: the next level's row j + 1 rows above the newest
+    };
+
+    // Row y of step l arrives (u, its x neighbours lft / rgt): the last terms
+    // of the next level's row y - R complete it (out), the sums of rows y - R
+    // + 1 .. y - 1 take their terms of row y, and row y's own sum is begun
+    // with all its terms up to row y.  Every chain is in canonical point
+    // order: centre, then (dy, dx) lexicographic.  J: slot of row y.
+    template <int J>
+    static __device__ __forceinline__ void advance(const Ctx& c, Level& s, const TC (&u)[VX], const TC (&lft)[R],
+                                                   const TC (&rgt)[R], TC (&out)[VX]) {
+        constexpr int N = R + 1;
+        constexpr int ROW = CLS == kStar ? 1 : Q;       // points of a row dy != 0
+        constexpr int CROW = CLS == kStar ? 2 * R : Q - 1;  // points of the centre row beside the centre
+        // rows that wait for row y as their row dy = 1 .. R, lowest first
+#pragma unroll
+        for (int dy = R; dy >= 1; --dy) {
+            constexpr int P0 = 1 + R * ROW + CROW;  // first point below the centre row
 #pragma unroll
             for (int e = 0; e < VX; ++e) {
-                TC acc = c.w[0] * q[CEN][e];
-                int p = 1;
+                TC acc = s.part[dy - 1][e];
+                if constexpr (CLS == kStar) {
+                    acc = fma_c(c.w[P0 + dy - 1], u[e], acc);
+                } else {
 #pragma unroll
-                for (int dy = -R; dy <= -1; ++dy, ++p)
-                    acc = fma_c(c.w[p], q[(J - R + dy + 2 * Q) % Q][e], acc);
-#pragma unroll
-                for (int dx = -R; dx <= -1; ++dx, ++p)
-                    acc = fma_c(c.w[p], xval(q[CEN], lft, rgt, e + dx), acc);
-#pragma unroll
-                for (int dx = 1; dx <= R; ++dx, ++p)
-                    acc = fma_c(c.w[p], xval(q[CEN], lft, rgt, e + dx), acc);
-#pragma unroll
-                for (int dy = 1; dy <= R; ++dy, ++p)
-                    acc = fma_c(c.w[p], q[(J - R + dy + 2 * Q) % Q][e], acc);
-                out[e] = acc;
-            }
-        } else {
-            TC lft[Q][R], rgt[Q][R];
-#pragma unroll
-            for (int s = 0; s < Q; ++s) side<LEVEL0>(q[s], xq[s], lft[s], rgt[s]);
-#pragma unroll
-            for (int e = 0; e < VX; ++e) {
-                TC acc = c.w[0] * q[CEN][e];
-                int p = 1;
-#pragma unroll
-                for (int dy = -R; dy <= R; ++dy) {
-                    const int sl = (J - R + dy + 2 * Q) % Q;
-#pragma unroll
-                    for (int dx = -R; dx <= R; ++dx) {
-                        if (dy == 0 && dx == 0) continue;
-                        acc = fma_c(c.w[p], xval(q[sl], lft[sl], rgt[sl], e + dx), acc);
-                        ++p;
-                    }
+                    for (int dx = -R; dx <= R; ++dx)
+                        acc = fma_c(c.w[P0 + (dy - 1) * ROW + dx + R], xval(u, lft, rgt, e + dx), acc);
                 }
-                out[e] = acc;
+                if (dy == R) out[e] = acc;
+                else s.part[dy < R ? dy : 0][e] = acc;
+            }
+        }
+        // row y's own sum
+#pragma unroll
+        for (int e = 0; e < VX; ++e) {
+            TC acc = c.w[0] * u[e];
+            int p = 1;
+#pragma unroll
+            for (int dy = -R; dy <= -1; ++dy) {
+                const int sl = (J + dy + 2 * N) % N;
+                if constexpr (CLS == kStar) {
+                    acc = fma_c(c.w[p++], s.row[sl][e], acc);
+                } else {
+#pragma unroll
+                    for (int dx = -R; dx <= R; ++dx)
+                        acc = fma_c(c.w[p++], xval(s.row[sl], s.lft[sl], s.rgt[sl], e + dx), acc);
+                }
+            }
+#pragma unroll
+            for (int dx = -R; dx <= R; ++dx) {
+                if (dx == 0) continue;
+                acc = fma_c(c.w[p++], xval(u, lft, rgt, e + dx), acc);
+            }
+            s.part[0][e] = acc;
+        }
+        constexpr int SN = J % N;
+#pragma unroll
+        for (int e = 0; e < VX; ++e) s.row[SN][e] = u[e];
+        if constexpr (CLS == kBox) {
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
+                s.lft[SN][k] = lft[k];
+                s.rgt[SN][k] = rgt[k];
             }
         }
     }
@@ -254,9 +293,9 @@ struct Kern {
     // Zero rule: ghost rows/columns stay 0; bfloat16 storage rounds every step.
     // (The last level skips this: ghost cells are never stored and the store
     // rounds.)
-    template <bool FAST>
+    template <bool FAST, bool EDGE>
     static __device__ __forceinline__ void finish(const Ctx& c, int32_t y, TC (&out)[VX]) {
-        const bool yg = ghost(y, c.ny);
+        const bool yg = EDGE && ghost(y, c.ny);
 #pragma unroll
         for (int e = 0; e < VX; ++e) {
             const bool g = yg || (!FAST && ghost(c.xl + e, c.nx));
@@ -267,7 +306,7 @@ struct Kern {
     template <bool FAST>
     static __device__ __forceinline__ void store_row(const Ctx& c, int32_t y, const TC (&out)[VX]) {
         const bool ok = static_cast<uint32_t>(y - c.ys) < static_cast<uint32_t>(c.ye - c.ys);
-        TS* base = ok ? c.dst + static_cast<int64_t>(y) * c.nx + c.ofirst : c.dst;
+        TS* base = c.dst + static_cast<int64_t>(ok ? y : 0) * c.nx + c.ofirst;
         const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(base, 0, ok ? c.out_bytes : 0, kRsrcWord3);
         if constexpr (FAST) {
             bstorev(r, c.so, out);
@@ -277,12 +316,14 @@ struct Kern {
         }
     }
 
+    // Rows prefetched: few where a row's pass through many levels covers the
+    // loads' latency, more where a row is short work.
+    static constexpr int pf_depth(int tb) { return R == 1 ? (tb >= 4 && CLS == kBox ? 2 : 4) : 3; }
     template <int TB>
     struct State {
-        TC q[TB][Q][VX];
-        TC xq[Q];           // step-0 ring values of the queued rows
-        TC pf[Q][VX];
-        TC pfx[Q];
+        Level lv[TB];
+        TC pf[pf_depth(TB)][VX];
+        TC pfx[pf_depth(TB)];
         int32_t yl;         // next row to load (wrapped when periodic)
         double fl;          // FLX: outflow through the y faces so far
         double xa[2];       // FLX: totals of the two candidate x-face columns
@@ -408,73 +449,92 @@ struct Kern {
     }
 
     // CAP: the iteration may capture band rows (TESS: only the first 2R*T_b
-    // and the last 2R iterations of a chunk do)
-    template <int TB, bool FAST, int J, bool CAP = TESS>
+    // and the last 2R iterations of a chunk do).  EDGE: rows outside the grid
+    // may be streamed (zero rule).
+    template <int TB, bool FAST, bool EDGE, int J, bool CAP = TESS>
     static __device__ __forceinline__ void step(const Ctx& c, int32_t it, int32_t yfirst, State<TB>& s) {
+        constexpr int P = pf_depth(TB), SP = J % P;
         const int32_t yin = yfirst + it;
+        TC u[VX];
 #pragma unroll
-        for (int e = 0; e < VX; ++e) s.q[0][J][e] = s.pf[J][e];
-        s.xq[J] = s.pfx[J];
-        if constexpr (FLX) flux_add<TB, FAST>(c, s, yin, s.q[0][J]);  // the pass's input state
-        if constexpr (TESS && CAP) tess_capture<TB, 0>(c, yin, s.q[0][J], s.xq[J]);
+        for (int e = 0; e < VX; ++e) u[e] = s.pf[SP][e];
+        const TC xr = s.pfx[SP];
+        if constexpr (FLX) flux_add<TB, FAST>(c, s, yin, u);  // the pass's input state
+        if constexpr (TESS && CAP) tess_capture<TB, 0>(c, yin, u, xr);
         // rows past the end of the stream are never consumed: load the last
         // streamed row again (a cache hit)
-        load_row<FAST>(c, yin + Q <= c.ylast ? s.yl : c.ylast_w, s.pf[J], s.pfx[J]);
+        load_row<FAST>(c, yin + P <= c.ylast ? s.yl : c.ylast_w, s.pf[SP], s.pfx[SP]);
         s.yl = next_row(c, s.yl);
 #pragma unroll
         for (int l = 0; l < TB; ++l) {
-            TC out[VX];
-            if (l == 0) compute<J, true>(c, s.q[0], s.xq, out);
-            else compute<J, false>(c, s.q[l], s.xq, out);
+            TC lft[R], rgt[R], out[VX];
+            if (l == 0) side<true>(u, xr, lft, rgt);
+            else side<false>(u, TC(0), lft, rgt);
+            advance<J>(c, s.lv[l], u, lft, rgt, out);
             const int32_t yc = yin - (l + 1) * R;
             if (l + 1 == TB) {
                 store_row<FAST>(c, yc, out);
             } else {
-                finish<FAST>(c, yc, out);
+                finish<FAST, EDGE>(c, yc, out);
                 if constexpr (FLX) flux_add<TB, FAST>(c, s, yc, out);  // state after step l
                 if constexpr (TESS && CAP) tess_capture_l<TB>(c, l + 1, yc, out);
 #pragma unroll
-                for (int e = 0; e < VX; ++e) s.q[l + 1][J][e] = out[e];
+                for (int e = 0; e < VX; ++e) u[e] = out[e];
             }
         }
     }
 
-    template <int TB, bool FAST, bool CAP, int... J>
+    template <int TB, bool FAST, bool EDGE, bool CAP, int... J>
     static __device__ __forceinline__ void group(const Ctx& c, int32_t base, int32_t yfirst, State<TB>& s,
                                                  std::integer_sequence<int, J...>) {
-        (step<TB, FAST, J, CAP>(c, base + J, yfirst, s), ...);
+        (step<TB, FAST, EDGE, J, CAP>(c, base + J, yfirst, s), ...);
     }
-    template <int TB, bool FAST, int... J>
+    template <int TB, bool FAST, bool EDGE, int... J>
     static __device__ __forceinline__ void tail(const Ctx& c, int32_t base, int32_t nit, int32_t yfirst,
                                                 State<TB>& s, std::integer_sequence<int, J...>) {
-        ((base + J < nit ? step<TB, FAST, J>(c, base + J, yfirst, s) : void()), ...);
+        ((base + J < nit ? step<TB, FAST, EDGE, J>(c, base + J, yfirst, s) : void()), ...);
     }
 
     static __device__ __forceinline__ int32_t wrap_row(const Ctx& c, int32_t y) {
         return PER ? wrap_idx(y, c.ny) : y;
     }
 
-    template <int TB, bool FAST>
+    template <int TB, bool FAST, bool EDGE>
     static __device__ __forceinline__ void body(Ctx& c) {
         // TESS: a junction side streams no halo rows (the triangle); a grid
         // edge under the zero rule streams the ghost rows as usual
+        constexpr int P = pf_depth(TB);
+        // rows per loop trip: a multiple of the row slots and of the prefetch
+        // depth, and long enough that no value changes its register (with R +
+        // 1 rows a trip an eighth of the loop is copies)
+        constexpr int U = R == 1 ? 4 : 6;
+        static_assert(U % P == 0 && U % (R + 1) == 0, "slots repeat every loop trip");
         const int32_t yfirst = TESS ? (c.jlo ? c.cs : c.cs - R * TB) : c.ys - R * TB;
         const int32_t nit = TESS ? (c.jhi ? c.ce : c.ce + R * TB) - yfirst : (c.ye - c.ys) + 2 * R * TB;
         c.ylast = yfirst + nit - 1;
         c.ylast_w = wrap_row(c, c.ylast);
         State<TB> s;
 #pragma unroll
-        for (int l = 0; l < TB; ++l)
+        for (int l = 0; l < TB; ++l) {
+            Level& v = s.lv[l];
 #pragma unroll
-            for (int sl = 0; sl < Q; ++sl)
+            for (int sl = 0; sl < R + 1; ++sl)
 #pragma unroll
-                for (int e = 0; e < VX; ++e) s.q[l][sl][e] = TC(0);
+                for (int e = 0; e < VX; ++e) v.row[sl][e] = TC(0);
+#pragma unroll
+            for (int sl = 0; sl < (CLS == kBox ? R + 1 : 1); ++sl)
+#pragma unroll
+                for (int k = 0; k < R; ++k) v.lft[sl][k] = v.rgt[sl][k] = TC(0);
+#pragma unroll
+            for (int j = 0; j < R; ++j)
+#pragma unroll
+                for (int e = 0; e < VX; ++e) v.part[j][e] = TC(0);
+        }
         s.yl = wrap_row(c, yfirst);
         s.fl = 0.0;
         s.xa[0] = s.xa[1] = 0.0;
 #pragma unroll
-        for (int sl = 0; sl < Q; ++sl) {
-            s.xq[sl] = TC(0);
+        for (int sl = 0; sl < P; ++sl) {
             load_row<FAST>(c, yfirst + sl <= c.ylast ? s.yl : c.ylast_w, s.pf[sl], s.pfx[sl]);
             s.yl = next_row(c, s.yl);
         }
@@ -485,31 +545,31 @@ struct Kern {
             // row is loaded, so captures happen only in the first 2R*T_b
             // iterations (junction above) and the last 2R (junction below)
             const int32_t head = 2 * R * TB, tail0 = nit - 2 * R;
-            for (; base + Q <= nit && base < head; base += Q)
-                group<TB, FAST, true>(c, base, yfirst, s, std::make_integer_sequence<int, Q>{});
-            for (; base + Q <= tail0; base += Q)
-                group<TB, FAST, false>(c, base, yfirst, s, std::make_integer_sequence<int, Q>{});
-            for (; base + Q <= nit; base += Q)
-                group<TB, FAST, true>(c, base, yfirst, s, std::make_integer_sequence<int, Q>{});
+            for (; base + U <= nit && base < head; base += U)
+                group<TB, FAST, EDGE, true>(c, base, yfirst, s, std::make_integer_sequence<int, U>{});
+            for (; base + U <= tail0; base += U)
+                group<TB, FAST, EDGE, false>(c, base, yfirst, s, std::make_integer_sequence<int, U>{});
+            for (; base + U <= nit; base += U)
+                group<TB, FAST, EDGE, true>(c, base, yfirst, s, std::make_integer_sequence<int, U>{});
         } else {
-            for (; base + Q <= nit; base += Q)
-                group<TB, FAST, false>(c, base, yfirst, s, std::make_integer_sequence<int, Q>{});
+            for (; base + U <= nit; base += U)
+                group<TB, FAST, EDGE, false>(c, base, yfirst, s, std::make_integer_sequence<int, U>{});
         }
-        tail<TB, FAST>(c, base, nit, yfirst, s, std::make_integer_sequence<int, Q>{});
+        tail<TB, FAST, EDGE>(c, base, nit, yfirst, s, std::make_integer_sequence<int, U>{});
         if constexpr (FLX) flux_store<TB, FAST>(c, s);
     }
 
     // one specialised pipeline per fused depth
-    template <bool FAST>
+    template <bool FAST, bool EDGE>
     static __device__ __forceinline__ void dispatch(Ctx& c, int tb) {
-        if constexpr (TBMAX >= 8) if (tb == 8) return body<8, FAST>(c);
-        if constexpr (TBMAX >= 7) if (tb == 7) return body<7, FAST>(c);
-        if constexpr (TBMAX >= 6) if (tb == 6) return body<6, FAST>(c);
-        if constexpr (TBMAX >= 5) if (tb == 5) return body<5, FAST>(c);
-        if constexpr (TBMAX >= 4) if (tb == 4) return body<4, FAST>(c);
-        if constexpr (TBMAX >= 3) if (tb == 3) return body<3, FAST>(c);
-        if constexpr (TBMAX >= 2) if (tb == 2) return body<2, FAST>(c);
-        body<1, FAST>(c);
+        if constexpr (TBMAX >= 8) if (tb == 8) return body<8, FAST, EDGE>(c);
+        if constexpr (TBMAX >= 7) if (tb == 7) return body<7, FAST, EDGE>(c);
+        if constexpr (TBMAX >= 6) if (tb == 6) return body<6, FAST, EDGE>(c);
+        if constexpr (TBMAX >= 5) if (tb == 5) return body<5, FAST, EDGE>(c);
+        if constexpr (TBMAX >= 4) if (tb == 4) return body<4, FAST, EDGE>(c);
+        if constexpr (TBMAX >= 3) if (tb == 3) return body<3, FAST, EDGE>(c);
+        if constexpr (TBMAX >= 2) if (tb == 2) return body<2, FAST, EDGE>(c);
+        body<1, FAST, EDGE>(c);
     }
 
     // everything is inlined into the kernel: no device-function calls
@@ -615,13 +675,27 @@ struct Kern {
             c.fx = c.ofirst < 1 || c.olast > c.nx - 1;
             c.fyb = c.ys < 1 || c.ye > c.ny - 1;
         }
-        if (fast) dispatch<true>(c, tb);
-        else dispatch<false>(c, tb);
+        // chunks that stream no row outside the grid skip the ghost-row tests
+        const bool edge = !PER && (c.ys - R * tb < 0 || c.ye + R * tb > c.ny);
+        if constexpr (!PER && !TESS && !FLX) {
+            if (fast && !edge) return dispatch<true, false>(c, tb);
+        }
+        if (fast) dispatch<true, true>(c, tb);
+        else dispatch<false, true>(c, tb);
     }
 };
 
+// Waves per SIMD the register allocation has to leave room for: what the
+// instance's state takes without scratch.  (Left to itself the compiler takes
+// registers for longer schedules, down to one wave for the 25-point boxes.)
+constexpr int min_waves(int radius, int cls, int tbmax, int bytes, bool extra) {
+    if (extra) return 1;
+    if (radius == 2) return tbmax < 4 ? 4 : (cls == kBox ? 2 : 3);
+    return tbmax < 8 ? 4 : (cls == kBox && bytes != 4 ? 2 : 3);
+}
+
 template <typename TS, int R, int CLS, int TBMAX, int VX, bool PER, bool FLX, bool TESS = false>
-__global__ __launch_bounds__(256) void stream2d_kernel(const Stream2DArgs a) {
+__global__ __launch_bounds__(256, min_waves(R, CLS, TBMAX, sizeof(TS), FLX || TESS)) void stream2d_kernel(const Stream2DArgs a) {
     Kern<TS, R, CLS, TBMAX, VX, PER, FLX, TESS>::run(a);
 }
 

@@ -1,0 +1,48 @@
+"""GPU parity of the streaming pipelines at the places where their loops, tiles
+and pass lists end: every fused depth with every remainder of the loop trip,
+bit for bit against the one-step kernel (same point order, same chain), which
+itself is checked against the FP64 oracle."""
+import numpy as np
+import pytest
+
+import synth
+from gpu_helpers import check, gpu_sweep, oracle_ref
+
+pytestmark = pytest.mark.gpu
+
+
+def _weights(offsets, seed, dtype):
+    r = np.random.default_rng(seed).random(len(offsets))
+    return synth.adjust_centre(r / r.sum(), "f64" if dtype == "f64" else "f32")
+
+
+def _against_naive(plan, naive, u0, offs, w, steps, bc, dtype, select=None, what=""):
+    print(f"{what} steps {steps}", flush=True)
+    got, _ = gpu_sweep(u0, offs, w, steps, bc, dtype, select=select, plan=plan)
+    one, _ = gpu_sweep(u0, offs, w, steps, bc, dtype, plan=naive)
+    assert np.array_equal(got, one), f"{what} steps {steps}: differs from the one-step kernel"
+    return one
+
+
+# 2D: the rows of a chunk over the loop trip (4 rows, 6 at radius 2) leave every
+# remainder, chunks that touch neither edge take the loop without ghost-row
+# tests (several chunks of 8 rows), and the step counts bring every depth
+@pytest.mark.parametrize("dtype", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("bc", ["zero", "periodic"])
+@pytest.mark.parametrize("pattern,radius", [("star", 1), ("box", 1), ("star", 2), ("box", 2)])
+@pytest.mark.parametrize("ny", [1, 6, 43, 90])
+def test_2d_every_depth_and_row_remainder(dtype, bc, pattern, radius, ny):
+    import paper_2303_08365_amd as st
+    offs = (synth.star_offsets if pattern == "star" else synth.box_offsets)(2, radius)
+    w = _weights(offs, 31, dtype)
+    shape = (ny, 260)  # whole-vector rows, two strips
+    u0 = synth.uniform_field(shape, seed=32)
+    plan, naive = st.Plan(offs, shape, dtype, bc), st.Plan(offs, shape, dtype, bc, naive=True)
+    top = max(c["tb"] for c in plan.candidates() if not c["tessellated"])
+    chunks = {c["tile_y"]: k for k, c in enumerate(plan.candidates())
+              if c["kernel"] == st.KERNEL_STREAM2D and c["tb"] == top and not c["tessellated"]}
+    for rows, k in sorted(chunks.items())[:3]:
+        for steps in [top + d for d in range(1, top + 1)] + [2 * top]:
+            one = _against_naive(plan, naive, u0, offs, w, steps, bc, dtype, {"variant": k},
+                                 f"{dtype} {bc} {pattern}{radius} ny {ny} chunk {rows}")
+    check(one, oracle_ref(u0, offs, w, steps, bc, dtype), dtype, steps, "one-step kernel")
