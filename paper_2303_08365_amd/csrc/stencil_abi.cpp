@@ -245,10 +245,25 @@ void classify(st_plan_s* p) {
 struct Geo2 {
     int32_t hxa, out_w, tiles_x, chunk_y, chunks_y;
     int64_t items;
+    bool vec;  // the strips allow whole-vector rows (element-aligned buffers; not the tessellated form)
 };
 
 // Resident waves of the 2D kernel (4 independent waves per work-group).
 int64_t wave_capacity2(const Candidate& c) { return static_cast<int64_t>(device_cus()) * (c.occ > 0 ? c.occ : 2) * 4; }
+
+// Whole-vector rows under the periodic rule when vx does not divide nx.  The
+// last strip starts early so that the wrap falls between two of its lanes; no
+// other strip's halo may reach the wrap and the last one's may not reach
+// column 0 (whole lanes both), so every strip owns at least its halo and a
+// lane or two: the widest strip of at most out_w columns that leaves the last
+// one so much, two strips at least; 0 when there is none.
+int32_t wrap_strip(int64_t nx, int32_t out_w, int32_t hxa, int vx) {
+    const int32_t least = hxa + 2 * vx;
+    int32_t w = static_cast<int32_t>(std::min<int64_t>(out_w, round_up(ceil_div(nx, 2), vx)));
+    for (; w >= least; w -= vx)
+        if (w < nx && nx % w >= least) return w;
+    return 0;
+}
 
 bool geo2(const Candidate& c, int64_t ny, int64_t nx, int tb, Geo2& g, int64_t chunk_override = 0) {
     const int vx = c.k2.vx, R = c.k2.radius;
@@ -278,6 +293,12 @@ bool geo2(const Candidate& c, int64_t ny, int64_t nx, int tb, Geo2& g, int64_t c
     g.hxa = static_cast<int32_t>(round_up(static_cast<int64_t>(R) * (tb - 1), vx));
     g.out_w = 64 * vx - 2 * g.hxa;
     if (g.out_w <= 0) return false;
+    g.vec = true;
+    if (c.k2.bc == kPeriodic && nx % vx != 0) {
+        const int32_t w = wrap_strip(nx, g.out_w, g.hxa, vx);
+        g.vec = w > 0;
+        if (g.vec) g.out_w = w;
+    }
     g.tiles_x = static_cast<int32_t>(ceil_div(nx, g.out_w));
     int64_t chunk = chunk_override > 0 ? chunk_override : c.chunk;
     if (chunk <= 0)
@@ -661,6 +682,9 @@ void canonical_weights(const st_plan_s* p, const double* coeffs, double* out) {
     }
 }
 
+bool elem_aligned(const void* ptr, int dtype) {
+    return reinterpret_cast<uintptr_t>(ptr) % static_cast<uintptr_t>(elem_bytes(dtype)) == 0;
+}
 bool aligned16(const void* ptr) { return (reinterpret_cast<uintptr_t>(ptr) & 15u) == 0; }
 
 // Fused depths of the passes of one run: all tb except the remainder, and
@@ -790,7 +814,7 @@ st_status launch_pass(const st_plan_s* p, const Candidate& c, const void* src, v
         G.chunk_y = g.chunk_y;
         G.out_w = g.out_w;
         G.hxa = g.hxa;
-        G.vec_ok = vec_ok ? 1 : 0;
+        G.vec_ok = (c.k2.tess ? vec_ok : g.vec && elem_aligned(src, p->dtype) && elem_aligned(dst, p->dtype)) ? 1 : 0;
         G.tb = tb;
         G.tile_begin = 0;
         for (int i = 0; i < p->npoints; ++i) G.w[i] = wcan[i];
@@ -1584,7 +1608,7 @@ st_status batch_table(st_plan_s* plan, const Candidate& c, int32_t n, void* cons
         G.chunk_y = geo.chunk_y;
         G.out_w = geo.out_w;
         G.hxa = geo.hxa;
-        G.vec_ok = (G.nx % c.k2.vx == 0) && aligned16(grids[g]) && aligned16(works[g]);
+        G.vec_ok = geo.vec && elem_aligned(grids[g], plan->dtype) && elem_aligned(works[g], plan->dtype);
         G.tb = c.tb;
         G.full = full;
         for (int j = 0; j < 3; ++j) G.tail[j] = full + j < static_cast<int>(v.size()) ? v[full + j] : 0;

@@ -46,3 +46,41 @@ def test_2d_every_depth_and_row_remainder(dtype, bc, pattern, radius, ny):
             one = _against_naive(plan, naive, u0, offs, w, steps, bc, dtype, {"variant": k},
                                  f"{dtype} {bc} {pattern}{radius} ny {ny} chunk {rows}")
     check(one, oracle_ref(u0, offs, w, steps, bc, dtype), dtype, steps, "one-step kernel")
+
+
+def _offset_view(u0, dtype):
+    """The field on the device, one element past the allocation's start."""
+    import torch
+    t = {"f64": torch.float64, "f32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    base = torch.zeros(u0.size + 1, dtype=t, device="cuda")
+    g = base[1:].view(u0.shape)
+    g.copy_(torch.from_numpy(u0).to(t))
+    return g
+
+
+# 2D rows whose length the lane width does not divide, in whole vectors: one
+# column more and less than a strip (64 lanes x 2 or 4 columns) and than two,
+# the last strip a lane wide or less, periodic rows too short for two strips
+@pytest.mark.parametrize("dtype", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("bc", ["zero", "periodic"])
+@pytest.mark.parametrize("pattern,radius", [("star", 1), ("box", 2)])
+def test_2d_rows_of_any_length(dtype, bc, pattern, radius):
+    import paper_2303_08365_amd as st
+    import torch
+    from gpu_helpers import to_host
+    offs = (synth.star_offsets if pattern == "star" else synth.box_offsets)(2, radius)
+    w = _weights(offs, 33, dtype)
+    for nx in [19, 45, 127, 129, 131, 226, 241, 243, 255, 257, 259, 262, 381, 495, 511, 513, 517]:
+        shape = (23, nx)
+        u0 = synth.uniform_field(shape, seed=nx)
+        plan, naive = st.Plan(offs, shape, dtype, bc), st.Plan(offs, shape, dtype, bc, naive=True)
+        depths = {c["tb"]: k for k, c in reversed(list(enumerate(plan.candidates())))
+                  if c["kernel"] == st.KERNEL_STREAM2D and not c["tessellated"]}
+        for tb, k in sorted(depths.items()):
+            _against_naive(plan, naive, u0, offs, w, 2 * tb + 1, bc, dtype, {"variant": k}, f"{dtype} {bc} nx {nx} tb {tb}")
+        # buffers that are aligned to an element only
+        g, work, ref = _offset_view(u0, dtype), _offset_view(u0, dtype), _offset_view(u0, dtype)
+        plan.run(g, list(w), 5, work=work)
+        naive.run(ref, list(w), 5)
+        torch.cuda.synchronize()
+        assert np.array_equal(to_host(g), to_host(ref)), f"{dtype} {bc} nx {nx}: element-aligned buffers"
