@@ -38,6 +38,7 @@ struct Kern {
     static_assert(RIN <= 32, "the outer columns of a wave's rows fit in half a wave");
     static constexpr int32_t kRsrcWord3 = 0x00020000;
     static constexpr int32_t kNT = 2;
+    static constexpr uint32_t kOut = 0x80000000u;           // past the end of any row
 
     struct Ctx {
         const TS* src;
@@ -54,7 +55,8 @@ struct Kern {
         uint32_t xr_off;        // this lane's outer-column element within a plane
         bool xr_zero;           // that element is an x ghost (zero rule)
         int32_t ox0, ox1;       // owned columns
-        uint32_t so, out_bytes;
+        int32_t obase;          // stores: column the descriptor of an output row starts at,
+        uint32_t so, out_bytes; // lane offset from it (kOut: not an output lane), its range
         int lane;
         TC w[27];
     };
@@ -235,7 +237,7 @@ struct Kern {
         for (int k = 0; k < K; ++k) {
             const int32_t y = c.yw + k;
             const bool ok = zok && static_cast<uint32_t>(y) < static_cast<uint32_t>(c.ny);
-            TS* base = ok ? c.dst + static_cast<int64_t>(z) * c.plane_elems + y * c.nx + c.ox0 : c.dst;
+            TS* base = ok ? c.dst + static_cast<int64_t>(z) * c.plane_elems + y * c.nx + c.obase : c.dst;
             const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(base, 0, ok ? c.out_bytes : 0, kRsrcWord3);
             if constexpr (FAST) {
                 bstorev(r, c.so, out[k]);
@@ -298,11 +300,14 @@ struct Kern {
         c.plane_elems = a.ny * a.nx;
         c.row_bytes = static_cast<uint32_t>(c.nx) * sizeof(TS);
         c.plane_bytes = static_cast<uint32_t>(c.plane_elems) * sizeof(TS);
-        constexpr int32_t OUTW = W - 2 * HX;
-        c.ox0 = tx * OUTW;
-        c.ox1 = c.ox0 + OUTW < c.nx ? c.ox0 + OUTW : c.nx;
+        c.ox0 = tx * a.out_w;
+        c.ox1 = c.ox0 + a.out_w < c.nx ? c.ox0 + a.out_w : c.nx;
         int32_t X0 = c.ox0 - HX;
         if (!PER && FAST) X0 = X0 < 0 ? 0 : (X0 + W > c.nx ? c.nx - W : X0);
+        // periodic rows that are no multiple of VX: the tile that ends at the
+        // row's end starts up to VX - 1 columns early, so that the wrap falls
+        // between two lanes
+        if (PER && FAST && c.ox1 == c.nx) X0 -= (VX - c.nx % VX) % VX;
         c.xl = X0 + c.lane * VX;
         c.yw = ty * H + wave * K;
 #pragma unroll
@@ -324,8 +329,18 @@ struct Kern {
             c.xr_off = static_cast<uint32_t>(ry * c.nx + rx) * sizeof(TS);
             c.xr_zero = ghost(xx, c.nx);
         }
-        c.so = static_cast<uint32_t>(c.xl - c.ox0) * sizeof(TS);
-        c.out_bytes = static_cast<uint32_t>(c.ox1 - c.ox0) * sizeof(TS);
+        if constexpr (FAST) {
+            // whole lanes through the whole row: a lane across ox0 (the tile
+            // was moved off the lane grid) stores columns that are exact here
+            // and that the neighbouring tile stores with the same bits
+            c.obase = 0;
+            c.out_bytes = c.row_bytes;
+            c.so = c.xl + VX > c.ox0 && c.xl < c.ox1 ? static_cast<uint32_t>(c.xl) * sizeof(TS) : kOut;
+        } else {
+            c.obase = c.ox0;
+            c.out_bytes = static_cast<uint32_t>(c.ox1 - c.ox0) * sizeof(TS);
+            c.so = static_cast<uint32_t>(c.xl - c.ox0) * sizeof(TS);
+        }
         c.zs = cz * a.chunk_z;
         c.ze = c.zs + a.chunk_z < c.nz ? c.zs + a.chunk_z : c.nz;
 #pragma unroll

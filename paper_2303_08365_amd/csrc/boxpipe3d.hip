@@ -35,8 +35,9 @@
 // and a 32-bit vector offset per row fixed for the pass; rows outside the
 // grid and cells the tile does not own use an offset past the range, so
 // such loads return 0 and such stores are dropped.  Needs the zero rule,
-// nx >= 64*VX, ny >= NW*K, planes below 2 GiB and, for an even VX,
-// nx % VX == 0.
+// nx >= 64*VX, ny >= NW*K and planes below 2 GiB; rows of any length and
+// element-aligned buffers (a tile moved off the lane grid at the edge overlaps
+// its neighbour by less than a lane and stores the same bits there).
 #include "dev_common.h"
 #include "internal.h"
 
@@ -63,10 +64,6 @@ struct Pipe {
     static constexpr uint32_t kOut = 0x80000000u;       // past the end of any plane (planes < 2 GiB)
     static constexpr int32_t kRsrcWord3 = 0x00020000;  // gfx9: raw 32-bit data
     static constexpr int kNT = 2;                      // stores: non-temporal
-    // An odd lane width cannot keep tile edges on lane boundaries (the edge
-    // tiles touch the grid's edge): then ownership and stores go per element.
-    static constexpr bool kElem = VX % 2 != 0;
-    static constexpr int SO = kElem ? K * VX : K;
 
     struct Ctx {
         const TS* src;
@@ -75,7 +72,7 @@ struct Pipe {
         int64_t plane_elems;
         uint32_t plane_bytes;
         uint32_t lo[R];  // byte offset of the lane's columns in rows yw-1 .. yw+K; kOut outside the grid
-        uint32_t so[SO];  // same for the stores of the wave's rows (per element if kElem); kOut: not owned
+        uint32_t so[K];  // same for the stores of the wave's rows; kOut: not owned
         int lane, wave;
         TC w[27];
     };
@@ -159,23 +156,8 @@ struct Pipe {
     }
     static __device__ __forceinline__ void store_plane(const Ctx& c, int32_t z, const TC (&v)[K][VX]) {
         const __amdgpu_buffer_rsrc_t r = plane_out(c, z);
-        if constexpr (kElem) {
 #pragma unroll
-            for (int k = 0; k < K; ++k)
-#pragma unroll
-                for (int e = 0; e < VX; ++e) {
-                    const TS x = S::narrow(v[k][e]);
-                    if constexpr (sizeof(TS) == 8)
-                        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, x), r, c.so[k * VX + e], 0, kNT);
-                    else if constexpr (sizeof(TS) == 4)
-                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), r, c.so[k * VX + e], 0, kNT);
-                    else
-                        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, x), r, c.so[k * VX + e], 0, kNT);
-                }
-        } else {
-#pragma unroll
-            for (int k = 0; k < K; ++k) strow(r, c.so[k], v[k]);
-        }
+        for (int k = 0; k < K; ++k) strow(r, c.so[k], v[k]);
     }
 
     // The value left of a row's first column and right of its last.
@@ -280,23 +262,13 @@ struct Pipe {
                           ? static_cast<uint32_t>(y * nx + xl) * kE
                           : kOut;
         }
-        if constexpr (kElem) {
+        // whole lanes: a lane across ox0 (the tile was moved off the lane grid)
+        // stores columns that the neighbouring tile stores with the same bits
+        const bool xown = xl + VX > ox0 && xl < ox1;
 #pragma unroll
-            for (int k = 0; k < K; ++k)
-#pragma unroll
-                for (int e = 0; e < VX; ++e) {
-                    const int32_t y = yw + k, x = xl + e;
-                    c.so[k * VX + e] = x >= ox0 && x < ox1 && y >= oy0 && y < oy1
-                                           ? static_cast<uint32_t>(y * nx + x) * kE
-                                           : kOut;
-                }
-        } else {
-            const bool xown = xl >= ox0 && xl + VX <= ox1;
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const int32_t y = yw + k;
-                c.so[k] = xown && y >= oy0 && y < oy1 ? static_cast<uint32_t>(y * nx + xl) * kE : kOut;
-            }
+        for (int k = 0; k < K; ++k) {
+            const int32_t y = yw + k;
+            c.so[k] = xown && y >= oy0 && y < oy1 ? static_cast<uint32_t>(y * nx + xl) * kE : kOut;
         }
 #pragma unroll
         for (int p = 0; p < 27; ++p) c.w[p] = suni(static_cast<TC>(a.w[p]));

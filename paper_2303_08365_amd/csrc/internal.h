@@ -42,7 +42,7 @@ struct Stream2DGrid {
     int32_t chunk_y;     // output rows per chunk
     int32_t out_w;       // output columns per strip = 64*VX - 2*hxa
     int32_t hxa;         // redundant halo columns each side (multiple of VX)
-    int32_t vec_ok;      // rows and base are aligned for whole-vector access
+    int32_t vec_ok;      // rows are read and stored in whole vectors
     int32_t tb;          // fused steps this pass (<= template depth); batch: the full depth
     int32_t full;        // batch: passes of depth tb, then up to 3 tail passes
     int32_t tail[3];     // batch: depths of the tail passes (0 = no such pass)
@@ -86,7 +86,6 @@ struct Stream3DArgs {
     int32_t tiles_x, tiles_y, chunks_z;
     int32_t out_w, out_h, chunk_z;
     int32_t hxa, hya;    // redundant halo columns/rows inside the register tile
-    int32_t vec_ok;
     int32_t tb;
     double w[32];        // canonical-order weights (6R+1 used)
     double* flux_part;   // outflow variants: one partial sum per wave (work-group * NW + wave)
@@ -117,7 +116,7 @@ struct Stream1DArgs {
     int32_t out_w;       // owned cells per strip = 64*VX - 2*halo
     int32_t halo;        // stale cells at each end of a strip (>= R*tb, multiple of VX)
     int32_t tb;          // steps this pass
-    int32_t vec_ok;      // whole-vector access (n % VX == 0, n >= 64*VX, 16-byte aligned)
+    int32_t vec_ok;      // whole-vector access (n >= 64*VX, element-aligned buffers)
     double w[9];         // canonical-order weights (2R+1 used)
 };
 bool stream1d_has(int dtype, int radius);
@@ -131,6 +130,7 @@ struct Box3DArgs {
     void* dst;
     int64_t nz, ny, nx;
     int32_t tiles_x, tiles_y, chunks_z, chunk_z;
+    int32_t out_w;       // owned columns per tile (box3d_kernel)
     int32_t tb;          // steps per pass: 1 or 2
     double w[27];        // canonical-order weights
 };

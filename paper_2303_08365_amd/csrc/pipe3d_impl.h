@@ -55,8 +55,14 @@
 // output rows, lanes whose columns lie outside the output tile, and halo rows
 // outside the grid use an offset past the range's end: the hardware drops
 // such a store and returns 0 for such a load.  (The range check covers the
-// vector offset only, so the scalar offset stays 0.)  Needs planes below
-// 2 GiB, whole-vector rows, and under the zero rule nx >= 64*VX, ny >= NW*K.
+// vector offset only, so the scalar offset stays 0.)  Needs planes below 2 GiB
+// and under the zero rule nx >= 64*VX, ny >= NW*K.  Rows of any length are read
+// and stored in whole vectors (8- and 16-byte buffer accesses need the
+// element's alignment only): a tile moved inward off the lane grid overlaps
+// its neighbour by less than a lane; under the periodic rule the planner's
+// tiles put the wrap between two lanes.  251 x 319 x 377 FP64, 50 steps: 3200 us
+// on the queued-plane kernel's element form, 1877 us here.  The LDS queue's
+// loads are the exception: they keep to 16-byte aligned rows.
 #pragma once
 
 #include <utility>
@@ -595,10 +601,17 @@ struct Pipe {
             X0 = X0 < 0 ? 0 : (X0 + W > nx ? nx - W : X0);
             Y0 = Y0 < 0 ? 0 : (Y0 + H > ny ? ny - H : Y0);
         }
+        // periodic rows that are no multiple of VX: the tile that ends at the
+        // row's end starts up to VX - 1 columns early, so that the wrap falls
+        // between two lanes
+        if (PER && !LQ && ox1 == nx) X0 -= (VX - nx % VX) % VX;
         const int32_t xl = X0 + c.lane * VX;
         const int32_t yw = Y0 + c.wave * K;
         const int32_t x0 = PER ? wrap_idx(xl, nx) : xl;
-        const bool xown = xl >= ox0 && xl < ox1;  // whole lanes: out_w, hxa and nx are multiples of VX
+        // whole lanes: a lane across ox0 (the tile was moved off the lane grid)
+        // stores columns that are exact here and that the neighbouring tile
+        // stores with the same bits
+        const bool xown = xl + VX > ox0 && xl < ox1;
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             // zero rule: rows yw + k lie in the grid (the tile was moved inward)

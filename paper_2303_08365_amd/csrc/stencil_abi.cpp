@@ -338,6 +338,8 @@ bool geo1(const st_plan_s* p, int tb, Geo1& g) {
 
 struct GeoB {
     int32_t tiles_x, tiles_y, chunk_z, chunks_z;
+    int32_t out_w;  // box3d_kernel: owned columns per tile
+    bool vec;       // the tiles allow whole-vector rows (element-aligned buffers)
 };
 
 // 3D boxes: tiles of out_w x h owned cells (the register tile is 64*VX wide;
@@ -353,7 +355,9 @@ bool geob(const st_plan_s* p, const Candidate& c, int tb, GeoB& g) {
         // at least one register tile wide and high; one work-group of 8
         // waves per CU (2 waves per SIMD); 5 planes re-streamed per chunk
         const BoxPipeShape sh = boxpipe3d_shape(p->dtype, c.bpipe - 1);
-        if (p->bc != kZero || n[2] < sh.w || n[1] < sh.h || (sh.vx % 2 == 0 && n[2] % sh.vx != 0)) return false;
+        if (p->bc != kZero || n[2] < sh.w || n[1] < sh.h) return false;
+        g.out_w = sh.out_w;
+        g.vec = true;
         g.tiles_x = static_cast<int32_t>(ceil_div(n[2], sh.out_w));
         g.tiles_y = static_cast<int32_t>(ceil_div(n[1], sh.out_h));
         const int64_t per_plane = static_cast<int64_t>(g.tiles_x) * g.tiles_y;
@@ -365,7 +369,16 @@ bool geob(const st_plan_s* p, const Candidate& c, int tb, GeoB& g) {
         return per_plane * g.chunks_z < (int64_t(1) << 31);
     }
     const Box3DShape sh = box3d_shape(p->dtype, tb);
-    g.tiles_x = static_cast<int32_t>(ceil_div(n[2], sh.out_w));
+    // whole-vector rows: the zero rule's edge tiles move inward, which needs
+    // the grid at least one register tile wide
+    g.out_w = sh.out_w;
+    g.vec = p->bc == kPeriodic || n[2] >= sh.w;
+    if (p->bc == kPeriodic && n[2] % sh.vx != 0) {
+        const int32_t w = wrap_strip(n[2], sh.out_w, (sh.w - sh.out_w) / 2, sh.vx);
+        g.vec = w > 0;
+        if (g.vec) g.out_w = w;
+    }
+    g.tiles_x = static_cast<int32_t>(ceil_div(n[2], g.out_w));
     g.tiles_y = static_cast<int32_t>(ceil_div(n[1], sh.h));
     const int64_t per_plane = static_cast<int64_t>(g.tiles_x) * g.tiles_y;
     int64_t chunk = c.chunk;
@@ -378,6 +391,7 @@ bool geob(const st_plan_s* p, const Candidate& c, int tb, GeoB& g) {
 
 struct Geo3 {
     int32_t hxa, hya, out_w, out_h, tiles_x, tiles_y, chunk_z, chunks_z;
+    bool vec;  // the tiles allow whole-vector rows (element-aligned buffers)
 };
 
 bool geo3(const Candidate& c, const int64_t n[3], int tb, Geo3& g) {
@@ -395,6 +409,14 @@ bool geo3(const Candidate& c, const int64_t n[3], int tb, Geo3& g) {
     g.out_w = 64 * vx - 2 * g.hxa;
     g.out_h = H - 2 * g.hya;
     if (g.out_w <= 0 || g.out_h <= 0) return false;
+    // whole-vector rows: the zero rule's edge tiles move inward, which needs
+    // the grid at least one register tile wide and high
+    g.vec = c.k3.bc == kPeriodic || (n[2] >= 64 * vx && n[1] >= H);
+    if (c.k3.bc == kPeriodic && n[2] % vx != 0) {
+        const int32_t w = wrap_strip(n[2], g.out_w, g.hxa, vx);
+        g.vec = w > 0;
+        if (g.vec) g.out_w = w;
+    }
     g.tiles_x = static_cast<int32_t>(ceil_div(n[2], g.out_w));
     g.tiles_y = static_cast<int32_t>(ceil_div(n[1], g.out_h));
     int64_t chunk = c.chunk;
@@ -712,15 +734,26 @@ std::vector<int> pass_list(int64_t steps, int tb, bool& copy) {
     return v;
 }
 
-// The whole-vector form of a 3D tiling applies to this grid (what
-// launch_pass decides per pass from the same facts).
-bool fast3(const st_plan_s* p, const Candidate& c, bool vec_ok) {
-    return vec_ok && (p->bc == kPeriodic || (p->n[2] >= 64 * c.k3.vx && p->n[1] >= static_cast<int64_t>(c.k3.k) * c.k3.nw));
+// Buffers aligned to 16 bytes and rows of whole vectors: what the LDS input
+// queue (16-byte LDS loads) and the tessellated tiling ask for; every other
+// whole-vector form takes any row length and element-aligned buffers.
+bool whole16(const st_plan_s* p, int vx, const void* a, const void* b) {
+    return p->n[2] % vx == 0 && aligned16(a) && aligned16(b);
+}
+
+// The whole-vector form of a 3D tiling applies to a pass of depth tb between
+// these buffers.
+bool fast3(const st_plan_s* p, const Candidate& c, int tb, const void* a, const void* b) {
+    if (!elem_aligned(a, p->dtype) || !elem_aligned(b, p->dtype)) return false;
+    if (c.k3.pipe >= 100 && !whole16(p, c.k3.vx, a, b)) return false;
+    Geo3 g;
+    return geo3(c, p->n, tb, g) && g.vec;
 }
 
 st_status launch_pass(const st_plan_s* p, const Candidate& c, const void* src, void* dst,
-                      const double* wcan, int tb, bool vec_ok, hipStream_t s, double* fpart = nullptr) {
+                      const double* wcan, int tb, hipStream_t s, double* fpart = nullptr) {
     hipError_t e = hipSuccess;
+    const bool elems = elem_aligned(src, p->dtype) && elem_aligned(dst, p->dtype);
     if (c.kernel == ST_KERNEL_NAIVE) {
         NaiveArgs a;
         a.src = src;
@@ -745,9 +778,7 @@ st_status launch_pass(const st_plan_s* p, const Candidate& c, const void* src, v
         // other pass of the candidate runs on box3d_kernel (same bits)
         Candidate cb = c;
         if (cb.bpipe > 0) {
-            const BoxPipeShape sh = boxpipe3d_shape(p->dtype, cb.bpipe - 1);
-            const bool ok = tb == 2 && (sh.vx % 2 != 0 || p->n[2] % sh.vx == 0) && aligned16(src) && aligned16(dst);
-            if (!ok || !geob(p, cb, tb, g)) {
+            if (tb != 2 || !elems || !geob(p, cb, tb, g)) {
                 cb.bpipe = 0;
                 cb.chunk = 0;
             }
@@ -764,6 +795,7 @@ st_status launch_pass(const st_plan_s* p, const Candidate& c, const void* src, v
         a.tiles_y = g.tiles_y;
         a.chunks_z = g.chunks_z;
         a.chunk_z = g.chunk_z;
+        a.out_w = g.out_w;
         a.tb = tb;
         for (int i = 0; i < p->npoints; ++i) a.w[i] = wcan[i];
         if (cb.bpipe > 0) {
@@ -771,10 +803,7 @@ st_status launch_pass(const st_plan_s* p, const Candidate& c, const void* src, v
             if (e != hipSuccess) return hip_fail(e, "boxpipe3d launch");
             return ST_OK;
         }
-        // whole-vector rows; under the zero rule the edge tiles move inward,
-        // which needs the grid at least one register tile wide
-        const bool fast = vec_ok && (p->bc == kPeriodic || p->n[2] >= box3d_shape(p->dtype, tb).w);
-        e = launch_box3d(p->dtype, p->bc == kPeriodic, fast, a, s);
+        e = launch_box3d(p->dtype, p->bc == kPeriodic, elems && g.vec, a, s);
         if (e != hipSuccess) return hip_fail(e, "box3d launch");
         return ST_OK;
     }
@@ -790,7 +819,7 @@ st_status launch_pass(const st_plan_s* p, const Candidate& c, const void* src, v
         a.out_w = g.out_w;
         a.halo = g.halo;
         a.tb = tb;
-        a.vec_ok = vec_ok && p->n[2] >= 64 * kStream1DVX ? 1 : 0;
+        a.vec_ok = elems && p->n[2] >= 64 * kStream1DVX ? 1 : 0;
         for (int i = 0; i < p->npoints; ++i) a.w[i] = wcan[i];
         e = launch_stream1d(p->dtype, p->radius, p->bc == kPeriodic, a, s);
         if (e != hipSuccess) return hip_fail(e, "stream1d launch");
@@ -814,7 +843,7 @@ st_status launch_pass(const st_plan_s* p, const Candidate& c, const void* src, v
         G.chunk_y = g.chunk_y;
         G.out_w = g.out_w;
         G.hxa = g.hxa;
-        G.vec_ok = (c.k2.tess ? vec_ok : g.vec && elem_aligned(src, p->dtype) && elem_aligned(dst, p->dtype)) ? 1 : 0;
+        G.vec_ok = (c.k2.tess ? whole16(p, c.k2.vx, src, dst) : elems && g.vec) ? 1 : 0;
         G.tb = tb;
         G.tile_begin = 0;
         for (int i = 0; i < p->npoints; ++i) G.w[i] = wcan[i];
@@ -847,7 +876,7 @@ st_status launch_pass(const st_plan_s* p, const Candidate& c, const void* src, v
         Geo3 g;
         if (!geo3(c, p->n, tb, g)) return fail(ST_ERR_UNSUPPORTED, "3D tiling infeasible");
         Stream3DKey key = c.k3;
-        key.fast = fast3(p, c, vec_ok) ? 1 : 0;
+        key.fast = fast3(p, c, tb, src, dst) ? 1 : 0;
         key.flux = fpart ? 1 : 0;
         if (key.pipe && (!key.fast || !stream3d_has(key))) {
             // the pipeline has whole-vector rows only (and outflow twins for
@@ -855,7 +884,7 @@ st_status launch_pass(const st_plan_s* p, const Candidate& c, const void* src, v
             // plan (same result bit for bit)
             for (const Candidate& o : p->cands)
                 if (o.kernel == ST_KERNEL_STREAM3D && !o.k3.pipe && o.k3.tbmax >= tb)
-                    return launch_pass(p, o, src, dst, wcan, tb, vec_ok, s, fpart);
+                    return launch_pass(p, o, src, dst, wcan, tb, s, fpart);
             return fail(ST_ERR_UNSUPPORTED, "no queued-plane 3D tiling for a pass of depth %d", tb);
         }
         const int lds = stream3d_lds_bytes(key);
@@ -877,7 +906,6 @@ st_status launch_pass(const st_plan_s* p, const Candidate& c, const void* src, v
         a.chunk_z = g.chunk_z;
         a.hxa = g.hxa;
         a.hya = g.hya;
-        a.vec_ok = vec_ok ? 1 : 0;
         a.tb = tb;
         for (int i = 0; i < p->npoints; ++i) a.w[i] = wcan[i];
         a.flux_part = fpart;
@@ -939,24 +967,15 @@ st_status check_flux_parts(const st_plan_s* p, int64_t need) {
 
 // Run `steps` steps with candidate c: grid -> work -> grid ...  With `flux`
 // (zero rule only), the outflow of every step is also added to flux[0].
-int cand_vx(const st_plan_s* p, const Candidate& c) {
-    return c.kernel == ST_KERNEL_STREAM2D   ? c.k2.vx
-           : c.kernel == ST_KERNEL_STREAM3D ? c.k3.vx
-           : c.kernel == ST_KERNEL_STREAM1D ? kStream1DVX
-           : c.kernel == ST_KERNEL_BOX3D    ? box3d_shape(p->dtype, 1).vx
-                                            : 1;
-}
-
 st_status run_steps(st_plan_s* p, const Candidate& c_sel, void* grid, void* work, const double* wcan,
                     int64_t steps, hipStream_t s, double* flux = nullptr) {
     // The pipeline has whole-vector rows only: on a grid that does not take
-    // them (too small, unaligned) the run uses the plan's first other
+    // them (too small) the run uses the plan's first other
     // candidate, with its own depth (every candidate gives the same bits; the
     // list always ends with the one-step kernel).
     const Candidate* pick = &c_sel;
     if (c_sel.kernel == ST_KERNEL_STREAM3D && c_sel.k3.pipe) {
-        const bool v0 = (p->n[2] % cand_vx(p, c_sel) == 0) && aligned16(grid) && aligned16(work);
-        if (!fast3(p, c_sel, v0)) {
+        if (!fast3(p, c_sel, c_sel.tb, grid, work)) {
             for (const Candidate& o : p->cands)
                 if (!(o.kernel == ST_KERNEL_STREAM3D && o.k3.pipe)) {
                     pick = &o;
@@ -965,15 +984,9 @@ st_status run_steps(st_plan_s* p, const Candidate& c_sel, void* grid, void* work
         }
     }
     const Candidate& c_in = *pick;
-    const int vx = c_in.kernel == ST_KERNEL_STREAM2D   ? c_in.k2.vx
-                   : c_in.kernel == ST_KERNEL_STREAM3D ? c_in.k3.vx
-                   : c_in.kernel == ST_KERNEL_STREAM1D ? kStream1DVX
-                   : c_in.kernel == ST_KERNEL_BOX3D    ? box3d_shape(p->dtype, 1).vx
-                                                       : 1;
-    const bool vec_ok = (p->n[2] % vx == 0) && aligned16(grid) && aligned16(work);
     // the pipeline's outflow twin has whole-vector rows only
     const bool fused = flux && flux_fused(p, c_in) &&
-                       !(c_in.kernel == ST_KERNEL_STREAM3D && c_in.k3.pipe && !fast3(p, c_in, vec_ok));
+                       !(c_in.kernel == ST_KERNEL_STREAM3D && c_in.k3.pipe && !fast3(p, c_in, c_in.tb, grid, work));
     Candidate c = c_in;
     if (flux && !fused) c.tb = 1;
     const int tb = (c.kernel == ST_KERNEL_NAIVE) ? 1 : c.tb;
@@ -1008,7 +1021,7 @@ st_status run_steps(st_plan_s* p, const Candidate& c_sel, void* grid, void* work
             if (hipError_t e = launch_flux_band(p->dtype, fb, p->flux_part, kFluxBandBlocks, s); e != hipSuccess)
                 return hip_fail(e, "outflow band launch");
         }
-        st_status r = launch_pass(p, c, src, dst, wcan, t, vec_ok, s, fused ? p->flux_part : nullptr);
+        st_status r = launch_pass(p, c, src, dst, wcan, t, s, fused ? p->flux_part : nullptr);
         if (r != ST_OK) return r;
         if (flux) {
             if (hipError_t e = launch_flux_reduce(p->flux_part, flux_parts(p, c, fused, t), flux, s); e != hipSuccess)

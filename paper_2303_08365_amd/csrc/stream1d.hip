@@ -9,10 +9,11 @@
 // the strip's ends are stale, so a strip owns its middle 64*VX - 2H cells
 // (H >= R*T_b, a multiple of VX) and neighbouring strips overlap by 2H.
 //
-// Zero rule, whole-vector rows (n % VX == 0, n >= 64*VX, 16-byte aligned):
-// the strips at the grid's ends are moved inward to start at 0 / end at n,
-// where the zero entering through DPP is exactly the ghost cell; no masks.
-// Otherwise (short or unaligned grids) cells outside [0, n) are loaded as 0
+// Zero rule, whole-vector rows (n >= 64*VX, any n: 16-byte buffer accesses
+// need the element's alignment only): the strips at the grid's ends are moved
+// inward to start at 0 / end at n, where the zero entering through DPP is
+// exactly the ghost cell; no masks.
+// Otherwise (short grids) cells outside [0, n) are loaded as 0
 // (buffer range) and set back to 0 after every step.  Periodic: strips keep
 // their place and every index wraps (lanes whose cells straddle the wrap
 // load them one by one).
@@ -34,6 +35,7 @@ struct Kern {
     static constexpr int NP = 2 * R + 1;
     static constexpr int32_t kRsrcWord3 = 0x00020000;  // gfx9: raw 32-bit data
     static constexpr int32_t kNT = 2;                  // store cache policy: non-temporal
+    static constexpr uint32_t kOut = 0x80000000u;      // past the end of any grid (below 2 GiB)
 
     static __device__ __forceinline__ TC bload1(__amdgpu_buffer_rsrc_t r, uint32_t off) {
         if constexpr (sizeof(TS) == 8) {
@@ -135,13 +137,17 @@ struct Kern {
             }
         }
         // owned cells [ofirst, olast): stores outside the range are dropped
-        TS* base = dst + ofirst;
-        const __amdgpu_buffer_rsrc_t rout =
-            __builtin_amdgcn_make_buffer_rsrc(base, 0, static_cast<uint32_t>(olast - ofirst) * sizeof(TS), kRsrcWord3);
-        const uint32_t so = static_cast<uint32_t>(xl - ofirst) * sizeof(TS);
         if constexpr (FAST) {
-            bstorev(rout, so, v);
+            // whole lanes: a lane across ofirst (the strip was moved off the
+            // lane grid) stores cells that are exact here and that the
+            // neighbouring strip stores with the same bits
+            const __amdgpu_buffer_rsrc_t rout =
+                __builtin_amdgcn_make_buffer_rsrc(dst, 0, static_cast<uint32_t>(n) * sizeof(TS), kRsrcWord3);
+            bstorev(rout, xl + VX > ofirst && xl < olast ? static_cast<uint32_t>(xl) * sizeof(TS) : kOut, v);
         } else {
+            const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(
+                dst + ofirst, 0, static_cast<uint32_t>(olast - ofirst) * sizeof(TS), kRsrcWord3);
+            const uint32_t so = static_cast<uint32_t>(xl - ofirst) * sizeof(TS);
 #pragma unroll
             for (int e = 0; e < VX; ++e) bstore1(rout, so + e * static_cast<uint32_t>(sizeof(TS)), v[e]);
         }
@@ -157,6 +163,9 @@ struct Kern {
         const int32_t olast = ofirst + a.out_w < n ? ofirst + a.out_w : n;
         int32_t X0 = ofirst - a.halo;
         if (!PER && a.vec_ok) X0 = X0 < 0 ? 0 : (X0 + W > n ? n - W : X0);
+        // periodic grids that are no multiple of VX: the last strip starts up
+        // to VX - 1 cells early, so that it ends with a whole lane
+        if (PER && a.vec_ok && olast == n) X0 -= (VX - n % VX) % VX;
         const int32_t xl = X0 + lane * VX;
         TC w[NP];
 #pragma unroll

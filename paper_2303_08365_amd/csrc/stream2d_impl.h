@@ -715,7 +715,7 @@ struct Kern {
 // instance's state takes without scratch.  (Left to itself the compiler takes
 // registers for longer schedules, down to one wave for the 25-point boxes.)
 constexpr int min_waves(int radius, int cls, int tbmax, int bytes, bool tess) {
-    if (radius == 2) return tbmax < 4 ? 4 : (cls == kBox || tess ? 2 : 3);
+    if (radius == 2) return tbmax < 4 ? 4 : (cls == kBox && tess && bytes == 8 ? 1 : (cls == kBox || tess ? 2 : 3));
     return tbmax < 8 ? (tess ? 3 : 4) : (cls == kBox && bytes != 4 ? 2 : 3);
 }
 

@@ -37,9 +37,13 @@
 // place and every index wraps.  A z chunk [zs, ze) streams planes
 // zs - R*tb .. ze - 1 + R*tb.
 //
-// FAST = whole-vector row access (nx % VX == 0, 16-byte aligned base, and
-// under the zero rule nx >= 64*VX, ny >= NW*K); otherwise every element is
-// loaded and stored on its own, with the same arithmetic.
+// FAST = whole-vector row access: under the zero rule nx >= 64*VX, ny >= NW*K,
+// under the periodic rule VX divides nx or the planner found tiles that put
+// the wrap between two lanes; otherwise every element is loaded and stored on
+// its own, with the same arithmetic.  Buffer accesses of 8 and 16 bytes need
+// the element's alignment only, so any row length and base will do; a tile
+// moved off the lane grid overlaps its neighbour by less than a lane and
+// stores the same bits there.
 #pragma once
 
 #include <utility>
@@ -95,8 +99,9 @@ struct Kern {
         uint32_t xr_off;               // byte offset of the x-ring element in its plane
         bool xr_xg;                    // that element is an x ghost (zero rule)
         TS* dstg;                      // output grid (buffer stores)
-        uint32_t so;                   // byte offset of this lane's first column from ox0
-        uint32_t out_bytes;            // bytes of one output row of the tile
+        int32_t obase;                 // stores: column the descriptor of an output row starts at,
+        uint32_t so;                   // lane offset from it (kOut: not an output lane),
+        uint32_t out_bytes;            // its range
         int lane, wave;
         TC w[NP];
         double* fpart;                 // FLX: this wave's partial outflow slot
@@ -115,6 +120,7 @@ struct Kern {
     // grid.  Periodic indices arrive wrapped.
     static constexpr int32_t kRsrcWord3 = 0x00020000;  // gfx9: raw 32-bit data
     static constexpr int32_t kNT = 2;                  // store cache policy: non-temporal
+    static constexpr uint32_t kOut = 0x80000000u;      // past the end of any row
     static __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const Ctx& c, int32_t zz, int32_t y) {
         const bool out = ghost(zz, c.nz) || ghost(y, c.ny);
         const TS* base = out ? c.src : c.src + static_cast<int64_t>(zz) * c.plane_elems + y * c.nx;
@@ -339,7 +345,7 @@ struct Kern {
         for (int k = 0; k < K; ++k) {
             const int32_t y = c.yw + k;
             const bool ok = zok && static_cast<uint32_t>(y - c.oy0) < static_cast<uint32_t>(c.oy1 - c.oy0);
-            TS* base = ok ? c.dstg + static_cast<int64_t>(z) * c.plane_elems + y * c.nx + c.ox0 : c.dstg;
+            TS* base = ok ? c.dstg + static_cast<int64_t>(z) * c.plane_elems + y * c.nx + c.obase : c.dstg;
             const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(base, 0, ok ? c.out_bytes : 0, kRsrcWord3);
             if constexpr (FAST) {
                 bstorev(r, c.so, out[k]);
@@ -570,6 +576,10 @@ struct Kern {
             c.X0 = c.X0 < 0 ? 0 : (c.X0 + W > c.nx ? c.nx - W : c.X0);
             c.Y0 = c.Y0 < 0 ? 0 : (c.Y0 + H > c.ny ? c.ny - H : c.Y0);
         }
+        // periodic rows that are no multiple of VX: the tile that ends at the
+        // row's end starts up to VX - 1 columns early, so that the wrap falls
+        // between two lanes
+        if (PER && FAST && c.ox1 == c.nx) c.X0 -= (VX - c.nx % VX) % VX;
         c.xl = c.X0 + c.lane * VX;
         c.yw = c.Y0 + c.wave * K;
         {
@@ -611,8 +621,18 @@ struct Kern {
             c.xr_xg = ghost(c.xr_x, c.nx);
         }
         c.dstg = static_cast<TS*>(a.dst);
-        c.so = static_cast<uint32_t>(c.xl - c.ox0) * sizeof(TS);
-        c.out_bytes = static_cast<uint32_t>(c.ox1 - c.ox0) * sizeof(TS);
+        if constexpr (FAST) {
+            // whole lanes through the whole row: a lane across ox0 (the tile
+            // was moved off the lane grid) stores columns that are exact here
+            // and that the neighbouring tile stores with the same bits
+            c.obase = 0;
+            c.out_bytes = c.row_bytes;
+            c.so = c.xl + VX > c.ox0 && c.xl < c.ox1 ? static_cast<uint32_t>(c.xl) * sizeof(TS) : kOut;
+        } else {
+            c.obase = c.ox0;
+            c.out_bytes = static_cast<uint32_t>(c.ox1 - c.ox0) * sizeof(TS);
+            c.so = static_cast<uint32_t>(c.xl - c.ox0) * sizeof(TS);
+        }
         c.zs = cz * a.chunk_z;
         c.ze = c.zs + a.chunk_z < c.nz ? c.zs + a.chunk_z : c.nz;
 #pragma unroll

@@ -84,3 +84,46 @@ def test_2d_rows_of_any_length(dtype, bc, pattern, radius):
         naive.run(ref, list(w), 5)
         torch.cuda.synchronize()
         assert np.array_equal(to_host(g), to_host(ref)), f"{dtype} {bc} nx {nx}: element-aligned buffers"
+
+
+# 3D rows whose length the lane width does not divide, in whole vectors: grids
+# one register tile wide and high or a little more (64 lanes x 2 or 4 columns,
+# 24 to 64 rows), several tiles, periodic rows too short for two tiles
+@pytest.mark.parametrize("dtype", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("bc", ["zero", "periodic"])
+@pytest.mark.parametrize("pattern,radius", [("star", 1), ("star", 4), ("box", 1)])
+def test_3d_rows_of_any_length(dtype, bc, pattern, radius):
+    import paper_2303_08365_amd as st
+    import torch
+    from gpu_helpers import to_host
+    offs = (synth.star_offsets if pattern == "star" else synth.box_offsets)(3, radius)
+    w = _weights(offs, 35, dtype)
+    for nz, ny, nx in [(5, 33, 45), (9, 64, 129), (7, 49, 193), (10, 66, 257), (3, 35, 259), (6, 65, 395)]:
+        shape = (nz, ny, nx)
+        u0 = synth.uniform_field(shape, seed=nx)
+        plan, naive = st.Plan(offs, shape, dtype, bc), st.Plan(offs, shape, dtype, bc, naive=True)
+        forms = {(c["kernel"], c["tb"], c["block"], c["tile_x"], c["tile_y"], c["pipeline"]): k
+                 for k, c in reversed(list(enumerate(plan.candidates()))) if c["kernel"] != st.KERNEL_NAIVE}
+        for form, k in sorted(forms.items()):
+            _against_naive(plan, naive, u0, offs, w, 2 * form[1], bc, dtype, {"variant": k}, f"{dtype} {bc} {shape} {form}")
+        g, work, ref = _offset_view(u0, dtype), _offset_view(u0, dtype), _offset_view(u0, dtype)
+        plan.run(g, list(w), 5, work=work)
+        naive.run(ref, list(w), 5)
+        torch.cuda.synchronize()
+        assert np.array_equal(to_host(g), to_host(ref)), f"{dtype} {bc} {shape}: element-aligned buffers"
+
+
+# 1D grids whose length the 16 cells of a lane do not divide: one strip (1024
+# cells) and a little more, the last strip short, each fused depth
+@pytest.mark.parametrize("dtype", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("bc", ["zero", "periodic"])
+@pytest.mark.parametrize("radius", [1, 2])
+def test_1d_any_length(dtype, bc, radius):
+    import paper_2303_08365_amd as st
+    offs = synth.star_offsets(1, radius)
+    w = _weights(offs, 37, dtype)
+    for n in [1023, 1024, 1025, 1039, 1793, 1923, 2049, 5003]:
+        u0 = synth.uniform_field((n,), seed=n)
+        plan, naive = st.Plan(offs, (n,), dtype, bc), st.Plan(offs, (n,), dtype, bc, naive=True)
+        for k, c in enumerate(plan.candidates()):
+            _against_naive(plan, naive, u0, offs, w, 2 * c["tb"] + 1, bc, dtype, {"variant": k}, f"{dtype} {bc} n {n} tb {c['tb']}")
