@@ -25,8 +25,9 @@ struct NaiveArgs {
     int32_t bc;
     int32_t off[kMaxPoints][3];  // canonical order, centre first
     double w[kMaxPoints];        // weights already rounded to compute precision
+    int64_t lin[kMaxPoints];     // filled by launch_naive: elements from a row to point p's row
 };
-hipError_t launch_naive(int dtype, const NaiveArgs& a, hipStream_t s);
+hipError_t launch_naive(int dtype, NaiveArgs& a, hipStream_t s);
 
 // ----------------------------------------------------------------------------
 // 2D: rows streamed through registers, T_b fused steps per pass

@@ -127,3 +127,22 @@ def test_1d_any_length(dtype, bc, radius):
         plan, naive = st.Plan(offs, (n,), dtype, bc), st.Plan(offs, (n,), dtype, bc, naive=True)
         for k, c in enumerate(plan.candidates()):
             _against_naive(plan, naive, u0, offs, w, 2 * c["tb"] + 1, bc, dtype, {"variant": k}, f"{dtype} {bc} n {n} tb {c['tb']}")
+
+
+# the one-step kernel: rows of one, two and four columns a lane with remainders,
+# point counts that leave every kind of last batch, offsets of a whole extent
+# and beyond it under the periodic rule
+@pytest.mark.parametrize("dtype", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("bc", ["zero", "periodic"])
+@pytest.mark.parametrize("npoints", [1, 2, 15, 17, 33, 125])
+def test_one_step_kernel_rows_and_batches(dtype, bc, npoints):
+    import paper_2303_08365_amd as st
+    box = synth.box_offsets(3, 2)
+    far = [(4, 0, 0), (0, -4, 0), (0, 0, 4), (-3, 2, -4)]
+    offs = (box if npoints == 125 else box[:1] + (far + box[1:])[:npoints - 1])
+    w = _weights(offs, 39, dtype)
+    for shape in [(3, 5, 1), (2, 3, 63), (4, 6, 64), (5, 4, 65), (1, 9, 129), (6, 2, 257), (4, 4, 515)]:
+        u0 = synth.uniform_field(shape, seed=shape[2])
+        print(f"one step {dtype} {bc} {npoints} points {shape}", flush=True)
+        got, _ = gpu_sweep(u0, offs, w, 3, bc, dtype, plan=st.Plan(offs, shape, dtype, bc, naive=True))
+        check(got, oracle_ref(u0, offs, w, 3, bc, dtype), dtype, 3, f"{shape}")
