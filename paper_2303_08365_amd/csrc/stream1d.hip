@@ -18,6 +18,13 @@
 // their place and every index wraps (lanes whose cells straddle the wrap
 // load them one by one).
 //
+// What bounds it.  10^7 FP64 cells, 3 points: 32 steps a pass move 160 MB and
+// take 44 us (HBM; 3.6 TB/s), 64 steps 78 us (vector ALU: 96 multiply/FMA of 104
+// instructions for two steps).  Loading and storing a lane's 16 cells straight
+// from its registers, 16 bytes of 64 different lines per instruction, took 171
+// us at any depth up to 32: hence the piece order through LDS.  One step a loop
+// trip copied 15 values a step (32 steps 50 us, 64 steps 92).
+//
 // Canonical point order: centre, then offsets -R..-1, +1..+R, one multiply
 // then an FMA chain -- the same arithmetic as the one-step kernel, so every
 // depth gives the same bits.
@@ -46,18 +53,6 @@ struct Kern {
             return bf16_to_f32(__builtin_amdgcn_raw_buffer_load_b16(r, off, 0, 0));
         }
     }
-    static __device__ __forceinline__ void bloadv(__amdgpu_buffer_rsrc_t r, uint32_t off, TC (&v)[VX]) {
-        constexpr int kBytes = VX * static_cast<int>(sizeof(TS));
-        static_assert(kBytes % 16 == 0, "whole 16-byte units per lane");
-        TS vals[VX];
-        u32x4 raw[kBytes / 16];
-#pragma unroll
-        for (int i = 0; i < kBytes / 16; ++i)
-            raw[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off + 16 * i, 0, 0));
-        __builtin_memcpy(vals, raw, kBytes);
-#pragma unroll
-        for (int e = 0; e < VX; ++e) v[e] = S::widen(vals[e]);
-    }
     static __device__ __forceinline__ void bstore1(__amdgpu_buffer_rsrc_t r, uint32_t off, TC v) {
         const TS x = S::narrow(v);
         if constexpr (sizeof(TS) == 8) {
@@ -68,15 +63,54 @@ struct Kern {
             __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, x), r, off, 0, kNT);
         }
     }
-    static __device__ __forceinline__ void bstorev(__amdgpu_buffer_rsrc_t r, uint32_t off, const TC (&v)[VX]) {
-        constexpr int kBytes = VX * static_cast<int>(sizeof(TS));
+    // A strip between memory and the lanes' registers.  In memory order lane L
+    // moves the 16-byte pieces L, 64 + L, ..., whole lines per instruction; a
+    // lane's cells are CH consecutive pieces.  The two orders meet in LDS,
+    // each wave in its own 64*VX cells; piece j of lane L lies at slot
+    // j ^ swz(L) of the lane's CH, so that the 16 lanes an LDS cycle serves read
+    // 16 different 16-byte columns.
+    static constexpr int CH = VX * static_cast<int>(sizeof(TS)) / 16;  // pieces per lane
+    static constexpr int CE = 16 / static_cast<int>(sizeof(TS));       // cells per piece
+    static_assert(CH >= 1 && CH <= 16 && (CH & (CH - 1)) == 0, "a power of two of 16-byte pieces per lane");
+    static __device__ __forceinline__ int slot(int piece) {
+        const int l = piece / CH, j = piece % CH;
+        return l * CH + (j ^ ((l / (16 / CH)) & (CH - 1)));
+    }
+    // pieces of the strip that starts at byte offset b0, all inside the range
+    static __device__ __forceinline__ void load_strip(__amdgpu_buffer_rsrc_t r, uint32_t b0, int lane, u32x4* lds,
+                                                      TC (&v)[VX]) {
+        u32x4 raw[CH];
+#pragma unroll
+        for (int i = 0; i < CH; ++i)
+            raw[i] = __builtin_bit_cast(
+                u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, b0 + 16u * static_cast<uint32_t>(i * 64 + lane), 0, 0));
+#pragma unroll
+        for (int i = 0; i < CH; ++i) lds[slot(i * 64 + lane)] = raw[i];
+#pragma unroll
+        for (int j = 0; j < CH; ++j) raw[j] = lds[slot(lane * CH + j)];
+        TS vals[VX];
+        __builtin_memcpy(vals, raw, sizeof(raw));
+#pragma unroll
+        for (int e = 0; e < VX; ++e) v[e] = S::widen(vals[e]);
+    }
+    // stores the pieces that reach into [ofirst, olast); X0: the strip's first cell
+    static __device__ __forceinline__ void store_strip(__amdgpu_buffer_rsrc_t r, int32_t X0, int32_t ofirst,
+                                                       int32_t olast, int lane, u32x4* lds, const TC (&v)[VX]) {
         TS vals[VX];
 #pragma unroll
         for (int e = 0; e < VX; ++e) vals[e] = S::narrow(v[e]);
-        u32x4 raw[kBytes / 16];
-        __builtin_memcpy(raw, vals, kBytes);
+        u32x4 raw[CH];
+        __builtin_memcpy(raw, vals, sizeof(raw));
 #pragma unroll
-        for (int i = 0; i < kBytes / 16; ++i) __builtin_amdgcn_raw_buffer_store_b128(raw[i], r, off + 16 * i, 0, kNT);
+        for (int j = 0; j < CH; ++j) lds[slot(lane * CH + j)] = raw[j];
+#pragma unroll
+        for (int i = 0; i < CH; ++i) raw[i] = lds[slot(i * 64 + lane)];
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const int32_t x = X0 + (i * 64 + lane) * CE;
+            const uint32_t o = x + CE > ofirst && x < olast ? static_cast<uint32_t>(x) * static_cast<uint32_t>(sizeof(TS)) : kOut;
+            __builtin_amdgcn_raw_buffer_store_b128(raw[i], r, o, 0, kNT);
+        }
     }
 
     // One step on the strip.  left[j] is cell xl - R + j (lane L-1's cell
@@ -102,19 +136,19 @@ struct Kern {
     }
 
     template <bool FAST>
-    static __device__ __forceinline__ void body(const Stream1DArgs& a, int32_t n, int32_t xl, int32_t ofirst,
-                                                int32_t olast, int tb, const TC (&w)[NP]) {
+    static __device__ __forceinline__ void body(const Stream1DArgs& a, int32_t n, int32_t X0, int lane, int32_t ofirst,
+                                                int32_t olast, int tb, const TC (&w)[NP], u32x4* lds) {
+        const int32_t xl = X0 + lane * VX;
         const TS* src = static_cast<const TS*>(a.src);
         TS* dst = static_cast<TS*>(a.dst);
         const __amdgpu_buffer_rsrc_t rin =
             __builtin_amdgcn_make_buffer_rsrc(const_cast<TS*>(src), 0, static_cast<uint32_t>(n) * sizeof(TS), kRsrcWord3);
         TC v[VX];
-        if constexpr (FAST && !PER) {
-            bloadv(rin, static_cast<uint32_t>(xl) * sizeof(TS), v);
-        } else if constexpr (FAST) {
-            if (xl >= 0 && xl + VX <= n) {
-                bloadv(rin, static_cast<uint32_t>(xl) * sizeof(TS), v);
+        if constexpr (FAST) {
+            if (!PER || (X0 >= 0 && X0 + W <= n)) {
+                load_strip(rin, static_cast<uint32_t>(X0) * sizeof(TS), lane, lds, v);
             } else {
+                // a strip across the periodic wrap: cell by cell
 #pragma unroll
                 for (int e = 0; e < VX; ++e) v[e] = bload1(rin, static_cast<uint32_t>(wrap_idx(xl + e, n)) * sizeof(TS));
             }
@@ -124,26 +158,36 @@ struct Kern {
             for (int e = 0; e < VX; ++e)
                 v[e] = bload1(rin, static_cast<uint32_t>(PER ? wrap_idx(xl + e, n) : xl + e) * sizeof(TS));
         }
-        for (int t = 0; t < tb; ++t) {
-            TC out[VX];
-            step(w, v, out);
-            const bool last = t + 1 == tb;
+        // two steps a trip, from v to u and back: one step's results could only
+        // take the place of its inputs through a copy of each
+        const auto advance = [&](const TC (&in)[VX], TC (&out)[VX]) {
+            step(w, in, out);
 #pragma unroll
             for (int e = 0; e < VX; ++e) {
-                TC o = out[e];
-                if constexpr (!FAST && !PER) o = static_cast<uint32_t>(xl + e) >= static_cast<uint32_t>(n) ? TC(0) : o;
-                // bfloat16 storage rounds every step (the store rounds the last)
-                v[e] = last ? o : S::round(o);
+                if constexpr (!FAST && !PER) out[e] = static_cast<uint32_t>(xl + e) >= static_cast<uint32_t>(n) ? TC(0) : out[e];
+                out[e] = S::round(out[e]);  // bfloat16 storage rounds every step
             }
+        };
+        int t = 0;
+        for (; t + 2 <= tb; t += 2) {
+            TC u[VX];
+            advance(v, u);
+            advance(u, v);
+        }
+        if (t < tb) {
+            TC u[VX];
+            advance(v, u);
+#pragma unroll
+            for (int e = 0; e < VX; ++e) v[e] = u[e];
         }
         // owned cells [ofirst, olast): stores outside the range are dropped
         if constexpr (FAST) {
-            // whole lanes: a lane across ofirst (the strip was moved off the
-            // lane grid) stores cells that are exact here and that the
+            // whole pieces: one across ofirst (the strip was moved off the
+            // piece grid) holds cells that are exact here and that the
             // neighbouring strip stores with the same bits
             const __amdgpu_buffer_rsrc_t rout =
                 __builtin_amdgcn_make_buffer_rsrc(dst, 0, static_cast<uint32_t>(n) * sizeof(TS), kRsrcWord3);
-            bstorev(rout, xl + VX > ofirst && xl < olast ? static_cast<uint32_t>(xl) * sizeof(TS) : kOut, v);
+            store_strip(rout, X0, ofirst, olast, lane, lds, v);
         } else {
             const __amdgpu_buffer_rsrc_t rout = __builtin_amdgcn_make_buffer_rsrc(
                 dst + ofirst, 0, static_cast<uint32_t>(olast - ofirst) * sizeof(TS), kRsrcWord3);
@@ -153,7 +197,7 @@ struct Kern {
         }
     }
 
-    static __device__ __forceinline__ void run(const Stream1DArgs& a) {
+    static __device__ __forceinline__ void run(const Stream1DArgs& a, u32x4* lds) {
         const int lane = threadIdx.x & 63;
         const int64_t strip = __builtin_amdgcn_readfirstlane(
             static_cast<int>(xcd_remap(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6)));
@@ -166,18 +210,18 @@ struct Kern {
         // periodic grids that are no multiple of VX: the last strip starts up
         // to VX - 1 cells early, so that it ends with a whole lane
         if (PER && a.vec_ok && olast == n) X0 -= (VX - n % VX) % VX;
-        const int32_t xl = X0 + lane * VX;
         TC w[NP];
 #pragma unroll
         for (int p = 0; p < NP; ++p) w[p] = static_cast<TC>(a.w[p]);
-        if (a.vec_ok) body<true>(a, n, xl, ofirst, olast, a.tb, w);
-        else body<false>(a, n, xl, ofirst, olast, a.tb, w);
+        if (a.vec_ok) body<true>(a, n, X0, lane, ofirst, olast, a.tb, w, lds + (threadIdx.x >> 6) * (64 * CH));
+        else body<false>(a, n, X0, lane, ofirst, olast, a.tb, w, lds);
     }
 };
 
 template <typename TS, int R, int VX, bool PER>
 __global__ __launch_bounds__(256) void stream1d_kernel(const Stream1DArgs a) {
-    Kern<TS, R, VX, PER>::run(a);
+    __shared__ u32x4 lds[4 * 64 * Kern<TS, R, VX, PER>::CH];
+    Kern<TS, R, VX, PER>::run(a, lds);
 }
 
 template <typename TS, int R, int VX, bool PER>
