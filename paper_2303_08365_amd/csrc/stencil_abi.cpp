@@ -156,6 +156,7 @@ struct Candidate {
     int32_t chunk = 0;  // y chunk (2D) or z chunk (3D); 0 = automatic
     int32_t occ = 0;    // resident work-groups per CU (0 = unknown: assume 2)
     int32_t bpipe = 0;  // ST_KERNEL_BOX3D, two steps: 0 = box3d_kernel, v + 1 = boxpipe3d variant v
+    int32_t auto_chunk = 0;  // the time model's chunk at depth tb (chunk == 0; 0: not asked yet)
 };
 
 struct BatchGrid {
@@ -178,6 +179,10 @@ struct st_plan_s {
     int32_t cls = kGeneral;
     std::vector<Candidate> cands;
     int32_t sel = 0;
+    // the selection is the time model's own (not the caller's, the
+    // autotuner's or the environment's), and it puts one step per launch
+    // before the selected tiling: the grid is too small for tiles
+    bool modelled = false, one_step = false;
     // Device memory a plan owns is allocated when the plan is made (see
     // plan_buffers), never by a run call.
     void* owned_work = nullptr;   // ST_PLAN_OWN_WORK
@@ -241,6 +246,83 @@ void classify(st_plan_s* p) {
     if (p->npoints == box_n) p->cls = kBox;  // points are distinct and within radius r
 }
 
+// ---------------------------------------------------------------------------
+// time model of a pass: picks chunk lengths, and the depth and tiling of plans
+// that are not autotuned
+// ---------------------------------------------------------------------------
+// A pass costs its launch (with the first loads and the last stores), then
+// about the larger of two times: of the iterations (rows or planes) its waves walk, and
+// of the bytes.  An iteration costs a lone wave its latency, `lat`, and a SIMD
+// the issue time of its vector instructions, `thr`, for every wave it holds.
+// Fitted on MI355X to 5400 two-dimensional passes (256^2 .. 8192^2, 4 to 256
+// rows a chunk, every depth, pattern and type: 10 % mean error, the choice 3 %
+// from the best of the sweep on average, 26 % at most) and to 7900
+// three-dimensional ones (48^3 .. 251 x 319 x 377: 4 to 12 % for the
+// pipelines, 10 % for boxes, 19 % for queued planes; choice 3 to 5 % from the
+// best).  The fixed depths and the fill rule before it: 512^2 FP64 4 steps x 25
+// rows 15 us a pass, now 8 x 4 rows in 11; 89 x 97 x 101 FP32 4 x 23 planes 77 us,
+// now one-step launches of 8; 10^7 1D cells 64 steps instead of 32.
+constexpr double kUsPerInstr = 4.0 / 2400.0;  // a wave's vector instruction: 4 clocks at 2.4 GHz
+
+// `groups` work-groups, `occ` resident per CU, each walking `nit` iterations.
+double walk_us(double groups, int occ, double nit, double lat, double thr) {
+    const double q = groups / device_cus();
+    if (q > 2.0 * occ) return nit * (std::max(lat / occ, thr) * q + 0.8 * lat);  // many rounds even out
+    const double full = std::floor(q / occ), rem = std::ceil(q - full * occ - 1e-9);
+    // rounds overlap a little, more where a CU holds several work-groups
+    return (q > occ ? (occ > 1 ? 0.93 : 0.97) : 1.0) * nit * (full * std::max(lat, occ * thr) + (rem > 0 ? std::max(lat, rem * thr) : 0.0));
+}
+
+// Bytes over the bandwidth (`tbs` TB/s with `enough` waves a SIMD) that
+// `groups` work-groups of `waves` waves, `occ` resident per CU, keep busy.
+double bytes_us(double bytes, double tbs, double enough, double groups, int occ, int waves) {
+    const double w = std::min(groups / device_cus(), static_cast<double>(occ)) * waves / 4;
+    return bytes / (tbs * 1e6 * std::pow(std::min(1.0, w / enough), 0.2));
+}
+
+// Where the two come near each other both are felt.
+double both_us(double a, double b) { return std::sqrt(std::sqrt(a * a * a * a + b * b * b * b)); }
+
+// The chunk length (extent n, at least `least`) that the model finds fastest; a
+// shorter one has to be 2 % better (well inside the model's error).
+template <typename F>
+int64_t best_chunk(int64_t n, int64_t least, const F& us) {
+    int64_t best = n, last = 0;
+    double best_us = 1e300;
+    for (int64_t c = 1; c <= n; c += std::max<int64_t>(1, c / 16)) {
+        const int64_t chunk = (n + c - 1) / c;
+        if (chunk < least && c > 1) break;
+        if (chunk == last) continue;
+        last = chunk;
+        const double v = us(chunk);
+        if (v < best_us * 0.98) {
+            best_us = v;
+            best = chunk;
+        }
+    }
+    return best;
+}
+
+// 2D rows (4 waves a work-group, one per SIMD): `items` strips x chunks of at
+// most `nit` rows, `streamed` cells read and `cells` written.
+double rows_us(const Candidate& c, int tb, int64_t items, int64_t nit, double streamed, double cells) {
+    const int vx = c.k2.vx, R = c.k2.radius, dw = c.k2.dtype == kF64 ? 2 : 1;
+    const int points = c.k2.cls == kStar ? 4 * R + 1 : (2 * R + 1) * (2 * R + 1);
+    const double us = kUsPerInstr * (tb * (vx * points + 2 * R * dw) + 12);
+    const double rnd = c.k2.dtype == kBF16 ? kUsPerInstr * tb * 2 * vx : 0.0;  // bfloat16 rounds every level
+    const double groups = static_cast<double>(ceil_div(items, 4));
+    const int occ = c.occ > 0 ? c.occ : 2;
+    return 4.0 + both_us(walk_us(groups, occ, static_cast<double>(nit), 0.075 + 1.18 * (us + 2 * rnd), 1.08 * (us + rnd)),
+                         bytes_us(elem_bytes(c.k2.dtype) * (streamed + cells), 5.2, 3.0, groups, occ, 4));
+}
+
+// 3D planes: a pass over `grid` bytes in chunks of `chunk` planes, `nit` with
+// the halo (the tiles' xy halos come from L2).
+double planes_us(double launch, double tbs, double groups, int occ, int waves, double nit, double chunk, double lat, double thr,
+                 double grid) {
+    return launch + both_us(walk_us(groups, occ, nit, lat, thr), bytes_us(grid * (nit / chunk + 1.0), tbs, 2.0, groups, occ, waves));
+}
+
 // Geometry of one 2D pass for a grid.
 struct Geo2 {
     int32_t hxa, out_w, tiles_x, chunk_y, chunks_y;
@@ -263,6 +345,12 @@ int32_t wrap_strip(int64_t nx, int32_t out_w, int32_t hxa, int vx) {
     for (; w >= least; w -= vx)
         if (w < nx && nx % w >= least) return w;
     return 0;
+}
+
+double rows2_us(const Candidate& c, int64_t ny, int64_t nx, int tb, int64_t tiles_x, int64_t chunk) {
+    const int64_t chunks = ceil_div(ny, chunk), halo = 2 * static_cast<int64_t>(c.k2.radius) * tb;
+    return rows_us(c, tb, tiles_x * chunks, std::min(chunk, ny) + halo,
+                   static_cast<double>(nx) * static_cast<double>(ny + chunks * halo), static_cast<double>(nx) * static_cast<double>(ny));
 }
 
 bool geo2(const Candidate& c, int64_t ny, int64_t nx, int tb, Geo2& g, int64_t chunk_override = 0) {
@@ -301,9 +389,9 @@ bool geo2(const Candidate& c, int64_t ny, int64_t nx, int tb, Geo2& g, int64_t c
     }
     g.tiles_x = static_cast<int32_t>(ceil_div(nx, g.out_w));
     int64_t chunk = chunk_override > 0 ? chunk_override : c.chunk;
+    if (chunk <= 0 && tb == c.tb) chunk = c.auto_chunk;
     if (chunk <= 0)
-        chunk = pick_chunk(ny, g.tiles_x, wave_capacity2(c), 2 * static_cast<int64_t>(R) * tb,
-                           std::max<int64_t>(8, 2 * R * tb));
+        chunk = best_chunk(ny, 4, [&](int64_t len) { return rows2_us(c, ny, nx, tb, g.tiles_x, len); });
     chunk = std::min<int64_t>(chunk, ny);
     g.chunk_y = static_cast<int32_t>(chunk);
     g.chunks_y = static_cast<int32_t>(ceil_div(ny, chunk));
@@ -342,6 +430,27 @@ struct GeoB {
     bool vec;       // the tiles allow whole-vector rows (element-aligned buffers)
 };
 
+double box_us(const st_plan_s* p, const Candidate& c, int tb, int64_t per_plane, int64_t chunk) {
+    const int64_t chunks = ceil_div(p->n[0], chunk);
+    const double groups = static_cast<double>(per_plane) * static_cast<double>(chunks);
+    const int dw = p->dtype == kF64 ? 2 : 1, esz = elem_bytes(p->dtype);
+    const double grid = static_cast<double>(plan_cells(p)) * esz, len = static_cast<double>(std::min(chunk, p->n[0]));
+    if (c.bpipe > 0 && tb == 2) {
+        const BoxPipeShape sh = boxpipe3d_shape(p->dtype, c.bpipe - 1);
+        const double us = kUsPerInstr * (2 * sh.k * sh.vx * (27 + (p->dtype == kBF16 ? 2 : 0)) + 4 * (sh.k + 2) * 2 * dw);
+        return planes_us(3.7, 4.8, groups, 1, sh.block / 64, len + 5, len,
+                         (0.8 + 1.83 * us) * (p->dtype == kF64 ? 1.0 : 1.1), 0.0, grid);
+    }
+    const Box3DShape sh = box3d_shape(p->dtype, tb);
+    const int waves = sh.block / 64, k = sh.h / waves;
+    int rows = 0;
+    for (int l = 0; l < tb; ++l) rows += k + 2 * (tb - 1 - l);
+    // (two steps FP64 measured well over the fit of the others: registers)
+    const double us = kUsPerInstr * (rows * sh.vx * (27 + (p->dtype == kBF16 ? 2 : 0)) + 6 * (k + 2 * tb) * dw * tb) *
+                      (tb == 2 && p->dtype == kF64 ? 1.7 : 1.0);
+    return planes_us(7.0, 5.5, groups, tb == 1 ? 2 : 1, waves, len + 2 * tb, len, 0.54 + 1.42 * us, 1.22 * us * waves / 4, grid);
+}
+
 // 3D boxes: tiles of out_w x h owned cells (the register tile is 64*VX wide;
 // with two steps per pass neighbouring tiles overlap by whole lanes), z
 // chunks sized to fill the device; 32-bit plane offsets.
@@ -362,7 +471,8 @@ bool geob(const st_plan_s* p, const Candidate& c, int tb, GeoB& g) {
         g.tiles_y = static_cast<int32_t>(ceil_div(n[1], sh.out_h));
         const int64_t per_plane = static_cast<int64_t>(g.tiles_x) * g.tiles_y;
         int64_t chunk = c.chunk;
-        if (chunk <= 0) chunk = pick_chunk(n[0], per_plane, static_cast<int64_t>(device_cus()), 5, 8);
+        if (chunk <= 0) chunk = c.auto_chunk;
+        if (chunk <= 0) chunk = best_chunk(n[0], 4, [&](int64_t len) { return box_us(p, c, tb, per_plane, len); });
         chunk = std::min<int64_t>(chunk, n[0]);
         g.chunk_z = static_cast<int32_t>(chunk);
         g.chunks_z = static_cast<int32_t>(ceil_div(n[0], chunk));
@@ -382,11 +492,27 @@ bool geob(const st_plan_s* p, const Candidate& c, int tb, GeoB& g) {
     g.tiles_y = static_cast<int32_t>(ceil_div(n[1], sh.h));
     const int64_t per_plane = static_cast<int64_t>(g.tiles_x) * g.tiles_y;
     int64_t chunk = c.chunk;
-    if (chunk <= 0) chunk = pick_chunk(n[0], per_plane, static_cast<int64_t>(device_cus()) * 4, 2 * tb, 8);
+    if (chunk <= 0 && tb == c.tb && c.bpipe == 0) chunk = c.auto_chunk;
+    if (chunk <= 0) chunk = best_chunk(n[0], 4, [&](int64_t len) { return box_us(p, c, tb, per_plane, len); });
     chunk = std::min<int64_t>(chunk, n[0]);
     g.chunk_z = static_cast<int32_t>(chunk);
     g.chunks_z = static_cast<int32_t>(ceil_div(n[0], chunk));
     return per_plane * g.chunks_z < (int64_t(1) << 31);
+}
+
+double star3_us(const Candidate& c, const int64_t n[3], int tb, int64_t per_plane, int64_t chunk, bool vec) {
+    const int R = c.k3.radius, K = c.k3.k, vx = c.k3.vx, dw = c.k3.dtype == kF64 ? 2 : 1, esz = elem_bytes(c.k3.dtype);
+    const double groups = static_cast<double>(per_plane) * static_cast<double>(ceil_div(n[0], chunk));
+    const double len = static_cast<double>(std::min(chunk, n[0])), nit = len + 2 * R * tb;
+    const double grid = static_cast<double>(n[0]) * static_cast<double>(n[1]) * static_cast<double>(n[2]) * esz;
+    const double us = kUsPerInstr * (tb * K * (vx * (6 * R + 1 + (c.k3.dtype == kBF16 ? 2 : 0)) + 2 * R * dw) + 8 * K);
+    if (c.k3.pipe) return planes_us(3.9, 4.8, groups, 1, c.k3.nw, nit, len, 0.8 + 1.88 * us, 0.0, grid);
+    if (R > 1) {  // one step; the loads of the halo rows set the pace
+        const double lat = c.k3.dtype == kF64 ? 1.85 : (c.k3.dtype == kF32 ? 1.5 : 1.35);
+        return planes_us(4.0, 5.4, groups, 1, c.k3.nw, nit, len, lat * (vec ? 1.0 : 1.2), 0.0, grid);
+    }
+    return planes_us(7.7, 5.4, groups, c.occ > 0 ? c.occ : 1, c.k3.nw, nit, len, (0.8 + 1.6 * us) * (vec ? 1.0 : 1.2),
+                     2.46 * us * c.k3.nw / 4, grid);
 }
 
 struct Geo3 {
@@ -421,15 +547,80 @@ bool geo3(const Candidate& c, const int64_t n[3], int tb, Geo3& g) {
     g.tiles_y = static_cast<int32_t>(ceil_div(n[1], g.out_h));
     int64_t chunk = c.chunk;
     const int64_t per_plane = static_cast<int64_t>(g.tiles_x) * g.tiles_y;
-    if (chunk <= 0) {
-        const int64_t cap = static_cast<int64_t>(device_cus()) * (c.occ > 0 ? c.occ : 2);
-        chunk = pick_chunk(n[0], per_plane, cap, 2 * static_cast<int64_t>(R) * tb,
-                           std::max<int64_t>(8, 2 * R * tb));
-    }
+    if (chunk <= 0 && tb == c.tb) chunk = c.auto_chunk;
+    if (chunk <= 0) chunk = best_chunk(n[0], 4, [&](int64_t len) { return star3_us(c, n, tb, per_plane, len, g.vec); });
     chunk = std::min<int64_t>(chunk, n[0]);
     g.chunk_z = static_cast<int32_t>(chunk);
     g.chunks_z = static_cast<int32_t>(ceil_div(n[0], chunk));
     return per_plane * g.chunks_z < (int64_t(1) << 31);
+}
+
+int64_t batch_chunk(const st_plan_s* p, const Candidate& c, double* us_out = nullptr);
+
+// One time step of a candidate (its pass over its depth), us.
+double step_us(const st_plan_s* p, const Candidate& c) {
+    const double cells = static_cast<double>(plan_cells(p));
+    switch (c.kernel) {
+        case ST_KERNEL_STREAM1D: {
+            Geo1 g;
+            if (!geo1(p, c.tb, g)) return 1e300;
+            const int dw = p->dtype == kF64 ? 2 : 1;
+            const double us = kUsPerInstr * (kStream1DVX * (2 * p->radius + 1 + (p->dtype == kBF16 ? 2 : 0)) + 2 * p->radius * dw);
+            const double walk = walk_us(static_cast<double>(ceil_div(g.strips, 4)), p->dtype == kF64 ? 5 : 8, c.tb,
+                                        (p->dtype == kBF16 ? 1.3 : 1.15) * us, 1.1 * us);
+            const double mem = 2.0 * cells * elem_bytes(p->dtype) / 5.5e6;
+            return (4.0 + std::sqrt(walk * walk + mem * mem)) / c.tb;
+        }
+        case ST_KERNEL_STREAM2D: {
+            Geo2 g;
+            if (!geo2(c, p->n[1], p->n[2], c.tb, g)) return 1e300;
+            return rows2_us(c, p->n[1], p->n[2], c.tb, g.tiles_x, g.chunk_y) / c.tb;
+        }
+        case ST_KERNEL_STREAM3D: {
+            Geo3 g;
+            if (!geo3(c, p->n, c.tb, g)) return 1e300;
+            if (c.k3.pipe && !g.vec) return 1e300;  // never runs on this grid
+            return star3_us(c, p->n, c.tb, static_cast<int64_t>(g.tiles_x) * g.tiles_y, g.chunk_z, g.vec) / c.tb;
+        }
+        case ST_KERNEL_BOX3D: {
+            GeoB g;
+            if (!geob(p, c, c.tb, g)) return 1e300;
+            return box_us(p, c, c.tb, static_cast<int64_t>(g.tiles_x) * g.tiles_y, g.chunk_z) / c.tb;
+        }
+        default: {  // one step per launch: batches of points, L1 loads
+            const double v = p->n[2] > 128 ? 4 : (p->n[2] > 64 ? 2 : 1);
+            const double k = p->dtype == kF64 ? 1.6e-6 + 0.38e-6 * p->npoints
+                                              : 0.9e-6 + (p->bc == kZero ? 0.115e-6 : 0.2e-6) * p->npoints;
+            return 3.6 + 0.9 * std::ceil(p->npoints * v / 32.0) + k * cells;
+        }
+    }
+}
+
+// Selection of a plan that is not autotuned: the family's fastest candidate
+// with a model chunk, and whether one step per launch beats it.
+void model_select(st_plan_s* p, bool fixed) {
+    p->sel = 0;
+    p->modelled = p->one_step = false;
+    if (fixed || p->cands.size() <= 1) return;
+    p->modelled = true;
+    double best = 1e300;
+    for (size_t i = 0; i + 1 < p->cands.size(); ++i) {
+        Candidate& c = p->cands[i];
+        if (c.chunk != p->cands[0].chunk || (c.kernel == ST_KERNEL_STREAM2D && c.k2.tess)) continue;
+        double batch_us = 1e300;
+        if (p->batch) {
+            const int64_t len = batch_chunk(p, c, &batch_us);
+            if (c.chunk == 0) c.auto_chunk = static_cast<int32_t>(len);
+        }
+        // the list puts what measured fastest at large sizes first: a model
+        // gain within its error does not change it
+        const double us = (p->batch ? batch_us / c.tb : step_us(p, c)) * (i == 0 ? 0.97 : 1.0);
+        if (us < best) {
+            best = us;
+            p->sel = static_cast<int>(i);
+        }
+    }
+    p->one_step = !p->batch && step_us(p, p->cands.back()) < 0.9 * best;
 }
 
 // Default fused depth and lane width per family.
@@ -472,15 +663,16 @@ void build_candidates(st_plan_s* p) {
                     if (stream2d_has(c.k2) && have_device()) c.occ = stream2d_occupancy(c.k2);
                     Geo2 g;
                     if (stream2d_has(c.k2) && geo2(c, p->n[1], p->n[2], tb, g)) {
+                        if (ch == 0 && !p->batch) c.auto_chunk = g.chunk_y;
                         fast.push_back(c);
                         break;  // smallest instance that holds tb
                     }
                 }
             }
         }
-        // heuristic default first: deeper fusion for narrower storage, model chunk
+        // first what is fastest at large sizes; the time model selects
         // (radius 2: at most four fused steps are instantiated)
-        const int want = (p->dtype == kF64 || p->radius == 2) ? 4 : 8;
+        const int want = p->radius == 2 ? 4 : 8;
         std::stable_sort(fast.begin(), fast.end(), [&](const Candidate& a, const Candidate& b) {
             return (a.tb == want && a.chunk == 0) > (b.tb == want && b.chunk == 0);
         });
@@ -550,6 +742,7 @@ void build_candidates(st_plan_s* p) {
                         if (have_device()) c.occ = stream3d_occupancy(c.k3);
                         Geo3 g;
                         if (geo3(c, p->n, tb, g)) {
+                            if (ch == 0) c.auto_chunk = g.chunk_z;
                             fast.push_back(c);
                             break;
                         }
@@ -585,7 +778,9 @@ void build_candidates(st_plan_s* p) {
                     c.chunk = ch;
                     c.bpipe = v + 1;
                     GeoB g;
-                    if ((ch == 0 || ch < p->n[0]) && geob(p, c, 2, g)) fast.push_back(c);
+                    if ((ch > 0 && ch >= p->n[0]) || !geob(p, c, 2, g)) continue;
+                    if (ch == 0) c.auto_chunk = g.chunk_z;
+                    fast.push_back(c);
                 }
         };
         if (p->dtype == kF64) add_pipe();
@@ -596,7 +791,9 @@ void build_candidates(st_plan_s* p) {
                 c.tb = tb;
                 c.chunk = ch;
                 GeoB g;
-                if ((ch == 0 || ch < p->n[0]) && geob(p, c, tb, g)) fast.push_back(c);
+                if ((ch > 0 && ch >= p->n[0]) || !geob(p, c, tb, g)) continue;
+                if (ch == 0) c.auto_chunk = g.chunk_z;
+                fast.push_back(c);
             }
         if (p->dtype != kF64) add_pipe();
     }
@@ -619,15 +816,22 @@ void build_candidates(st_plan_s* p) {
     }
     p->cands = fast;
     p->cands.push_back(naive);
-    p->sel = 0;
+    model_select(p, force_naive);
     // environment overrides (testing and tuning): STENCIL_TB, STENCIL_VARIANT
     if (const char* v = std::getenv("STENCIL_VARIANT")) {
         const int i = std::atoi(v);
-        if (i >= 0 && i < static_cast<int>(p->cands.size())) p->sel = i;
+        if (i >= 0 && i < static_cast<int>(p->cands.size())) {
+            p->sel = i;
+            p->modelled = p->one_step = false;
+        }
     } else if (const char* t = std::getenv("STENCIL_TB")) {
         const int tb = std::atoi(t);
         for (size_t i = 0; i < p->cands.size(); ++i)
-            if (p->cands[i].tb == tb) { p->sel = static_cast<int>(i); break; }
+            if (p->cands[i].tb == tb) {
+                p->sel = static_cast<int>(i);
+                p->modelled = p->one_step = false;
+                break;
+            }
     }
 }
 
@@ -968,13 +1172,14 @@ st_status check_flux_parts(const st_plan_s* p, int64_t need) {
 // Run `steps` steps with candidate c: grid -> work -> grid ...  With `flux`
 // (zero rule only), the outflow of every step is also added to flux[0].
 st_status run_steps(st_plan_s* p, const Candidate& c_sel, void* grid, void* work, const double* wcan,
-                    int64_t steps, hipStream_t s, double* flux = nullptr) {
-    // The pipeline has whole-vector rows only: on a grid that does not take
+                    int64_t steps, hipStream_t s, double* flux = nullptr, bool one_step = false) {
+    // A selection of the time model may stand for one step per launch.  The pipeline has whole-vector rows only: on a grid that does not take
     // them (too small) the run uses the plan's first other
     // candidate, with its own depth (every candidate gives the same bits; the
     // list always ends with the one-step kernel).
     const Candidate* pick = &c_sel;
-    if (c_sel.kernel == ST_KERNEL_STREAM3D && c_sel.k3.pipe) {
+    if (one_step) pick = &p->cands.back();
+    else if (c_sel.kernel == ST_KERNEL_STREAM3D && c_sel.k3.pipe) {
         if (!fast3(p, c_sel, c_sel.tb, grid, work)) {
             for (const Candidate& o : p->cands)
                 if (!(o.kernel == ST_KERNEL_STREAM3D && o.k3.pipe)) {
@@ -1131,6 +1336,7 @@ bool tune_lookup(st_plan_s* p, const std::string& key) {
     const int idx = it->second.first, n = it->second.second;
     if (n != static_cast<int>(p->cands.size()) || idx < 0 || idx >= n) return false;
     p->sel = idx;
+    p->modelled = p->one_step = false;
     return true;
 }
 
@@ -1185,6 +1391,7 @@ st_status autotune(st_plan_s* p) {
     hipFree(a);
     hipFree(b);
     p->sel = best_i;
+    p->modelled = p->one_step = false;
     tune_store(tkey, best_i, static_cast<int>(p->cands.size()));
     g_last_error.clear();
     return ST_OK;
@@ -1386,12 +1593,14 @@ st_status stencil_plan_select(st_plan plan, int32_t kernel, int32_t tb, int32_t 
         if ((kernel >= 0 && c.kernel != kernel) || (tb > 0 && c.tb != tb))
             return fail(ST_ERR_UNSUPPORTED, "candidate %d is kernel %d depth %d", variant, c.kernel, c.tb);
         plan->sel = variant;
+        plan->modelled = plan->one_step = false;
         return ST_OK;
     }
     for (int i = 0; i < n; ++i) {
         const Candidate& c = plan->cands[i];
         if ((kernel < 0 || c.kernel == kernel) && (tb <= 0 || c.tb == tb)) {
             plan->sel = i;
+            plan->modelled = plan->one_step = false;
             return ST_OK;
         }
     }
@@ -1410,11 +1619,13 @@ st_status stencil_run(st_plan plan, void* grid, void* work, const double* coeffs
         key_push(key, grid);
         key_push(key, work);
         key_push(key, steps);
-        key_push(key, static_cast<int64_t>(plan->sel));
+        key_push(key, static_cast<int64_t>(plan->sel) * 2 + (plan->one_step ? 1 : 0));
         for (int i = 0; i < plan->npoints; ++i) key_push(key, wcan[i]);
     }
     const Candidate cand = plan->cands[plan->sel];
-    return run_graphed(plan, key, s, [&](hipStream_t st) { return run_steps(plan, cand, grid, work, wcan, steps, st); });
+    return run_graphed(plan, key, s, [&](hipStream_t st) {
+        return run_steps(plan, cand, grid, work, wcan, steps, st, nullptr, plan->one_step);
+    });
 }
 
 st_status stencil_run_noalloc(st_plan plan, void* grid, const double* coeffs, const int64_t* shape, int64_t steps,
@@ -1433,7 +1644,7 @@ st_status stencil_run_noalloc(st_plan plan, void* grid, const double* coeffs, co
         return r;
     // eager launches whatever the plan's flags (no graph is instantiated
     // here); inside a caller's capture they are recorded into its graph
-    return run_steps(plan, plan->cands[plan->sel], grid, work, wcan, steps, s);
+    return run_steps(plan, plan->cands[plan->sel], grid, work, wcan, steps, s, nullptr, plan->one_step);
 }
 
 st_status stencil_run_flux(st_plan plan, void* grid, void* work, const double* coeffs, const int64_t* shape,
@@ -1448,14 +1659,32 @@ st_status stencil_run_flux(st_plan plan, void* grid, void* work, const double* c
     // stands in for one without (same states bit for bit: every tiling of a
     // plan gives the same grid)
     Candidate cand = plan->cands[plan->sel];
-    if (cand.kernel == ST_KERNEL_STREAM3D && !flux_fused(plan, cand))
+    bool one_step = plan->one_step;
+    if (plan->modelled && plan->bc == kZero) {
+        // a launch more per pass where the kernel sums the outflow, two more
+        // per step where it does not (about 4 us each): the fastest of the
+        // model's candidates under that account
+        const auto account = [&](const Candidate& c, bool alone) {
+            if (alone || !flux_fused(plan, c)) return (alone ? step_us(plan, plan->cands.back()) : step_us(plan, c) * c.tb) + 8.0;
+            return step_us(plan, c) + 4.0 / c.tb;
+        };
+        double best = account(cand, plan->one_step);
+        for (const Candidate& c : plan->cands)
+            if (c.chunk == plan->cands[0].chunk && c.kernel != ST_KERNEL_NAIVE && flux_fused(plan, c))
+                if (const double us = account(c, false); us < 0.97 * best) {
+                    best = us;
+                    cand = c;
+                    one_step = false;
+                }
+    }
+    if (!one_step && cand.kernel == ST_KERNEL_STREAM3D && !flux_fused(plan, cand))
         for (const Candidate& c : plan->cands)
             if (c.kernel == cand.kernel && c.tb == cand.tb && flux_fused(plan, c)) {
                 cand = c;
                 break;
             }
     // a periodic grid has no boundary: nothing leaves
-    return run_steps(plan, cand, grid, work, wcan, steps, s, plan->bc == kZero ? flux : nullptr);
+    return run_steps(plan, cand, grid, work, wcan, steps, s, plan->bc == kZero ? flux : nullptr, one_step);
 }
 
 }  // extern "C"
@@ -1525,33 +1754,36 @@ extern "C" st_status stencil_batch_plan(st_plan* out, const st_pattern* pattern,
 
 namespace {
 
-// Common y-chunk length for the grids of one batched pass: maximises the
-// busy fraction of the dispatch rounds over all grids' work items times the
-// useful fraction of the streamed rows.
-int64_t batch_chunk(const st_plan_s* p, const Candidate& c, int tb, const std::vector<int>& active) {
-    const int64_t cap = wave_capacity2(c);
-    const int64_t halo = 2 * static_cast<int64_t>(c.k2.radius) * tb;
+// Common y-chunk length for the grids of one batched pass (0: infeasible).
+int64_t batch_chunk(const st_plan_s* p, const Candidate& c, double* us_out) {
+    const int64_t halo = 2 * static_cast<int64_t>(c.k2.radius) * c.tb;
     int64_t maxny = 1;
-    for (int g : active) maxny = std::max(maxny, p->grids[g].ny);
-    double best = -1.0;
-    int64_t best_len = maxny;
-    for (double lf = std::max<int64_t>(8, halo); lf <= static_cast<double>(maxny) * 1.0001; lf *= 1.08) {
-        const int64_t len = static_cast<int64_t>(lf);
-        int64_t items = 0, rows = 0, streamed = 0;
-        for (int g : active) {
+    double cells = 0;
+    for (const BatchGrid& g : p->grids) {
+        maxny = std::max(maxny, g.ny);
+        cells += static_cast<double>(g.ny) * static_cast<double>(g.nx);
+    }
+    double best = 1e300;
+    int64_t best_len = maxny, last = 0;
+    for (double lf = 4; lf <= static_cast<double>(maxny) * 1.08; lf *= 1.08) {
+        const int64_t len = std::min<int64_t>(static_cast<int64_t>(lf), maxny);
+        if (len == last) continue;
+        last = len;
+        int64_t items = 0;
+        double streamed = 0;
+        for (const BatchGrid& bg : p->grids) {
             Geo2 geo;
-            if (!geo2(c, p->grids[g].ny, p->grids[g].nx, tb, geo, len)) return 0;
+            if (!geo2(c, bg.ny, bg.nx, c.tb, geo, len)) return 0;
             items += geo.items;
-            rows += geo.tiles_x * p->grids[g].ny;
-            streamed += geo.tiles_x * (p->grids[g].ny + static_cast<int64_t>(geo.chunks_y) * halo);
+            streamed += static_cast<double>(bg.nx) * static_cast<double>(bg.ny + geo.chunks_y * halo);
         }
-        const double score =
-            std::pow(round_fill(items, cap), 0.25) * static_cast<double>(rows) / static_cast<double>(streamed);
-        if (score > best + 1e-9) {
-            best = score;
+        const double us = rows_us(c, c.tb, items, len + halo, streamed, cells);
+        if (us < best) {
+            best = us;
             best_len = len;
         }
     }
+    if (us_out) *us_out = best;
     return best_len;
 }
 
@@ -1564,9 +1796,7 @@ namespace {
 // run's arguments.
 int64_t batch_chunk_of(const st_plan_s* plan, const Candidate& c) {
     if (c.chunk > 0) return c.chunk;
-    std::vector<int> all(plan->grids.size());
-    for (size_t g = 0; g < all.size(); ++g) all[g] = static_cast<int>(g);
-    return batch_chunk(plan, c, c.tb, all);
+    return c.auto_chunk > 0 ? c.auto_chunk : batch_chunk(plan, c);
 }
 
 // Work items of every grid of a batch candidate, summed (the launch size of
@@ -1918,6 +2148,7 @@ st_status batch_autotune(st_plan_s* p) {
         hipEventDestroy(e0);
         hipEventDestroy(e1);
         p->sel = best_i;
+        p->modelled = p->one_step = false;
         p->table_shadow.clear();
         p->flags = flags;
         tune_store(tkey, best_i, static_cast<int>(p->cands.size()));

@@ -146,3 +146,24 @@ def test_one_step_kernel_rows_and_batches(dtype, bc, npoints):
         print(f"one step {dtype} {bc} {npoints} points {shape}", flush=True)
         got, _ = gpu_sweep(u0, offs, w, 3, bc, dtype, plan=st.Plan(offs, shape, dtype, bc, naive=True))
         check(got, oracle_ref(u0, offs, w, 3, bc, dtype), dtype, 3, f"{shape}")
+
+
+# plans that choose for themselves, from grids of a few cells (one step per
+# launch) to ones that fill the device with tiles: eager, replayed from a graph,
+# and after a selection by the caller
+@pytest.mark.parametrize("dtype", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("pattern,radius,shapes", [
+    ("star", 1, [(7,), (700,), (40000,), (9, 9), (200, 333), (1111, 640), (12, 13, 14), (40, 64, 131), (70, 130, 260)]),
+    ("box", 1, [(64, 64), (513, 1027), (20, 30, 40), (33, 70, 200)]),
+    ("star", 4, [(16, 20, 24), (30, 64, 300)])])
+def test_plans_that_choose_for_themselves(dtype, pattern, radius, shapes):
+    import paper_2303_08365_amd as st
+    for shape in shapes:
+        offs = (synth.star_offsets if pattern == "star" else synth.box_offsets)(len(shape), radius)
+        w = _weights(offs, 41, dtype)
+        u0 = synth.uniform_field(shape, seed=42)
+        naive = st.Plan(offs, shape, dtype, "zero", naive=True)
+        for graph in (False, True):
+            plan = st.Plan(offs, shape, dtype, "zero", graph=graph)
+            _against_naive(plan, naive, u0, offs, w, 13, "zero", dtype, what=f"{dtype} {shape} graph {graph}")
+            _against_naive(plan, naive, u0, offs, w, 13, "zero", dtype, {"variant": 0}, f"{dtype} {shape} selected")
