@@ -246,8 +246,10 @@ struct Pipe {
         c.zs = cz * a.chunk_z;
         c.ze = c.zs + a.chunk_z < nz ? c.zs + a.chunk_z : nz;
         // owned cells and the register tile, moved inward at the grid edges
-        const int32_t ox0 = tx * OUTW, ox1 = ox0 + OUTW < nx ? ox0 + OUTW : nx;
-        const int32_t oy0 = ty * OUTH, oy1 = oy0 + OUTH < ny ? oy0 + OUTH : ny;
+        // (where that saves a tile, the first and the last one own their outer
+        // halo, which needs no neighbour)
+        const int32_t ox0 = tx > 0 ? tx * OUTW + a.edge_x : 0, ox1 = tx + 1 < a.tiles_x ? (tx + 1) * OUTW + a.edge_x : nx;
+        const int32_t oy0 = ty > 0 ? ty * OUTH + a.edge_y : 0, oy1 = ty + 1 < a.tiles_y ? (ty + 1) * OUTH + a.edge_y : ny;
         int32_t X0 = ox0 - HXA;
         X0 = X0 < 0 ? 0 : (X0 + W > nx ? nx - W : X0);
         int32_t Y0 = oy0 - 1;

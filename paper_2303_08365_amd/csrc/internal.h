@@ -43,6 +43,7 @@ struct Stream2DGrid {
     int32_t chunk_y;     // output rows per chunk
     int32_t out_w;       // output columns per strip = 64*VX - 2*hxa
     int32_t hxa;         // redundant halo columns each side (multiple of VX)
+    int32_t edge;        // columns the first and the last strip own beyond out_w (their outer halo, or 0)
     int32_t vec_ok;      // rows are read and stored in whole vectors
     int32_t tb;          // fused steps this pass (<= template depth); batch: the full depth
     int32_t full;        // batch: passes of depth tb, then up to 3 tail passes
@@ -87,6 +88,7 @@ struct Stream3DArgs {
     int32_t tiles_x, tiles_y, chunks_z;
     int32_t out_w, out_h, chunk_z;
     int32_t hxa, hya;    // redundant halo columns/rows inside the register tile
+    int32_t edge_x, edge_y;  // columns/rows the first and the last tile own beyond out_w/out_h (their outer halo, or 0)
     int32_t tb;
     double w[32];        // canonical-order weights (6R+1 used)
     double* flux_part;   // outflow variants: one partial sum per wave (work-group * NW + wave)
@@ -132,6 +134,7 @@ struct Box3DArgs {
     int64_t nz, ny, nx;
     int32_t tiles_x, tiles_y, chunks_z, chunk_z;
     int32_t out_w;       // owned columns per tile (box3d_kernel)
+    int32_t edge_x, edge_y;  // boxpipe3d: columns/rows the first and the last tile own beyond the others' (or 0)
     int32_t tb;          // steps per pass: 1 or 2
     double w[27];        // canonical-order weights
 };

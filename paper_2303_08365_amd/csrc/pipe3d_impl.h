@@ -593,9 +593,11 @@ struct Pipe {
         c.nz = static_cast<int32_t>(a.nz);
         c.row_bytes = static_cast<uint32_t>(nx) * sizeof(TS);
         c.plane_bytes = static_cast<uint32_t>(ny) * c.row_bytes;
-        const int32_t ox0 = tx * a.out_w, oy0 = ty * a.out_h;
-        const int32_t ox1 = ox0 + a.out_w < nx ? ox0 + a.out_w : nx;
-        const int32_t oy1 = oy0 + a.out_h < ny ? oy0 + a.out_h : ny;
+        // where that saves a tile, the first and the last one, which touch the
+        // grid's edge (zero rule), own their outer halo: it needs no neighbour
+        const int32_t ox0 = tx > 0 ? tx * a.out_w + a.edge_x : 0, oy0 = ty > 0 ? ty * a.out_h + a.edge_y : 0;
+        const int32_t ox1 = tx + 1 < a.tiles_x ? (tx + 1) * a.out_w + a.edge_x : nx;
+        const int32_t oy1 = ty + 1 < a.tiles_y ? (ty + 1) * a.out_h + a.edge_y : ny;
         int32_t X0 = ox0 - a.hxa, Y0 = oy0 - a.hya;
         if (!PER) {  // move edge tiles inward (exact: the ghost layer is 0)
             X0 = X0 < 0 ? 0 : (X0 + W > nx ? nx - W : X0);

@@ -631,8 +631,11 @@ struct Kern {
         c.lane = lane;
         const int32_t local = static_cast<int32_t>(item - uni(gp->tile_begin));
         const int32_t cy = local / tiles_x, tx = local - cy * tiles_x;
-        c.ofirst = tx * out_w;
-        c.olast = c.ofirst + out_w < c.nx ? c.ofirst + out_w : c.nx;
+        // where that saves a strip, the first and the last one, which touch the
+        // grid's edge (zero rule), own their outer halo: it needs no neighbour
+        const int32_t edge_x = uni(gp->edge);
+        c.ofirst = tx > 0 ? tx * out_w + edge_x : 0;
+        c.olast = tx + 1 < tiles_x ? (tx + 1) * out_w + edge_x : c.nx;
         c.X0 = c.ofirst - hxa;
         const bool fast = vec_ok && (PER || c.nx >= W);
         if (!PER && fast) c.X0 = c.X0 < 0 ? 0 : (c.X0 + W > c.nx ? c.nx - W : c.X0);

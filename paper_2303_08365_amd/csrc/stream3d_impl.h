@@ -566,10 +566,13 @@ struct Kern {
         c.ny = static_cast<int32_t>(a.ny);
         c.nx = static_cast<int32_t>(a.nx);
         c.plane_elems = a.ny * a.nx;
-        c.ox0 = tx * a.out_w;
-        c.oy0 = ty * a.out_h;
-        c.ox1 = c.ox0 + a.out_w < c.nx ? c.ox0 + a.out_w : c.nx;
-        c.oy1 = c.oy0 + a.out_h < c.ny ? c.oy0 + a.out_h : c.ny;
+        // where that saves a tile, the first and the last one, which touch the
+        // grid's edge (FAST, zero rule), own their outer halo: it needs no
+        // neighbour
+        c.ox0 = tx > 0 ? tx * a.out_w + a.edge_x : 0;
+        c.oy0 = ty > 0 ? ty * a.out_h + a.edge_y : 0;
+        c.ox1 = tx + 1 < a.tiles_x ? (tx + 1) * a.out_w + a.edge_x : c.nx;
+        c.oy1 = ty + 1 < a.tiles_y ? (ty + 1) * a.out_h + a.edge_y : c.ny;
         c.X0 = c.ox0 - a.hxa;
         c.Y0 = c.oy0 - a.hya;
         if (!PER && FAST) {  // move edge tiles inward (exact: the ghost layer is 0)

@@ -167,3 +167,29 @@ def test_plans_that_choose_for_themselves(dtype, pattern, radius, shapes):
             plan = st.Plan(offs, shape, dtype, "zero", graph=graph)
             _against_naive(plan, naive, u0, offs, w, 13, "zero", dtype, what=f"{dtype} {shape} graph {graph}")
             _against_naive(plan, naive, u0, offs, w, 13, "zero", dtype, {"variant": 0}, f"{dtype} {shape} selected")
+
+
+# grids where the edge tiles own their outer halo because that saves a tile: one
+# cell around every such width and height, and the outflow account over them
+@pytest.mark.parametrize("dtype", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("pattern", ["star", "box"])
+@pytest.mark.parametrize("shape", [(6, 34, 128), (9, 58, 248), (5, 60, 249), (7, 64, 256), (6, 90, 500), (4, 118, 505),
+                                   (40, 128), (33, 248), (21, 256), (30, 500), (17, 737)])
+def test_edge_tiles_own_their_outer_halo(dtype, pattern, shape):
+    import torch
+    import oracle
+    import paper_2303_08365_amd as st
+    offs = (synth.star_offsets if pattern == "star" else synth.box_offsets)(len(shape), 1)
+    w = _weights(offs, 43, dtype)
+    u0 = synth.uniform_field(shape, seed=44)
+    plan, naive = st.Plan(offs, shape, dtype, "zero"), st.Plan(offs, shape, dtype, "zero", naive=True)
+    forms = {(c["kernel"], c["tb"], c["block"], c["tile_x"], c["tile_y"], c["pipeline"]): k
+             for k, c in reversed(list(enumerate(plan.candidates()))) if c["kernel"] != st.KERNEL_NAIVE and not c["tessellated"]}
+    for form, k in sorted(forms.items()):
+        _against_naive(plan, naive, u0, offs, w, 2 * form[1], "zero", dtype, {"variant": k}, f"{dtype} {shape} {form}")
+    from gpu_helpers import to_device
+    g, flux = to_device(u0, dtype), torch.zeros(1, dtype=torch.float64, device="cuda")
+    st.Plan(offs, shape, dtype, "zero").run_flux(g, list(w), 7, flux)
+    _, ref = oracle.sweep_flux(synth.round_to(u0, dtype), offs, synth.round_to(np.asarray(w), "f64" if dtype == "f64" else "f32"), 7)
+    tol = {"f64": 1e-12, "f32": 1e-5, "bf16": 7 * 2.0 ** -8}[dtype]
+    assert abs(float(flux.cpu()[0]) - ref) <= tol * max(abs(ref), 1.0), (float(flux.cpu()[0]), ref)
