@@ -275,9 +275,9 @@ double walk_us(double groups, int occ, double nit, double lat, double thr) {
 
 // Bytes over the bandwidth (`tbs` TB/s with `enough` waves a SIMD) that
 // `groups` work-groups of `waves` waves, `occ` resident per CU, keep busy.
-double bytes_us(double bytes, double tbs, double enough, double groups, int occ, int waves) {
+double bytes_us(double bytes, double tbs, double enough, double power, double groups, int occ, int waves) {
     const double w = std::min(groups / device_cus(), static_cast<double>(occ)) * waves / 4;
-    return bytes / (tbs * 1e6 * std::pow(std::min(1.0, w / enough), 0.2));
+    return bytes / (tbs * 1e6 * std::pow(std::min(1.0, w / enough), power));
 }
 
 // Where the two come near each other both are felt.
@@ -313,14 +313,14 @@ double rows_us(const Candidate& c, int tb, int64_t items, int64_t nit, double st
     const double groups = static_cast<double>(ceil_div(items, 4));
     const int occ = c.occ > 0 ? c.occ : 2;
     return 4.0 + both_us(walk_us(groups, occ, static_cast<double>(nit), 0.075 + 1.18 * (us + 2 * rnd), 1.08 * (us + rnd)),
-                         bytes_us(elem_bytes(c.k2.dtype) * (streamed + cells), 5.2, 3.0, groups, occ, 4));
+                         bytes_us(elem_bytes(c.k2.dtype) * (streamed + cells), 5.2, 3.0, 0.3, groups, occ, 4));
 }
 
 // 3D planes: a pass over `grid` bytes in chunks of `chunk` planes, `nit` with
 // the halo (the tiles' xy halos come from L2).
 double planes_us(double launch, double tbs, double groups, int occ, int waves, double nit, double chunk, double lat, double thr,
                  double grid) {
-    return launch + both_us(walk_us(groups, occ, nit, lat, thr), bytes_us(grid * (nit / chunk + 1.0), tbs, 2.0, groups, occ, waves));
+    return launch + both_us(walk_us(groups, occ, nit, lat, thr), bytes_us(grid * (nit / chunk + 1.0), tbs, 2.0, 0.2, groups, occ, waves));
 }
 
 // Geometry of one 2D pass for a grid.
@@ -364,6 +364,22 @@ int32_t edge_tiles(int64_t n, int32_t out, int32_t halo, int32_t& edge) {
     return static_cast<int32_t>(std::min(plain, wide));
 }
 
+// Where tiles start (rows of whole 128-byte lines).  3D: the widest tile of at
+// most `out` cells whose starts all lie on 128-byte, else 64-byte boundaries, if
+// that costs no tile more (512^3 FP64: 112 columns instead of 120, five tiles
+// either way, 12.38 -> 12.11 ms).  2D: on 64-byte boundaries always (`must`):
+// strips that start 32 bytes off them store partial sectors (8192^2 9-point star
+// FP64, 116 -> 112 columns: 257 -> 236 us a pass; no gain from 128 bytes).
+int32_t line_tile(int64_t n, int32_t out, int esz, bool must) {
+    if (n * esz % 128 != 0) return out;
+    for (int unit : {128, 64}) {
+        if (must && unit == 128) continue;
+        const int32_t w = out * esz / unit * unit / esz;
+        if (w > 0 && (must || ceil_div(n, w) == ceil_div(n, out))) return w;
+    }
+    return out;
+}
+
 // `elems`: the buffers are aligned to an element (they are, but for a caller's
 // byte arithmetic); without that there are no whole-vector rows.
 bool geo2(const Candidate& c, int64_t ny, int64_t nx, int tb, Geo2& g, int64_t chunk_override = 0, bool elems = true) {
@@ -402,6 +418,10 @@ bool geo2(const Candidate& c, int64_t ny, int64_t nx, int tb, Geo2& g, int64_t c
         if (g.vec) g.out_w = w;
     }
     g.tiles_x = edge_tiles(nx, g.out_w, c.k2.bc == kZero && g.vec && nx >= 64 * vx ? g.hxa : 0, g.edge);
+    if (g.vec && g.edge == 0) {
+        g.out_w = line_tile(nx, g.out_w, elem_bytes(c.k2.dtype), true);
+        g.tiles_x = static_cast<int32_t>(ceil_div(nx, g.out_w));
+    }
     int64_t chunk = chunk_override > 0 ? chunk_override : c.chunk;
     if (chunk <= 0 && tb == c.tb) chunk = c.auto_chunk;
     if (chunk <= 0)
@@ -460,9 +480,9 @@ double box_us(const st_plan_s* p, const Candidate& c, int tb, int64_t per_plane,
     const int waves = sh.block / 64, k = sh.h / waves;
     int rows = 0;
     for (int l = 0; l < tb; ++l) rows += k + 2 * (tb - 1 - l);
-    // (two steps FP64 measured well over the fit of the others: registers)
+    // (two steps measured over the fit of one, FP64 well over it: registers)
     const double us = kUsPerInstr * (rows * sh.vx * (27 + (p->dtype == kBF16 ? 2 : 0)) + 6 * (k + 2 * tb) * dw * tb) *
-                      (tb == 2 && p->dtype == kF64 ? 1.7 : 1.0);
+                      (tb == 1 ? 1.0 : (p->dtype == kF64 ? 1.7 : 1.12));
     return planes_us(7.0, 5.5, groups, tb == 1 ? 2 : 1, waves, len + 2 * tb, len, 0.54 + 1.42 * us, 1.22 * us * waves / 4, grid);
 }
 
@@ -561,6 +581,7 @@ bool geo3(const Candidate& c, const int64_t n[3], int tb, Geo3& g, bool elems = 
     }
     const bool edges = c.k3.bc == kZero && g.vec;
     g.tiles_x = edge_tiles(n[2], g.out_w, edges ? g.hxa : 0, g.edge_x);
+    if (g.vec && g.edge_x == 0) g.out_w = line_tile(n[2], g.out_w, elem_bytes(c.k3.dtype), false);
     g.tiles_y = edge_tiles(n[1], g.out_h, edges ? g.hya : 0, g.edge_y);
     int64_t chunk = c.chunk;
     const int64_t per_plane = static_cast<int64_t>(g.tiles_x) * g.tiles_y;
