@@ -167,19 +167,30 @@ struct VarcoefArgs {
     const void* k;      // conductivity
     const void* lam;    // adjoint only: dL/du^{n+1}
     void* out;          // u^{n+1} (forward) or dL/du^n (adjoint)
-    void* grad;         // adjoint only: dL/dk accumulator (+=), may be null
+    void* grad;         // adjoint only: dL/dk accumulator (+=), may be null (not in the two-step form)
+    const void* u1;     // two-step adjoint: u^{n-1}
+    void* mid;          // two-step forward: u^{n+1}, or null (out is u^{n+2})
     int64_t nz, ny, nx;
     double alpha;
     // filled by launch_varcoef: work-group index -> (row, x block), row -> (z, y)
     uint32_t nxb, nxb_m, nxb_l, ny_m, ny_l;
     // streaming kernels: tiles of varcoef_stream_shape(), chunks of planes
     int32_t tiles_x, tiles_y, chunks_z, chunk_z;
+    int32_t edge_x, edge_y;  // two-step form: columns/rows the first and last tile own beyond the others' (or 0)
 };
 hipError_t launch_varcoef(int dtype, bool adjoint, const VarcoefArgs& a, hipStream_t s);
 // z-streaming step / adjoint (needs nx >= w, ny >= h, planes below 2 GiB)
 void varcoef_stream_shape(int dtype, bool adjoint, int& w, int& h, int& block);
 hipError_t launch_varcoef_stream(int dtype, bool adjoint, const VarcoefArgs& a, hipStream_t s);
 int varcoef_stream_occupancy(int dtype, bool adjoint);  // work-groups per CU, 0 if unknown
+// two steps per pass (varcoef_pipe.hip): needs nx >= w, ny >= h, planes below
+// 2 GiB; the adjoint also nx % vx == 0 and a grad buffer.  4 planes re-streamed
+// per chunk.  vx: FP64 2 or 1, FP32 4 or 1.
+struct VarcoefPipeShape {
+    int w, h, out_w, out_h, wgs_per_cu;
+};
+VarcoefPipeShape varcoef_pipe_shape(int dtype, int vx, bool adjoint);
+hipError_t launch_varcoef_pipe(int dtype, int vx, bool adjoint, const VarcoefArgs& a, hipStream_t s);
 
 // ----------------------------------------------------------------------------
 // outflow across the zero-rule boundary (FP64 partial sums + fixed-order reduce)

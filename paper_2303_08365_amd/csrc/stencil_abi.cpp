@@ -2281,6 +2281,76 @@ st_status varcoef_launch(const st_plan_s* p, bool adjoint, const void* u, const 
     return ST_OK;
 }
 
+// Launch geometry of the two-step kernels for one plan and direction; vx == 0:
+// they do not take the plan.  They take every grid their tiles fit into, but
+// for FP64 grids below 3 * 2^17 cells: a pass is a chain of at least five
+// planes there (48x64x96: 6.2 us a step in pairs, 5.1 in single steps; 80^3: 6.5
+// and 8.5).  FP32 gains from the smallest on (64^3: 2.9 and 4.4).
+struct VarcoefPairs {
+    int vx = 0;
+    VarcoefArgs a;
+};
+VarcoefPairs varcoef_pairs(const st_plan_s* p, bool adjoint) {
+    VarcoefPairs best;
+    if (p->flags & ST_PLAN_NAIVE) return best;
+    const int64_t nz = p->n[0], ny = p->n[1], nx = p->n[2];
+    if (ny * nx * elem_bytes(p->dtype) >= (int64_t(1) << 31) || nz >= (int64_t(1) << 30)) return best;
+    if (p->dtype == kF64 && nz * ny * nx < 3 * (int64_t(1) << 17)) return best;
+    const int widest = p->dtype == kF64 ? 2 : 4;
+    double least = 0.0;
+    for (int vx : {widest, 1}) {
+        const VarcoefPipeShape sh = varcoef_pipe_shape(p->dtype, vx, adjoint);
+        if (nx < sh.w || ny < sh.h || (adjoint && nx % vx != 0)) continue;
+        VarcoefArgs a;
+        std::memset(&a, 0, sizeof(a));
+        a.nz = nz;
+        a.ny = ny;
+        a.nx = nx;
+        a.tiles_x = edge_tiles(nx, sh.out_w, (sh.w - sh.out_w) / 2, a.edge_x);
+        a.tiles_y = edge_tiles(ny, sh.out_h, 1, a.edge_y);
+        const int64_t per_plane = static_cast<int64_t>(a.tiles_x) * a.tiles_y;
+        const int64_t cap = static_cast<int64_t>(device_cus()) * sh.wgs_per_cu;
+        // rounds of work-groups, each streaming chunk + 4 planes of 64 * vx
+        // columns a wave; a column costs 1.5 times as much in narrow lanes (512^3
+        // FP32: 724 us an adjoint step with 3 tiles of 256 columns, 839 with 9
+        // of 64; 512^3 FP64: 1365 with 5 of 128, 1560 with 9 of 64)
+        const double plane = sh.wgs_per_cu * vx * (vx == widest ? 1.0 : 1.5);
+        for (int64_t chunk = nz, last = 0; chunk >= 1; --chunk) {
+            const int64_t chunks = ceil_div(nz, chunk);
+            if (chunks == last || per_plane * chunks >= (int64_t(1) << 31)) continue;
+            last = chunks;
+            const double cost = static_cast<double>(ceil_div(per_plane * chunks, cap)) * static_cast<double>(chunk + 4) *
+                                plane;
+            if (best.vx == 0 || cost < least) {
+                least = cost;
+                a.chunk_z = static_cast<int32_t>(chunk);
+                a.chunks_z = static_cast<int32_t>(chunks);
+                best.vx = vx;
+                best.a = a;
+            }
+        }
+    }
+    return best;
+}
+
+// Two steps: forward (u1 null) u -> mid (may be null) -> out; adjoint (u, u1 the
+// states before and two before) lam -> out, grad += both steps' terms.
+st_status varcoef_launch2(const st_plan_s* p, const VarcoefPairs& g, bool adjoint, const void* u, const void* u1,
+                          const void* k, const void* lam, void* mid, void* out, void* grad, double alpha, hipStream_t s) {
+    VarcoefArgs a = g.a;
+    a.u = u;
+    a.u1 = u1;
+    a.k = k;
+    a.lam = lam;
+    a.mid = mid;
+    a.out = out;
+    a.grad = grad;
+    a.alpha = alpha;
+    const hipError_t e = launch_varcoef_pipe(p->dtype, g.vx, adjoint, a, s);
+    if (e != hipSuccess) return hip_fail(e, adjoint ? "varcoef adjoint launch" : "varcoef step launch");
+    return ST_OK;
+}
+
 }  // namespace
 
 extern "C" st_status stencil_run_ckpt(st_plan plan, void* grid, void* work, const void* k, double alpha,
@@ -2302,10 +2372,18 @@ extern "C" st_status stencil_run_ckpt(st_plan plan, void* grid, void* work, cons
     const size_t bytes = static_cast<size_t>(plan_cells(plan)) * elem_bytes(plan->dtype);
     void* cur = grid;
     void* nxt = work;
+    // two steps per pass; a checkpoint of the state between is stored by the pass
+    const VarcoefPairs pairs = steps > 1 ? varcoef_pairs(plan, false) : VarcoefPairs();
     for (int64_t t = 0; t < steps; ++t) {
         if (ckpts && t % every == 0)
             ST_HIP(hipMemcpyAsync(ckpts[t / every], cur, bytes, hipMemcpyDeviceToDevice, s), "hipMemcpyAsync(checkpoint)");
-        if (st_status r = varcoef_launch(plan, false, cur, k, nullptr, nxt, nullptr, alpha, s); r != ST_OK) return r;
+        if (pairs.vx != 0 && t + 1 < steps) {
+            ++t;
+            void* mid = ckpts && t % every == 0 ? ckpts[t / every] : nullptr;
+            if (st_status r = varcoef_launch2(plan, pairs, false, cur, nullptr, k, nullptr, mid, nxt, nullptr, alpha, s);
+                r != ST_OK)
+                return r;
+        } else if (st_status r = varcoef_launch(plan, false, cur, k, nullptr, nxt, nullptr, alpha, s); r != ST_OK) return r;
         std::swap(cur, nxt);
     }
     if (cur != grid) ST_HIP(hipMemcpyAsync(grid, cur, bytes, hipMemcpyDeviceToDevice, s), "hipMemcpyAsync(work->grid)");
@@ -2342,19 +2420,36 @@ extern "C" st_status stencil_adjoint_run(st_plan plan, const void* k, double alp
     if (st_status r = need_device(); r != ST_OK) return r;
     void* cur = lambda;
     void* nxt = work;
+    const int64_t longest = std::min(every, steps);
+    const VarcoefPairs fwd = longest > 2 ? varcoef_pairs(plan, false) : VarcoefPairs();
+    const VarcoefPairs adj = longest > 1 && grad_k ? varcoef_pairs(plan, true) : VarcoefPairs();
     for (int64_t c = nck - 1; c >= 0; --c) {
         const int64_t n0 = c * every;
         const int64_t len = std::min(every, steps - n0);
         // recompute u^{n0+1} .. u^{n0+len-1} into seg[0 .. len-2]
         for (int64_t j = 1; j < len; ++j) {
             const void* prev = (j == 1) ? ckpts[c] : at(seg, j - 2, bytes);
+            if (fwd.vx != 0 && j + 1 < len) {
+                ++j;
+                if (st_status r = varcoef_launch2(plan, fwd, false, prev, nullptr, k, nullptr, at(seg, j - 2, bytes),
+                                                  at(seg, j - 1, bytes), nullptr, alpha, s);
+                    r != ST_OK)
+                    return r;
+                continue;
+            }
             if (st_status r = varcoef_launch(plan, false, prev, k, nullptr, at(seg, j - 1, bytes), nullptr, alpha, s);
                 r != ST_OK)
                 return r;
         }
         for (int64_t j = len - 1; j >= 0; --j) {
             const void* u = (j == 0) ? ckpts[c] : at(seg, j - 1, bytes);
-            if (st_status r = varcoef_launch(plan, true, u, k, cur, nxt, grad_k, alpha, s); r != ST_OK) return r;
+            if (adj.vx != 0 && j > 0) {
+                --j;
+                const void* u1 = (j == 0) ? ckpts[c] : at(seg, j - 1, bytes);
+                if (st_status r = varcoef_launch2(plan, adj, true, u, u1, k, cur, nullptr, nxt, grad_k, alpha, s);
+                    r != ST_OK)
+                    return r;
+            } else if (st_status r = varcoef_launch(plan, true, u, k, cur, nxt, grad_k, alpha, s); r != ST_OK) return r;
             std::swap(cur, nxt);
         }
     }

@@ -2,7 +2,7 @@
 //
 // The paper's sweep has constant weights; differentiating a simulation with
 // respect to a conductivity field needs the conservative variable form
-// (zero-Dirichlet ghost layer, faces visited z-, z+, y-, y+, x-, x+):
+// (zero-Dirichlet ghost layer, faces visited z-, y-, y+, x-, x+, z+):
 //   u'[i] = u[i] + alpha * sum_f kap_f * (u[i+f] - u[i]),
 //   kap_f = (k[i] + k[i+f]) / 2 inside the grid; kap_f = k[i], u = 0 on the
 //   ghost layer.
@@ -62,7 +62,8 @@ __global__ __launch_bounds__(256) void varcoef_step_kernel(const VarcoefArgs a) 
     const int64_t i = (z * ny + y) * nx + x;
     const TC uc = ld1(u + i), kc = ld1(k + i);
     const TC alpha = static_cast<TC>(a.alpha);
-    const int64_t dz[6] = {-1, 1, 0, 0, 0, 0}, dy[6] = {0, 0, -1, 1, 0, 0}, dx[6] = {0, 0, 0, 0, -1, 1};
+    // faces z-, y-, y+, x-, x+, z+
+    const int64_t dz[6] = {-1, 0, 0, 0, 0, 1}, dy[6] = {0, -1, 1, 0, 0, 0}, dx[6] = {0, 0, 0, -1, 1, 0};
     TC acc = TC(0);
 #pragma unroll
     for (int f = 0; f < 6; ++f) {
@@ -92,8 +93,10 @@ __global__ __launch_bounds__(256) void varcoef_adjoint_kernel(const VarcoefArgs 
     const int64_t i = (z * ny + y) * nx + x;
     const TC uc = ld1(u + i), kc = ld1(k + i), lc = ld1(lam + i);
     const TC alpha = static_cast<TC>(a.alpha);
-    const int64_t dz[6] = {-1, 1, 0, 0, 0, 0}, dy[6] = {0, 0, -1, 1, 0, 0}, dx[6] = {0, 0, 0, 0, -1, 1};
+    // faces z-, y-, y+, x-, x+, z+
+    const int64_t dz[6] = {-1, 0, 0, 0, 0, 1}, dy[6] = {0, -1, 1, 0, 0, 0}, dx[6] = {0, 0, 0, -1, 1, 0};
     TC acc = TC(0), gacc = TC(0);
+    int ng = 0;  // ghost faces: their dL/dk terms come last, as in the other kernels
 #pragma unroll
     for (int f = 0; f < 6; ++f) {
         const int64_t zz = z + dz[f], yy = y + dy[f], xx = x + dx[f];
@@ -105,9 +108,10 @@ __global__ __launch_bounds__(256) void varcoef_adjoint_kernel(const VarcoefArgs 
             gacc = fma_c(TC(0.5) * (ld1(u + j) - uc), lc - lf, gacc);
         } else {
             acc = fma_c(kc, -lc, acc);
-            gacc = fma_c(-uc, lc, gacc);
+            ng += 1;
         }
     }
+    gacc = fma_c(-static_cast<TC>(ng) * uc, lc, gacc);
     st1(out + i, fma_c(alpha, acc, lc));
     if (a.grad != nullptr) st1(g + i, fma_c(alpha, gacc, ld1(g + i)));
 }

@@ -10,7 +10,7 @@
 // operand.
 //
 // The ghost layer is produced by the loads themselves, so no face needs a
-// test.  The operator (the faces visited z-, z+, y-, y+, x-, x+):
+// test.  The operator (the faces visited z-, y-, y+, x-, x+, z+):
 //   u'[i] = u[i] + alpha * sum_f kap_f * (u[f] - u[i]),
 //   kap_f = (k[i] + k[f]) / 2 inside; across the grid edge kap = k[i], u = 0.
 // Fields that are 0 on the ghost layer (u in the step, lambda in the
@@ -173,15 +173,15 @@ struct Kern {
             const int ngzy = ngz + (y == 0) + (y == c.ny - 1);
 #pragma unroll
             for (int e = 0; e < VX; ++e) {
-                T nb[6][F];  // faces z-, z+, y-, y+, x-, x+
+                T nb[6][F];  // faces z-, y-, y+, x-, x+, z+
 #pragma unroll
                 for (int f = 0; f < F; ++f) {
                     nb[0][f] = Pm.v[f][k][e];
-                    nb[1][f] = Pp.v[f][k][e];
-                    nb[2][f] = k > 0 ? C.v[f][k > 0 ? k - 1 : 0][e] : r.above[f][e];
-                    nb[3][f] = k < K - 1 ? C.v[f][k < K - 1 ? k + 1 : 0][e] : r.below[f][e];
-                    nb[4][f] = e > 0 ? C.v[f][k][e > 0 ? e - 1 : 0] : lft[f];
-                    nb[5][f] = e < VX - 1 ? C.v[f][k][e < VX - 1 ? e + 1 : 0] : rgt[f];
+                    nb[5][f] = Pp.v[f][k][e];
+                    nb[1][f] = k > 0 ? C.v[f][k > 0 ? k - 1 : 0][e] : r.above[f][e];
+                    nb[2][f] = k < K - 1 ? C.v[f][k < K - 1 ? k + 1 : 0][e] : r.below[f][e];
+                    nb[3][f] = e > 0 ? C.v[f][k][e > 0 ? e - 1 : 0] : lft[f];
+                    nb[4][f] = e < VX - 1 ? C.v[f][k][e < VX - 1 ? e + 1 : 0] : rgt[f];
                 }
                 const T uc = C.v[0][k][e], kc = C.v[1][k][e];
                 T acc = T(0);

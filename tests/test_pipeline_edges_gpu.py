@@ -193,3 +193,35 @@ def test_edge_tiles_own_their_outer_halo(dtype, pattern, shape):
     _, ref = oracle.sweep_flux(synth.round_to(u0, dtype), offs, synth.round_to(np.asarray(w), "f64" if dtype == "f64" else "f32"), 7)
     tol = {"f64": 1e-12, "f32": 1e-5, "bf16": 7 * 2.0 ** -8}[dtype]
     assert abs(float(flux.cpu()[0]) - ref) <= tol * max(abs(ref), 1.0), (float(flux.cpu()[0]), ref)
+
+
+def _varcoef(u0, k, y, dtype, steps, every, naive):
+    """Forward with checkpoints and both gradients, every buffer one element off."""
+    import torch
+    import paper_2303_08365_amd as st
+    plan = st.varcoef_plan(u0.shape, dtype, naive=naive)
+    g, kk, lam, gk = (_offset_view(f, dtype) for f in (u0, k, y, 0.1 * y))
+    ck = [torch.full_like(g, float("nan")) for _ in range(-(-steps // every))]
+    plan.run_ckpt(g, kk, 0.1, steps, torch.full_like(g, float("nan")), every=every, ckpts=ck)
+    seg = torch.full((max(min(every, steps) - 1, 1),) + u0.shape, float("nan"), dtype=g.dtype, device="cuda")
+    plan.adjoint(lam, steps, torch.full_like(g, float("nan")), k=kk, alpha=0.1, ckpts=ck, every=every, grad_k=gk, seg=seg)
+    return [t.cpu().numpy() for t in (g, *ck, lam, gk)]
+
+
+# two steps per pass against the one-cell-per-thread kernels, bit for bit (every
+# kernel takes a cell's faces in the same order): the smallest grids of each
+# lane width (4, 2, 1 columns; 16 or 32 rows), one plane, fewer planes than a
+# pass re-streams, ragged tiles, rows of any length (forward only), and step
+# counts and intervals that leave every mix of single and paired steps
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("shape", [(1, 32, 64), (2, 33, 65), (3, 16, 128), (5, 62, 130), (9, 63, 256), (6, 95, 252),
+                                   (17, 40, 509), (33, 32, 512)])
+def test_varcoef_two_steps_per_pass(dtype, shape):
+    rng = np.random.default_rng(5)
+    u0, k, y = rng.random(shape), 0.5 + rng.random(shape), rng.random(shape)
+    for steps, every in [(2, 2), (3, 1), (5, 2), (7, 3), (8, 8)]:
+        print(f"varcoef {dtype} {shape} steps {steps} every {every}", flush=True)
+        got = _varcoef(u0, k, y, dtype, steps, every, False)
+        want = _varcoef(u0, k, y, dtype, steps, every, True)
+        for i, (a, b) in enumerate(zip(got, want)):
+            assert np.array_equal(a, b), f"buffer {i} of {len(got)}"
