@@ -147,6 +147,9 @@ int elem_bytes(int dtype) { return dtype == kF64 ? 8 : (dtype == kF32 ? 4 : 2); 
 // ---------------------------------------------------------------------------
 namespace {
 
+constexpr int32_t kKernelTile2D = 100;  // a Candidate's kernel: register tiles, in no plan's list
+enum StandIn { kNoStandIn, kOneStep, kTiles };
+
 // One tiling candidate of a plan.
 struct Candidate {
     int32_t kernel = ST_KERNEL_NAIVE;
@@ -182,7 +185,9 @@ struct st_plan_s {
     // the selection is the time model's own (not the caller's, the
     // autotuner's or the environment's), and it puts one step per launch
     // before the selected tiling: the grid is too small for tiles
-    bool modelled = false, one_step = false;
+    bool modelled = false;
+    int stand_in = kNoStandIn;  // what runs instead of a modelled plan's candidate
+    Candidate tile;             // kTiles: its depth and columns a lane
     // Device memory a plan owns is allocated when the plan is made (see
     // plan_buffers), never by a run call.
     void* owned_work = nullptr;   // ST_PLAN_OWN_WORK
@@ -634,11 +639,64 @@ double step_us(const st_plan_s* p, const Candidate& c) {
     }
 }
 
+// Geometry of a pass of t steps of the register tiles (tile2d.hip); false: they
+// do not take the plan.
+bool geo_tile(const st_plan_s* p, int vx, int t, Tile2DArgs& a) {
+    const int64_t ny = p->n[1], nx = p->n[2];
+    const int w = 64 * vx, h = tile2d_rows();
+    if (p->n[0] != 1 || p->batch || p->radius != 1 || p->npoints != (p->cls == kStar ? 5 : 9) || nx < w || ny < h) return false;
+    if (ny * nx * elem_bytes(p->dtype) >= (int64_t(1) << 31) || (p->bc != kZero && nx % vx != 0)) return false;
+    std::memset(&a, 0, sizeof(a));
+    a.ny = static_cast<int32_t>(ny);
+    a.nx = static_cast<int32_t>(nx);
+    a.t = t;
+    a.hx = static_cast<int32_t>(ceil_div(t, vx) * vx);
+    a.hy = t;
+    a.out_w = w - 2 * a.hx;
+    a.out_h = h - 2 * t;
+    if (a.out_w <= 0 || a.out_h <= 0) return false;
+    a.tiles_x = edge_tiles(nx, a.out_w, p->bc == kZero ? a.hx : 0, a.edge_x);
+    a.tiles_y = edge_tiles(ny, a.out_h, p->bc == kZero ? a.hy : 0, a.edge_y);
+    return static_cast<int64_t>(a.tiles_x) * a.tiles_y < (int64_t(1) << 31);
+}
+
+// The fastest register tiles of a plan: us a step.  A step of one work-group on
+// a CU is its arithmetic (two waves a SIMD) and the LDS round trip with its
+// barrier; further work-groups add their arithmetic and their tile's load and
+// store.  Measured us a step, FP64 5 points: 256^2 24 steps a pass 0.55 (rows
+// 1.23), 512^2 16 steps 0.63 (1.30), 1024^2 12 steps of two columns 0.89 (1.60),
+// 2048^2 2.36 (3.28), 4096^2 8 steps 7.5 (8.2: the rows are kept); FP32 9 points
+// 256^2 0.55 (1.94), 2048^2 2.64 (3.28).  The model is within 12 % of all of them.
+double tile_select(st_plan_s* p) {
+    double best = 1e300;
+    p->tile = Candidate();
+    p->tile.kernel = kKernelTile2D;
+    const int dw = p->dtype == kF64 ? 2 : 1, rows = tile2d_rows() / 8;
+    for (int vx : {1, 2, 4}) {
+        if ((p->dtype == kBF16) != (vx == 4)) continue;
+        const double us = 2 * kUsPerInstr * (rows * vx * (p->npoints + (p->dtype == kBF16 ? 2 : 0)) +
+                                             2 * dw * (p->cls == kStar ? rows : rows + 2));
+        for (int t = 2; 2 * t < tile2d_rows(); ++t) {
+            Tile2DArgs a;
+            if (!geo_tile(p, vx, t, a)) break;
+            const double groups = static_cast<double>(ceil_div(static_cast<int64_t>(a.tiles_x) * a.tiles_y, device_cus()));
+            const double pass = 2.3 + t * ((p->dtype == kF64 ? 0.21 : 0.16) + us) + (groups - 1) * (0.6 + t * us);
+            if (pass / t < best) {
+                best = pass / t;
+                p->tile.tb = t;
+                p->tile.k2.vx = vx;
+            }
+        }
+    }
+    return best;
+}
+
 // Selection of a plan that is not autotuned: the family's fastest candidate
 // with a model chunk, and whether one step per launch beats it.
 void model_select(st_plan_s* p, bool fixed) {
     p->sel = 0;
-    p->modelled = p->one_step = false;
+    p->modelled = false;
+    p->stand_in = kNoStandIn;
     if (fixed || p->cands.size() <= 1) return;
     p->modelled = true;
     double best = 1e300;
@@ -658,7 +716,12 @@ void model_select(st_plan_s* p, bool fixed) {
             p->sel = static_cast<int>(i);
         }
     }
-    p->one_step = !p->batch && step_us(p, p->cands.back()) < 0.9 * best;
+    if (p->batch) return;
+    if (step_us(p, p->cands.back()) < 0.9 * best) {
+        best = step_us(p, p->cands.back());
+        p->stand_in = kOneStep;
+    }
+    if (const double us = tile_select(p); us < 0.9 * best) p->stand_in = kTiles;
 }
 
 // Default fused depth and lane width per family.
@@ -860,14 +923,16 @@ void build_candidates(st_plan_s* p) {
         const int i = std::atoi(v);
         if (i >= 0 && i < static_cast<int>(p->cands.size())) {
             p->sel = i;
-            p->modelled = p->one_step = false;
+            p->modelled = false;
+            p->stand_in = kNoStandIn;
         }
     } else if (const char* t = std::getenv("STENCIL_TB")) {
         const int tb = std::atoi(t);
         for (size_t i = 0; i < p->cands.size(); ++i)
             if (p->cands[i].tb == tb) {
                 p->sel = static_cast<int>(i);
-                p->modelled = p->one_step = false;
+                p->modelled = false;
+                p->stand_in = kNoStandIn;
                 break;
             }
     }
@@ -996,6 +1061,16 @@ st_status launch_pass(const st_plan_s* p, const Candidate& c, const void* src, v
                       const double* wcan, int tb, hipStream_t s, double* fpart = nullptr) {
     hipError_t e = hipSuccess;
     const bool elems = elem_aligned(src, p->dtype) && elem_aligned(dst, p->dtype);
+    if (c.kernel == kKernelTile2D) {
+        Tile2DArgs a;
+        if (!geo_tile(p, c.k2.vx, tb, a)) return fail(ST_ERR_UNSUPPORTED, "tiling infeasible");
+        a.src = src;
+        a.dst = dst;
+        for (int i = 0; i < p->npoints; ++i) a.w[i] = wcan[i];
+        e = launch_tile2d(p->dtype, c.k2.vx, p->cls != kStar, p->bc != kZero, a, s);
+        if (e != hipSuccess) return hip_fail(e, "register tile launch");
+        return ST_OK;
+    }
     if (c.kernel == ST_KERNEL_NAIVE) {
         NaiveArgs a;
         a.src = src;
@@ -1215,13 +1290,15 @@ st_status check_flux_parts(const st_plan_s* p, int64_t need) {
 // Run `steps` steps with candidate c: grid -> work -> grid ...  With `flux`
 // (zero rule only), the outflow of every step is also added to flux[0].
 st_status run_steps(st_plan_s* p, const Candidate& c_sel, void* grid, void* work, const double* wcan,
-                    int64_t steps, hipStream_t s, double* flux = nullptr, bool one_step = false) {
-    // A selection of the time model may stand for one step per launch.  The pipeline has whole-vector rows only: on a grid that does not take
+                    int64_t steps, hipStream_t s, double* flux = nullptr, int stand_in = kNoStandIn) {
+    // A selection of the time model may stand for one step per launch or for
+    // the register tiles (no outflow form).  The pipeline has whole-vector rows only: on a grid that does not take
     // them (too small) the run uses the plan's first other
     // candidate, with its own depth (every candidate gives the same bits; the
     // list always ends with the one-step kernel).
     const Candidate* pick = &c_sel;
-    if (one_step) pick = &p->cands.back();
+    if (stand_in == kOneStep) pick = &p->cands.back();
+    else if (stand_in == kTiles && !flux && elem_aligned(grid, p->dtype) && elem_aligned(work, p->dtype)) pick = &p->tile;
     else if (c_sel.kernel == ST_KERNEL_STREAM3D && c_sel.k3.pipe) {
         if (!fast3(p, c_sel, c_sel.tb, grid, work)) {
             for (const Candidate& o : p->cands)
@@ -1380,7 +1457,8 @@ bool tune_lookup(st_plan_s* p, const std::string& key) {
     const int idx = it->second.first, n = it->second.second;
     if (n != static_cast<int>(p->cands.size()) || idx < 0 || idx >= n) return false;
     p->sel = idx;
-    p->modelled = p->one_step = false;
+    p->modelled = false;
+    p->stand_in = kNoStandIn;
     return true;
 }
 
@@ -1435,7 +1513,8 @@ st_status autotune(st_plan_s* p) {
     hipFree(a);
     hipFree(b);
     p->sel = best_i;
-    p->modelled = p->one_step = false;
+    p->modelled = false;
+    p->stand_in = kNoStandIn;
     tune_store(tkey, best_i, static_cast<int>(p->cands.size()));
     g_last_error.clear();
     return ST_OK;
@@ -1637,14 +1716,16 @@ st_status stencil_plan_select(st_plan plan, int32_t kernel, int32_t tb, int32_t 
         if ((kernel >= 0 && c.kernel != kernel) || (tb > 0 && c.tb != tb))
             return fail(ST_ERR_UNSUPPORTED, "candidate %d is kernel %d depth %d", variant, c.kernel, c.tb);
         plan->sel = variant;
-        plan->modelled = plan->one_step = false;
+        plan->modelled = false;
+        plan->stand_in = kNoStandIn;
         return ST_OK;
     }
     for (int i = 0; i < n; ++i) {
         const Candidate& c = plan->cands[i];
         if ((kernel < 0 || c.kernel == kernel) && (tb <= 0 || c.tb == tb)) {
             plan->sel = i;
-            plan->modelled = plan->one_step = false;
+            plan->modelled = false;
+            plan->stand_in = kNoStandIn;
             return ST_OK;
         }
     }
@@ -1663,12 +1744,12 @@ st_status stencil_run(st_plan plan, void* grid, void* work, const double* coeffs
         key_push(key, grid);
         key_push(key, work);
         key_push(key, steps);
-        key_push(key, static_cast<int64_t>(plan->sel) * 2 + (plan->one_step ? 1 : 0));
+        key_push(key, static_cast<int64_t>(plan->sel) * 3 + plan->stand_in);
         for (int i = 0; i < plan->npoints; ++i) key_push(key, wcan[i]);
     }
     const Candidate cand = plan->cands[plan->sel];
     return run_graphed(plan, key, s, [&](hipStream_t st) {
-        return run_steps(plan, cand, grid, work, wcan, steps, st, nullptr, plan->one_step);
+        return run_steps(plan, cand, grid, work, wcan, steps, st, nullptr, plan->stand_in);
     });
 }
 
@@ -1688,7 +1769,7 @@ st_status stencil_run_noalloc(st_plan plan, void* grid, const double* coeffs, co
         return r;
     // eager launches whatever the plan's flags (no graph is instantiated
     // here); inside a caller's capture they are recorded into its graph
-    return run_steps(plan, plan->cands[plan->sel], grid, work, wcan, steps, s, nullptr, plan->one_step);
+    return run_steps(plan, plan->cands[plan->sel], grid, work, wcan, steps, s, nullptr, plan->stand_in);
 }
 
 st_status stencil_run_flux(st_plan plan, void* grid, void* work, const double* coeffs, const int64_t* shape,
@@ -1703,7 +1784,7 @@ st_status stencil_run_flux(st_plan plan, void* grid, void* work, const double* c
     // stands in for one without (same states bit for bit: every tiling of a
     // plan gives the same grid)
     Candidate cand = plan->cands[plan->sel];
-    bool one_step = plan->one_step;
+    bool one_step = plan->stand_in == kOneStep;
     if (plan->modelled && plan->bc == kZero) {
         // a launch more per pass where the kernel sums the outflow, two more
         // per step where it does not (about 4 us each): the fastest of the
@@ -1712,7 +1793,7 @@ st_status stencil_run_flux(st_plan plan, void* grid, void* work, const double* c
             if (alone || !flux_fused(plan, c)) return (alone ? step_us(plan, plan->cands.back()) : step_us(plan, c) * c.tb) + 8.0;
             return step_us(plan, c) + 4.0 / c.tb;
         };
-        double best = account(cand, plan->one_step);
+        double best = account(cand, one_step);
         for (const Candidate& c : plan->cands)
             if (c.chunk == plan->cands[0].chunk && c.kernel != ST_KERNEL_NAIVE && flux_fused(plan, c))
                 if (const double us = account(c, false); us < 0.97 * best) {
@@ -1728,7 +1809,7 @@ st_status stencil_run_flux(st_plan plan, void* grid, void* work, const double* c
                 break;
             }
     // a periodic grid has no boundary: nothing leaves
-    return run_steps(plan, cand, grid, work, wcan, steps, s, plan->bc == kZero ? flux : nullptr, one_step);
+    return run_steps(plan, cand, grid, work, wcan, steps, s, plan->bc == kZero ? flux : nullptr, one_step ? kOneStep : kNoStandIn);
 }
 
 }  // extern "C"
@@ -2195,7 +2276,8 @@ st_status batch_autotune(st_plan_s* p) {
         hipEventDestroy(e0);
         hipEventDestroy(e1);
         p->sel = best_i;
-        p->modelled = p->one_step = false;
+        p->modelled = false;
+        p->stand_in = kNoStandIn;
         p->table_shadow.clear();
         p->flags = flags;
         tune_store(tkey, best_i, static_cast<int>(p->cands.size()));

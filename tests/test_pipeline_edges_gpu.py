@@ -225,3 +225,22 @@ def test_varcoef_two_steps_per_pass(dtype, shape):
         want = _varcoef(u0, k, y, dtype, steps, every, True)
         for i, (a, b) in enumerate(zip(got, want)):
             assert np.array_equal(a, b), f"buffer {i} of {len(got)}"
+
+
+# small 2D grids in register tiles (64 rows, 64 to 256 columns, up to 31 steps a
+# pass): the smallest grids they take, one row or column more, tiles moved
+# inward, edge tiles with their own halo, several tiles, rows off the lane grid,
+# and step counts below, at and past a pass's depth, against the one-step kernel
+@pytest.mark.parametrize("dtype", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("bc", ["zero", "periodic"])
+@pytest.mark.parametrize("pattern", ["star", "box"])
+@pytest.mark.parametrize("shape", [(64, 64), (65, 131), (66, 256), (97, 257), (256, 260), (130, 515)])
+def test_2d_small_grids_in_register_tiles(dtype, bc, pattern, shape):
+    import paper_2303_08365_amd as st
+    offs = (synth.star_offsets if pattern == "star" else synth.box_offsets)(2, 1)
+    w = _weights(offs, 51, dtype)
+    u0 = synth.uniform_field(shape, seed=52)
+    plan, naive = st.Plan(offs, shape, dtype, bc), st.Plan(offs, shape, dtype, bc, naive=True)
+    for steps in (1, 2, 5, 16, 33, 64):
+        one = _against_naive(plan, naive, u0, offs, w, steps, bc, dtype, None, f"tiles {dtype} {bc} {pattern} {shape}")
+    check(one, oracle_ref(u0, offs, w, steps, bc, dtype), dtype, steps, "one-step kernel")
