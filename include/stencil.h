@@ -174,8 +174,8 @@ st_status stencil_plan_destroy(st_plan plan);
 /*
  * Describe the plan's current choice.  A plan whose choice is its own (no
  * ST_PLAN_AUTOTUNE, no stencil_plan_select) may still run a grid that is too
- * small to fill the device with tiles one step per launch, or a small 2D grid
- * in register tiles with many steps per launch, with the same bits.
+ * small to fill the device with tiles one step per launch, or a small grid in
+ * register tiles with several steps per launch, with the same bits.
  */
 st_status stencil_plan_info(st_plan plan, st_plan_info* info);
 

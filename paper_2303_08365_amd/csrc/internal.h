@@ -96,6 +96,23 @@ int tile2d_rows();
 hipError_t launch_tile2d(int dtype, int vx, bool box, bool periodic, const Tile2DArgs& a, hipStream_t s);
 
 // ----------------------------------------------------------------------------
+// 3D 7-point star, small grids: bricks in registers, several steps per launch
+// ----------------------------------------------------------------------------
+// Bricks of 64*vx columns x brick3d_edge() rows x planes, per axis (z, y, x)
+// tiles owning `own` cells (the first and last `edge` more); t <= halo steps.
+// Needs a grid of at least one brick, below 2 GiB; periodic also n[2] % vx == 0.
+struct Brick3DArgs {
+    const void* src;
+    void* dst;
+    int32_t n[3], tiles[3], own[3], halo[3], edge[3];
+    int32_t t;
+    double w[7];
+};
+int brick3d_edge();
+// vx: FP64 1, FP32 1 or 2
+hipError_t launch_brick3d(int dtype, int vx, bool periodic, const Brick3DArgs& a, hipStream_t s);
+
+// ----------------------------------------------------------------------------
 // 3D star: planes streamed along z, K rows per lane, LDS edge-row exchange
 // ----------------------------------------------------------------------------
 struct Stream3DArgs {

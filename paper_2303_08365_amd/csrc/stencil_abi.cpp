@@ -147,7 +147,8 @@ int elem_bytes(int dtype) { return dtype == kF64 ? 8 : (dtype == kF32 ? 4 : 2); 
 // ---------------------------------------------------------------------------
 namespace {
 
-constexpr int32_t kKernelTile2D = 100;  // a Candidate's kernel: register tiles, in no plan's list
+// a Candidate's kernel: register tiles and bricks, in no plan's list
+constexpr int32_t kKernelTile2D = 100, kKernelBrick3D = 101;
 enum StandIn { kNoStandIn, kOneStep, kTiles };
 
 // One tiling candidate of a plan.
@@ -644,7 +645,7 @@ double step_us(const st_plan_s* p, const Candidate& c) {
 bool geo_tile(const st_plan_s* p, int vx, int t, Tile2DArgs& a) {
     const int64_t ny = p->n[1], nx = p->n[2];
     const int w = 64 * vx, h = tile2d_rows();
-    if (p->n[0] != 1 || p->batch || p->radius != 1 || p->npoints != (p->cls == kStar ? 5 : 9) || nx < w || ny < h) return false;
+    if (p->batch || p->ndim != 2 || p->radius != 1 || p->npoints != (p->cls == kStar ? 5 : 9) || nx < w || ny < h) return false;
     if (ny * nx * elem_bytes(p->dtype) >= (int64_t(1) << 31) || (p->bc != kZero && nx % vx != 0)) return false;
     std::memset(&a, 0, sizeof(a));
     a.ny = static_cast<int32_t>(ny);
@@ -658,6 +659,26 @@ bool geo_tile(const st_plan_s* p, int vx, int t, Tile2DArgs& a) {
     a.tiles_x = edge_tiles(nx, a.out_w, p->bc == kZero ? a.hx : 0, a.edge_x);
     a.tiles_y = edge_tiles(ny, a.out_h, p->bc == kZero ? a.hy : 0, a.edge_y);
     return static_cast<int64_t>(a.tiles_x) * a.tiles_y < (int64_t(1) << 31);
+}
+
+// The same for bricks (brick3d.hip).
+bool geo_brick(const st_plan_s* p, int vx, int t, Brick3DArgs& a) {
+    if (p->batch || p->ndim != 3 || p->dtype == kBF16 || p->radius != 1 || p->cls != kStar || p->npoints != 7) return false;
+    if (plan_cells(p) * elem_bytes(p->dtype) >= (int64_t(1) << 31) || (p->bc != kZero && p->n[2] % vx != 0)) return false;
+    std::memset(&a, 0, sizeof(a));
+    a.t = t;
+    int64_t bricks = 1;
+    for (int d = 0; d < 3; ++d) {
+        const int size = d == 2 ? 64 * vx : brick3d_edge();
+        if (p->n[d] < size) return false;
+        a.n[d] = static_cast<int32_t>(p->n[d]);
+        a.halo[d] = d == 2 ? static_cast<int32_t>(ceil_div(t, vx) * vx) : t;
+        a.own[d] = size - 2 * a.halo[d];
+        if (a.own[d] <= 0) return false;
+        a.tiles[d] = edge_tiles(p->n[d], a.own[d], p->bc == kZero ? a.halo[d] : 0, a.edge[d]);
+        bricks *= a.tiles[d];
+    }
+    return bricks < (int64_t(1) << 31);
 }
 
 // The fastest register tiles of a plan: us a step.  A step of one work-group on
@@ -691,8 +712,39 @@ double tile_select(st_plan_s* p) {
     return best;
 }
 
+// The fastest bricks of a plan: us a step.  A work-group is 16 waves, one to a
+// CU; a step is its arithmetic (four waves a SIMD) and the edge rows' way through
+// LDS.  Measured us a step, 7 points (plan without bricks): FP32 64^3 7 steps a
+// pass 2.5 (3.8), 89 x 97 x 101 3 steps 3.45 (7.5), 96^3 4 steps 3.0 (5.8), 128^3 4
+// steps of two columns 4.2 (9.1), 192^3 2 steps 11.2 (10.5: planes); FP64 96^3 4.1
+// (6.0), 128^3 7.7 (5.5: planes).
+double brick_select(st_plan_s* p) {
+    double best = 1e300;
+    p->tile = Candidate();
+    p->tile.kernel = kKernelBrick3D;
+    const bool wide = p->dtype == kF64;
+    const int cells = brick3d_edge() * brick3d_edge() / 16;  // a lane's rows
+    for (int vx = 1; vx <= (wide ? 1 : 2); ++vx) {
+        const double us = 4 * kUsPerInstr * (cells * vx * 8 + cells * (wide ? 4 : 2)) +
+                          2.0 * cells * 16 * 64 * vx * elem_bytes(p->dtype) / 128 / 2400 + (wide ? 0.25 : 0.1);
+        for (int t = 1; 2 * t < brick3d_edge(); ++t) {
+            Brick3DArgs a;
+            if (!geo_brick(p, vx, t, a)) break;
+            const int64_t bricks = static_cast<int64_t>(a.tiles[0]) * a.tiles[1] * a.tiles[2];
+            const double pass = (p->bc == kZero ? 4.5 : 5.7) + t * us +
+                                static_cast<double>(ceil_div(bricks, device_cus()) - 1) * (2.9 + 1.15 * t * us);
+            if (pass / t < best) {
+                best = pass / t;
+                p->tile.tb = t;
+                p->tile.k2.vx = vx;
+            }
+        }
+    }
+    return best;
+}
+
 // Selection of a plan that is not autotuned: the family's fastest candidate
-// with a model chunk, and whether one step per launch beats it.
+// with a model chunk, and whether one step per launch or tiles in registers beat it.
 void model_select(st_plan_s* p, bool fixed) {
     p->sel = 0;
     p->modelled = false;
@@ -721,7 +773,7 @@ void model_select(st_plan_s* p, bool fixed) {
         best = step_us(p, p->cands.back());
         p->stand_in = kOneStep;
     }
-    if (const double us = tile_select(p); us < 0.9 * best) p->stand_in = kTiles;
+    if (const double us = p->ndim == 2 ? tile_select(p) : brick_select(p); us < 0.9 * best) p->stand_in = kTiles;
 }
 
 // Default fused depth and lane width per family.
@@ -1061,6 +1113,16 @@ st_status launch_pass(const st_plan_s* p, const Candidate& c, const void* src, v
                       const double* wcan, int tb, hipStream_t s, double* fpart = nullptr) {
     hipError_t e = hipSuccess;
     const bool elems = elem_aligned(src, p->dtype) && elem_aligned(dst, p->dtype);
+    if (c.kernel == kKernelBrick3D) {
+        Brick3DArgs a;
+        if (!geo_brick(p, c.k2.vx, tb, a)) return fail(ST_ERR_UNSUPPORTED, "tiling infeasible");
+        a.src = src;
+        a.dst = dst;
+        for (int i = 0; i < p->npoints; ++i) a.w[i] = wcan[i];
+        e = launch_brick3d(p->dtype, c.k2.vx, p->bc != kZero, a, s);
+        if (e != hipSuccess) return hip_fail(e, "register brick launch");
+        return ST_OK;
+    }
     if (c.kernel == kKernelTile2D) {
         Tile2DArgs a;
         if (!geo_tile(p, c.k2.vx, tb, a)) return fail(ST_ERR_UNSUPPORTED, "tiling infeasible");

@@ -244,3 +244,21 @@ def test_2d_small_grids_in_register_tiles(dtype, bc, pattern, shape):
     for steps in (1, 2, 5, 16, 33, 64):
         one = _against_naive(plan, naive, u0, offs, w, steps, bc, dtype, None, f"tiles {dtype} {bc} {pattern} {shape}")
     check(one, oracle_ref(u0, offs, w, steps, bc, dtype), dtype, steps, "one-step kernel")
+
+
+# small 3D grids in register bricks (16 rows, 16 planes, 64 or 128 columns, up to 7
+# steps a pass): the smallest grids they take, one cell more per axis, edge bricks
+# with their own halo, several bricks, rows off the lane grid, against the
+# one-step kernel
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("bc", ["zero", "periodic"])
+@pytest.mark.parametrize("shape", [(16, 16, 64), (17, 18, 65), (16, 33, 128), (40, 21, 131), (64, 64, 64), (30, 50, 190)])
+def test_3d_small_grids_in_register_bricks(dtype, bc, shape):
+    import paper_2303_08365_amd as st
+    offs = synth.star_offsets(3, 1)
+    w = _weights(offs, 61, dtype)
+    u0 = synth.uniform_field(shape, seed=62)
+    plan, naive = st.Plan(offs, shape, dtype, bc), st.Plan(offs, shape, dtype, bc, naive=True)
+    for steps in (1, 2, 5, 7, 16, 30):
+        one = _against_naive(plan, naive, u0, offs, w, steps, bc, dtype, None, f"bricks {dtype} {bc} {shape}")
+    check(one, oracle_ref(u0, offs, w, steps, bc, dtype), dtype, steps, "one-step kernel")
