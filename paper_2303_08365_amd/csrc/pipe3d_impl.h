@@ -28,8 +28,8 @@
 // two thirds of the registers and a quarter of the barriers (four fused
 // steps), with the same arithmetic bit for bit.
 //
-// Input planes arrive one of two ways.  PD planes ahead in registers: the
-// loads of plane z+PD are issued when plane z enters.  Or (LQ) two planes
+// Input planes arrive one of two ways.  One plane ahead in registers: the
+// loads of plane z+1 are issued when plane z enters.  Or (LQ) two planes
 // ahead through a two-slot LDS queue that buffer-to-LDS loads fill: no
 // register holds a plane in flight, the loads have two iterations to land,
 // and a wave reads its rows back from LDS when the plane enters.  Counted on
@@ -80,7 +80,7 @@ struct Pipe {
     using TC = typename S::TC;
     static_assert(NW >= 2 && K >= 2, "a tile needs two waves of two rows");
     static_assert(NB == 1 || NB == 2, "one or two LDS buffers");
-    static_assert(PD >= 1 && PD <= 2, "one or two planes prefetched");
+    static_assert(PD == (LQ ? 2 : 1), "planes prefetched");
     static_assert(!FLX || !PER, "outflow: zero rule only (a periodic grid has no boundary)");
     static constexpr int W = 64 * VX;
     static constexpr int H = NW * K;
@@ -110,6 +110,16 @@ struct Pipe {
     static constexpr int QROW_BYTES = W * static_cast<int>(sizeof(TS));
     static constexpr int QSLOT_BYTES = QROWS * QROW_BYTES;
     static constexpr int Q_BYTES = LQ ? 2 * QSLOT_BYTES : 16;
+    // Planes per loop trip.  With two, planes change registers without being
+    // copied (FP64: 32 copies a plane instead of 64, of 354 vector instructions)
+    // and, no branch splitting the body, four fused FP64 steps need 206 VGPRs
+    // instead of 232.  512^3, us a pass, one plane a trip and two: FP64 520 and
+    // 504, FP32 (8 rows) 320 and 304, outflow FP32 397 and 385, bfloat16 328 and
+    // 317.  One where two spill: bfloat16 6 x 4 (217 and 375) and four steps of
+    // it, and where it gains nothing: the FP64 outflow twin.  A second plane
+    // prefetched fits FP64 then (228 VGPRs) and gains nothing (511).
+    static constexpr int kTrip =
+        LQ || (FLX && sizeof(TC) == 8) || (sizeof(TS) == 2 && TBMAX * K * VX > 48) ? 1 : 2;
     static constexpr int LDS_BYTES = DYN_BYTES + (LQ ? Q_BYTES : 0);
     static constexpr uint32_t kOut = 0x80000000u;  // past the end of any plane (planes < 2 GiB)
     static constexpr int32_t kRsrcWord3 = 0x00020000;  // gfx9: raw 32-bit data
@@ -145,16 +155,37 @@ struct Pipe {
     static __device__ __forceinline__ bool zghost(int32_t z, int32_t nz) {
         return !PER && static_cast<uint32_t>(z) >= static_cast<uint32_t>(nz);
     }
+    // All ones where 0 <= i < n, else 0.  Two planes per trip: planes outside are
+    // masked, not branched around (a branch splits the loop's body, and the
+    // compiler moves partial sums behind it, where their operands live longer).
+    static __device__ __forceinline__ int32_t inside(int32_t i, int32_t n) {
+        if constexpr (kTrip == 2) return ~((i | (n - 1 - i)) >> 31);
+        else return static_cast<uint32_t>(i) < static_cast<uint32_t>(n) ? -1 : 0;
+    }
+    // w, or 0 for a ghost plane
+    static __device__ __forceinline__ TC unless_ghost(TC w, int32_t z, int32_t nz) {
+        if constexpr (PER) return w;
+        if constexpr (kTrip == 1) return zghost(z, nz) ? TC(0) : w;
+        const int32_t keep = inside(z, nz);
+        if constexpr (sizeof(TC) == 8)
+            return __longlong_as_double(__double_as_longlong(w) & static_cast<int64_t>(keep));
+        else
+            return __int_as_float(__float_as_int(w) & keep);
+    }
+    static __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane(const Ctx& c, const TS* p, int32_t z, int32_t keep) {
+        if constexpr (kTrip == 1) {
+            const TS* base = keep ? p + static_cast<int64_t>(z) * (c.plane_bytes / sizeof(TS)) : p;
+            return __builtin_amdgcn_make_buffer_rsrc(const_cast<TS*>(base), 0, keep ? c.plane_bytes : 0, kRsrcWord3);
+        }
+        const TS* base = p + static_cast<int64_t>(z & keep) * (c.plane_bytes / sizeof(TS));
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<TS*>(base), 0, c.plane_bytes & keep, kRsrcWord3);
+    }
     static __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_in(const Ctx& c, int32_t zin) {
-        const int32_t zz = PER ? wrap_idx(zin < c.zlast ? zin : c.zlast, c.nz) : (zin < c.zlast ? zin : c.zlast);
-        const bool out = zghost(zz, c.nz);
-        const TS* base = out ? c.src : c.src + static_cast<int64_t>(zz) * (c.plane_bytes / sizeof(TS));
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<TS*>(base), 0, out ? 0 : c.plane_bytes, kRsrcWord3);
+        const int32_t zc = zin < c.zlast ? zin : c.zlast, zz = PER ? wrap_idx(zc, c.nz) : zc;
+        return plane(c, c.src, zz, PER ? -1 : inside(zz, c.nz));
     }
     static __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_out(const Ctx& c, int32_t z) {
-        const bool ok = static_cast<uint32_t>(z - c.zs) < static_cast<uint32_t>(c.ze - c.zs);
-        TS* base = ok ? c.dst + static_cast<int64_t>(z) * (c.plane_bytes / sizeof(TS)) : c.dst;
-        return __builtin_amdgcn_make_buffer_rsrc(base, 0, ok ? c.plane_bytes : 0, kRsrcWord3);
+        return plane(c, c.dst, z, inside(z - c.zs, c.ze - c.zs));
     }
 
     static __device__ __forceinline__ void ldrow(__amdgpu_buffer_rsrc_t r, uint32_t vo, TC (&v)[VX]) {
@@ -356,13 +387,13 @@ struct Pipe {
     struct State {
         TC prev[TB][K][VX];   // u_l(z-1)
         TC pend[TB][K][VX];   // P_l(z-1): u_{l+1}(z-1) short of its z+1 term
-        TC pf[PD][K][VX];     // prefetched input planes
-        TC hpf[PD][VX];       // their halo rows
+        TC pf[K][VX];         // prefetched input plane
+        TC hpf[VX];           // its halo row
         Flux fx;              // FLX only
     };
 
     // One iteration: input plane zin enters level 0.
-    template <int TB, int J>
+    template <int TB>
     static __device__ __forceinline__ void step(const Ctx& c, int32_t it, int32_t zfirst, State<TB>& s, TC* lds) {
         const int32_t zin = zfirst + it;
         TC cur[K][VX];  // the new plane of the level at hand: u_l(zin-l)
@@ -378,7 +409,7 @@ struct Pipe {
 #pragma unroll
             for (int k = 0; k < K; ++k)
 #pragma unroll
-                for (int e = 0; e < VX; ++e) cur[k][e] = s.pf[J][k][e];
+                for (int e = 0; e < VX; ++e) cur[k][e] = s.pf[k][e];
             // Level 0's halo row goes to LDS before the next plane's loads
             // are issued: its registers are then free to receive them.
             // (Written later, the halo would stay live across the loads, the
@@ -388,8 +419,8 @@ struct Pipe {
             // previous barrier.
             TC* lv = buf + c.hslot * W + c.lane * VX;
 #pragma unroll
-            for (int e = 0; e < VX; ++e) lv[e] = s.hpf[J][e];
-            load_plane(c, zin + PD, s.pf[J], s.hpf[J]);
+            for (int e = 0; e < VX; ++e) lv[e] = s.hpf[e];
+            load_plane(c, zin + 1, s.pf, s.hpf);
         }
 
         // FP64: phases A and B run at a raised wave priority: they form the
@@ -409,7 +440,7 @@ struct Pipe {
         TC nw[kEarly ? 1 : TB][K][VX];
 #pragma unroll
         for (int l = 0; l < TB; ++l) {
-            const TC w6 = (l > 0 && zghost(zin - l, c.nz)) ? TC(0) : c.w[6];
+            const TC w6 = l > 0 ? unless_ghost(c.w[6], zin - l, c.nz) : c.w[6];
             TC nxt[K][VX];
             if (l + 1 < TB) {
 #pragma unroll
@@ -427,7 +458,7 @@ struct Pipe {
                 }
             }
             if constexpr (kEarly) {
-                const TC w1 = (l > 0 && zghost(zin - l - 1, c.nz)) ? TC(0) : c.w[1];
+                const TC w1 = l > 0 ? unless_ghost(c.w[1], zin - l - 1, c.nz) : c.w[1];
 #pragma unroll
                 for (int k = 0; k < K; ++k)
 #pragma unroll
@@ -485,7 +516,7 @@ struct Pipe {
 #pragma unroll
         for (int l = 0; l < TB; ++l) {
             const TC (&u)[K][VX] = kEarly ? s.prev[l] : nw[kEarly ? 0 : l];
-            const TC w1 = (l > 0 && zghost(zin - l - 1, c.nz)) ? TC(0) : c.w[1];
+            const TC w1 = l > 0 ? unless_ghost(c.w[1], zin - l - 1, c.nz) : c.w[1];
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 const TC lft = from_lower_z(u[k][VX - 1]);
@@ -503,17 +534,6 @@ struct Pipe {
             }
         }
         if constexpr (NB == 1) sync();  // the next iteration rewrites the buffer
-    }
-
-    template <int TB, int... J>
-    static __device__ __forceinline__ void group(const Ctx& c, int32_t base, int32_t zfirst, State<TB>& s, TC* lds,
-                                                 std::integer_sequence<int, J...>) {
-        (step<TB, J>(c, base + J, zfirst, s, lds), ...);
-    }
-    template <int TB, int... J>
-    static __device__ __forceinline__ void tail(const Ctx& c, int32_t base, int32_t nit, int32_t zfirst, State<TB>& s,
-                                                TC* lds, std::integer_sequence<int, J...>) {
-        ((base + J < nit ? step<TB, J>(c, base + J, zfirst, s, lds) : void()), ...);
     }
 
     template <int TB>
@@ -555,19 +575,25 @@ struct Pipe {
 #pragma unroll
                 for (int k = 0; k < K; ++k) strow(none, c.so[k], zero);
             }
-            for (int32_t it = 0; it < nit; ++it) step<TB, 0>(c, it, zfirst, s, lds);
+            for (int32_t it = 0; it < nit; ++it) step<TB>(c, it, zfirst, s, lds);
             // the last two iterations' queue loads (planes past the chunk,
             // never read) land before the work-group's LDS is released
             __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0); expcnt, lgkmcnt: any
         } else {
-#pragma unroll
-            for (int p = 0; p < PD; ++p) load_plane(c, zfirst + p, s.pf[p], s.hpf[p]);
+            load_plane(c, zfirst, s.pf, s.hpf);
 #pragma unroll
             for (int k = 0; k < K; ++k) strow(none, c.so[k], zero);
-            int32_t base = 0;
-            for (; base + PD <= nit; base += PD)
-                group<TB>(c, base, zfirst, s, lds, std::make_integer_sequence<int, PD>{});
-            tail<TB>(c, base, nit, zfirst, s, lds, std::make_integer_sequence<int, PD>{});
+            if constexpr (kTrip == 2) {
+                // (an odd count takes in one plane more: nothing of it is stored)
+                for (int32_t it = 0; it < nit; it += 2) {
+                    step<TB>(c, it, zfirst, s, lds);
+                    __builtin_amdgcn_sched_barrier(0);
+                    step<TB>(c, it + 1, zfirst, s, lds);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            } else {
+                for (int32_t it = 0; it < nit; ++it) step<TB>(c, it, zfirst, s, lds);
+            }
         }
         if constexpr (FLX) flux_store(c, s.fx);
     }
