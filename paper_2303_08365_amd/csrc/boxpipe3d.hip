@@ -29,7 +29,13 @@
 // therefore exact on the tile shrunk by one row and two columns per side;
 // under the zero rule a tile that would cross the grid edge is moved inward
 // to touch it, where the zeros are the ghost layer.  Level 1's ghost planes
-// are set to 0 explicitly (one select per value).
+// are set to 0 explicitly (masked).
+//
+// What bounds it: vector instructions, 80 % of them the FMAs (FP64, 2 x 4: 432 of
+// 540 a plane).  Two planes per loop trip, with no branch in its body, rename
+// registers where one plane a trip copied 54 and needed 225 of them (now 197,
+// x neighbours kept from one plane to the next included, and four rows fit).
+// 512^3 us a step: FP64 281 -> 243, bfloat16 208 -> 175, FP32 211 -> 200.
 //
 // Memory access: one buffer descriptor per plane (empty for a ghost plane)
 // and a 32-bit vector offset per row fixed for the pass; rows outside the
@@ -82,18 +88,23 @@ struct Pipe {
         if constexpr (sizeof(TC) == 8) return uni(v);
         else return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
     }
-    static __device__ __forceinline__ bool zghost(int32_t z, int32_t nz) {
-        return static_cast<uint32_t>(z) >= static_cast<uint32_t>(nz);
+    // All ones where 0 <= i < n, else 0: planes outside are masked, not branched
+    // around (a branch splits the loop's body, and the compiler moves partial
+    // sums behind it, where their operands live longer).
+    static __device__ __forceinline__ int32_t inside(int32_t i, int32_t n) { return ~((i | (n - 1 - i)) >> 31); }
+    static __device__ __forceinline__ TC masked(TC v, int32_t keep) {
+        if constexpr (sizeof(TC) == 8) return __longlong_as_double(__double_as_longlong(v) & static_cast<int64_t>(keep));
+        else return __int_as_float(__float_as_int(v) & keep);
+    }
+    static __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_of(const Ctx& c, const TS* p, int32_t z, int32_t keep) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<TS*>(p) + static_cast<int64_t>(z & keep) * c.plane_elems, 0,
+                                                 c.plane_bytes & keep, kRsrcWord3);
     }
     static __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_in(const Ctx& c, int32_t z) {
-        const bool out = zghost(z, c.nz);
-        const TS* base = out ? c.src : c.src + static_cast<int64_t>(z) * c.plane_elems;
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<TS*>(base), 0, out ? 0 : c.plane_bytes, kRsrcWord3);
+        return plane_of(c, c.src, z, inside(z, c.nz));
     }
     static __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_out(const Ctx& c, int32_t z) {
-        const bool ok = static_cast<uint32_t>(z - c.zs) < static_cast<uint32_t>(c.ze - c.zs);
-        TS* base = ok ? c.dst + static_cast<int64_t>(z) * c.plane_elems : c.dst;
-        return __builtin_amdgcn_make_buffer_rsrc(base, 0, ok ? c.plane_bytes : 0, kRsrcWord3);
+        return plane_of(c, c.dst, z, inside(z - c.zs, c.ze - c.zs));
     }
 
     static __device__ __forceinline__ void ldrow(__amdgpu_buffer_rsrc_t r, uint32_t vo, TC (&v)[VX]) {
@@ -226,6 +237,54 @@ struct Pipe {
             for (int e = 0; e < VX; ++e) prev[i][e] = u[i][e];
     }
 
+    struct State {
+        TC pf[R][VX];                            // the next input plane
+        TC u0p[R][VX], P0[K][VX], x1[K][VX];     // level 0: previous plane, partial sum, its newest result
+        TC u1p[R][VX], P1[K][VX];                // level 1
+    };
+
+    // One input plane zin; rb, wb: the lane's place in the exchange buffers of
+    // the previous plane and of this one.
+    static __device__ __forceinline__ void plane(const Ctx& c, int32_t zin, const TC* rb, TC* wb, State& s) {
+        __syncthreads();
+        if constexpr (PR) __builtin_amdgcn_s_setprio(1);
+        TC u0[R][VX];
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+#pragma unroll
+            for (int e = 0; e < VX; ++e) u0[i][e] = s.pf[i][e];
+        load_plane(c, zin + 1, s.pf);
+        // level 1's plane from the previous iteration, with the rows
+        // above and below from the neighbouring waves
+        TC u1[R][VX];
+#pragma unroll
+        for (int e = 0; e < VX; ++e) {
+            u1[0][e] = rb[e];
+            u1[R - 1][e] = rb[3 * W + e];
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int e = 0; e < VX; ++e) u1[k + 1][e] = s.x1[k][e];
+        TC o0[K][VX];
+        level(c, u0, s.u0p, s.P0, o0);
+        const int32_t keep = inside(zin - 1, c.nz);
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int e = 0; e < VX; ++e) s.x1[k][e] = masked(S::round(o0[k][e]), keep);
+#pragma unroll
+        for (int e = 0; e < VX; ++e) {
+            wb[W + e] = s.x1[0][e];
+            wb[2 * W + e] = s.x1[K - 1][e];
+        }
+        if constexpr (PR) __builtin_amdgcn_s_setprio(0);
+        TC o1[K][VX];
+        level(c, u1, s.u1p, s.P1, o1);
+        store_plane(c, zin - 3, o1);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+
     static __device__ __forceinline__ void run(const Box3DArgs& a, TC* lds) {
         Ctx c;
         c.lane = threadIdx.x & 63;
@@ -278,61 +337,28 @@ struct Pipe {
         // both exchange buffers start at 0 (the zero rows are never written)
         for (int i = static_cast<int>(threadIdx.x); i < 2 * BUF; i += 64 * NW) lds[i] = TC(0);
 
-        TC pf[R][VX], u0p[R][VX], P0[K][VX], x1[K][VX], u1p[R][VX], P1[K][VX];
+        State s;
 #pragma unroll
         for (int i = 0; i < R; ++i)
 #pragma unroll
-            for (int e = 0; e < VX; ++e) u0p[i][e] = u1p[i][e] = TC(0);
+            for (int e = 0; e < VX; ++e) s.u0p[i][e] = s.u1p[i][e] = TC(0);
 #pragma unroll
         for (int k = 0; k < K; ++k)
 #pragma unroll
-            for (int e = 0; e < VX; ++e) P0[k][e] = x1[k][e] = P1[k][e] = TC(0);
+            for (int e = 0; e < VX; ++e) s.P0[k][e] = s.x1[k][e] = s.P1[k][e] = TC(0);
 
         // input planes zs-2 .. ze+2: the plane taken in iteration zin
         // finishes level 1's plane zin-1 and level 2's plane zin-3
         const int32_t zfirst = c.zs - 2, nit = c.ze - c.zs + 5;
         const int rd = 2 * c.wave * W + c.lane * VX;  // this lane's place in slot 2w
-        load_plane(c, zfirst, pf);
-        for (int32_t it = 0; it < nit; ++it) {
-            const int32_t zin = zfirst + it;
-            __syncthreads();
-            if constexpr (PR) __builtin_amdgcn_s_setprio(1);
-            TC u0[R][VX];
-#pragma unroll
-            for (int i = 0; i < R; ++i)
-#pragma unroll
-                for (int e = 0; e < VX; ++e) u0[i][e] = pf[i][e];
-            load_plane(c, zin + 1, pf);
-            // level 1's plane from the previous iteration, with the rows
-            // above and below from the neighbouring waves
-            TC u1[R][VX];
-            const TC* rb = lds + ((it + 1) & 1) * BUF + rd;
-#pragma unroll
-            for (int e = 0; e < VX; ++e) {
-                u1[0][e] = rb[e];
-                u1[R - 1][e] = rb[3 * W + e];
-            }
-#pragma unroll
-            for (int k = 0; k < K; ++k)
-#pragma unroll
-                for (int e = 0; e < VX; ++e) u1[k + 1][e] = x1[k][e];
-            TC o0[K][VX];
-            level(c, u0, u0p, P0, o0);
-            const bool g = zghost(zin - 1, nz);
-#pragma unroll
-            for (int k = 0; k < K; ++k)
-#pragma unroll
-                for (int e = 0; e < VX; ++e) x1[k][e] = g ? TC(0) : S::round(o0[k][e]);
-            TC* wb = lds + (it & 1) * BUF + rd;
-#pragma unroll
-            for (int e = 0; e < VX; ++e) {
-                wb[W + e] = x1[0][e];
-                wb[2 * W + e] = x1[K - 1][e];
-            }
-            if constexpr (PR) __builtin_amdgcn_s_setprio(0);
-            TC o1[K][VX];
-            level(c, u1, u1p, P1, o1);
-            store_plane(c, zin - 3, o1);
+        load_plane(c, zfirst, s.pf);
+        // two planes per trip (an odd count takes in one plane more, whose store
+        // falls outside the chunk)
+        TC* b0 = lds + rd;
+        TC* b1 = lds + BUF + rd;
+        for (int32_t it = 0; it < nit; it += 2) {
+            plane(c, zfirst + it, b1, b0, s);
+            plane(c, zfirst + it + 1, b0, b1, s);
         }
     }
 };
@@ -359,14 +385,18 @@ constexpr BoxPipeShape shape_t() {
 
 }  // namespace bp3d
 
-// Instances per type (columns x rows a lane, 8 waves): FP64 2 x 3 (level 0
-// at wave priority 1: 476 against 472 Gcell/s at 512^3) and 3 x 2 (2 x 4 and
-// 3 x 3 spill), FP32 2 x 6, bfloat16 4 x 4.
-int boxpipe3d_variants(int dtype) { return dtype == kF64 ? 2 : (dtype == kF32 || dtype == kBF16 ? 1 : 0); }
+// Instances per type (columns x rows a lane, 8 waves): FP64 2 x 3 (level 0 at
+// wave priority 1: +1 % at 512^3), 3 x 2 (rows that 186 columns fit better:
+// 251 x 319 x 377 61.5 us a step, 67 at 2 x 3) and 2 x 4 (large grids: 512^3 243 us
+// a step against 260 at 2 x 3; 128^3 13.0 against 11.0), FP32 2 x 6 (2 x 8: no
+// gain), bfloat16 4 x 4.
+int boxpipe3d_variants(int dtype) { return dtype == kF64 ? 3 : (dtype == kF32 || dtype == kBF16 ? 1 : 0); }
 
 BoxPipeShape boxpipe3d_shape(int dtype, int v) {
     switch (dtype) {
-        case kF64: return v == 0 ? bp3d::shape_t<double, 2, 3, 8, true>() : bp3d::shape_t<double, 3, 2, 8>();
+        case kF64:
+            return v == 0 ? bp3d::shape_t<double, 2, 3, 8, true>()
+                          : (v == 1 ? bp3d::shape_t<double, 3, 2, 8>() : bp3d::shape_t<double, 2, 4, 8, true>());
         case kF32: return bp3d::shape_t<float, 2, 6, 8>();
         default: return bp3d::shape_t<bf16s, 4, 4, 8>();
     }
@@ -375,7 +405,9 @@ BoxPipeShape boxpipe3d_shape(int dtype, int v) {
 hipError_t launch_boxpipe3d(int dtype, int v, const Box3DArgs& a, hipStream_t s) {
     if (static_cast<int64_t>(a.tiles_x) * a.tiles_y * a.chunks_z <= 0) return hipSuccess;
     switch (dtype) {
-        case kF64: return v == 0 ? bp3d::launch_t<double, 2, 3, 8, true>(a, s) : bp3d::launch_t<double, 3, 2, 8>(a, s);
+        case kF64:
+            return v == 0 ? bp3d::launch_t<double, 2, 3, 8, true>(a, s)
+                          : (v == 1 ? bp3d::launch_t<double, 3, 2, 8>(a, s) : bp3d::launch_t<double, 2, 4, 8, true>(a, s));
         case kF32: return bp3d::launch_t<float, 2, 6, 8>(a, s);
         case kBF16: return bp3d::launch_t<bf16s, 4, 4, 8>(a, s);
         default: return hipErrorInvalidValue;

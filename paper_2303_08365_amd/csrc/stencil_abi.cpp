@@ -480,7 +480,7 @@ double box_us(const st_plan_s* p, const Candidate& c, int tb, int64_t per_plane,
         const BoxPipeShape sh = boxpipe3d_shape(p->dtype, c.bpipe - 1);
         const double us = kUsPerInstr * (2 * sh.k * sh.vx * (27 + (p->dtype == kBF16 ? 2 : 0)) + 4 * (sh.k + 2) * 2 * dw);
         return planes_us(3.7, 4.8, groups, 1, sh.block / 64, len + 5, len,
-                         (0.8 + 1.83 * us) * (p->dtype == kF64 ? 1.0 : 1.1), 0.0, grid);
+                         (0.8 + (p->dtype == kF64 && sh.k == 4 ? 2.2 : 1.83) * us) * (p->dtype == kF64 ? 1.0 : 1.1), 0.0, grid);
     }
     const Box3DShape sh = box3d_shape(p->dtype, tb);
     const int waves = sh.block / 64, k = sh.h / waves;
