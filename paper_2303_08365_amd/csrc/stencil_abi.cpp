@@ -548,7 +548,17 @@ double star3_us(const Candidate& c, const int64_t n[3], int tb, int64_t per_plan
     const double len = static_cast<double>(std::min(chunk, n[0])), nit = len + 2 * R * tb;
     const double grid = static_cast<double>(n[0]) * static_cast<double>(n[1]) * static_cast<double>(n[2]) * esz;
     const double us = kUsPerInstr * (tb * K * (vx * (6 * R + 1 + (c.k3.dtype == kBF16 ? 2 : 0)) + 2 * R * dw) + 8 * K);
-    if (c.k3.pipe) return planes_us(3.9, 4.8, groups, 1, c.k3.nw, nit, len, 0.8 + 1.88 * us, 0.0, grid);
+    if (c.k3.pipe) {
+        // us a plane.  Fitted again to the forms with two planes per loop trip:
+        // FP32 with four columns a lane (0.49 of arithmetic: 1.54 measured, 0.85:
+        // 2.25) and bfloat16 with four rows up to three steps (0.81 at three: 1.86
+        // to 1.96; two steps 1.33 on aligned rows, 1.65 on odd ones); the others
+        // stay within 6 % of the first line.
+        double plane = 0.8 + 1.88 * us;
+        if (c.k3.dtype == kF32 && vx == 4) plane = 0.3 + 2.4 * us;
+        if (c.k3.dtype == kBF16 && K == 4 && c.k3.tbmax == 3) plane = (tb == 2 ? 0.45 : 0.2) + 2.1 * us;
+        return planes_us(3.9, 4.8, groups, 1, c.k3.nw, nit, len, plane, 0.0, grid);
+    }
     if (R > 1) {  // one step; the loads of the halo rows set the pace
         const double lat = c.k3.dtype == kF64 ? 1.85 : (c.k3.dtype == kF32 ? 1.5 : 1.35);
         return planes_us(4.0, 5.4, groups, 1, c.k3.nw, nit, len, lat * (vec ? 1.0 : 1.2), 0.0, grid);
