@@ -111,7 +111,7 @@ __global__ __launch_bounds__(256) void varcoef_adjoint_kernel(const VarcoefArgs 
             ng += 1;
         }
     }
-    gacc = fma_c(-static_cast<TC>(ng) * uc, lc, gacc);
+    if (ng > 0) gacc = fma_c(-static_cast<TC>(ng) * uc, lc, gacc);
     st1(out + i, fma_c(alpha, acc, lc));
     if (a.grad != nullptr) st1(g + i, fma_c(alpha, gacc, ld1(g + i)));
 }

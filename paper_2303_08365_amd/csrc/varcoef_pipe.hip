@@ -188,7 +188,8 @@ struct Pipe {
                     const T du = T(0.5) * (u[i][e] - s.uprev[i][e]);
                     const T g = fma_c(du, -d, s.gacc[i][e]);
                     const int ng = ngz + c.ngy[i] + c.ngx[e];
-                    gout[i][e] = fma_c(-static_cast<T>(ng) * s.uprev[i][e], s.prev[i][e], g);
+                    // (a cell without ghost faces keeps its sum, also where u is infinite)
+                    gout[i][e] = fma_c(-static_cast<T>(ng) * (ng > 0 ? s.uprev[i][e] : T(0)), s.prev[i][e], g);
                     s.gacc[i][e] = fma_c(-du, d, T(0));
                 }
             }

@@ -262,3 +262,16 @@ def test_3d_small_grids_in_register_bricks(dtype, bc, shape):
     for steps in (1, 2, 5, 7, 16, 30):
         one = _against_naive(plan, naive, u0, offs, w, steps, bc, dtype, None, f"bricks {dtype} {bc} {shape}")
     check(one, oracle_ref(u0, offs, w, steps, bc, dtype), dtype, steps, "one-step kernel")
+
+
+# an infinite value inside the grid reaches the same cells, as the same values,
+# through one pass of two steps as through two of one
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_varcoef_infinite_value_inside(dtype):
+    shape = (9, 95, 512)
+    rng = np.random.default_rng(7)
+    u0, k, y = rng.random(shape), 0.5 + rng.random(shape), rng.random(shape)
+    u0[4, 50, 200] = np.inf
+    got, want = (_varcoef(u0, k, y, dtype, 2, 2, naive) for naive in (False, True))
+    for i, (a, b) in enumerate(zip(got, want)):
+        assert np.array_equal(a, b, equal_nan=True), f"buffer {i}"
