@@ -79,21 +79,21 @@ bool stream2d_has(const Stream2DKey& k);
 int stream2d_occupancy(const Stream2DKey& k);  // work-groups per CU, 0 if unknown
 
 // ----------------------------------------------------------------------------
-// 2D, radius 1, small grids: tiles in registers, many steps per launch
+// 2D, radius 1 and 2, small grids: tiles in registers, many steps per launch
 // ----------------------------------------------------------------------------
 // Tiles of 64*vx columns x tile2d_rows() rows own out_w x out_h cells each (the
-// first and last edge_x / edge_y more) and advance t steps; hx >= t and hy = t.
+// first and last edge_x / edge_y more) and advance t steps; hx >= R*t and hy = R*t.
 // Needs a grid of at least one tile, below 2 GiB; periodic also nx % vx == 0.
 struct Tile2DArgs {
     const void* src;
     void* dst;
     int32_t ny, nx, t;
     int32_t tiles_x, tiles_y, out_w, out_h, hx, hy, edge_x, edge_y;
-    double w[9];
+    double w[25];
 };
 int tile2d_rows();
-// vx: FP64 and FP32 1 or 2, bfloat16 4
-hipError_t launch_tile2d(int dtype, int vx, bool box, bool periodic, const Tile2DArgs& a, hipStream_t s);
+// vx: FP64 and FP32 1 (radius 1) or 2, bfloat16 4
+hipError_t launch_tile2d(int dtype, int radius, int vx, bool box, bool periodic, const Tile2DArgs& a, hipStream_t s);
 
 // ----------------------------------------------------------------------------
 // 3D 7-point star, small grids: bricks in registers, several steps per launch

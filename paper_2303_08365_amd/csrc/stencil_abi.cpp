@@ -655,16 +655,17 @@ double step_us(const st_plan_s* p, const Candidate& c) {
 bool geo_tile(const st_plan_s* p, int vx, int t, Tile2DArgs& a) {
     const int64_t ny = p->n[1], nx = p->n[2];
     const int w = 64 * vx, h = tile2d_rows();
-    if (p->batch || p->ndim != 2 || p->radius != 1 || p->npoints != (p->cls == kStar ? 5 : 9) || nx < w || ny < h) return false;
+    const int R = p->radius;
+    if (p->batch || p->ndim != 2 || R > 2 || vx < R || p->npoints != (p->cls == kStar ? 4 * R + 1 : (2 * R + 1) * (2 * R + 1)) || nx < w || ny < h) return false;
     if (ny * nx * elem_bytes(p->dtype) >= (int64_t(1) << 31) || (p->bc != kZero && nx % vx != 0)) return false;
     std::memset(&a, 0, sizeof(a));
     a.ny = static_cast<int32_t>(ny);
     a.nx = static_cast<int32_t>(nx);
     a.t = t;
-    a.hx = static_cast<int32_t>(ceil_div(t, vx) * vx);
-    a.hy = t;
+    a.hx = static_cast<int32_t>(ceil_div(R * t, vx) * vx);
+    a.hy = R * t;
     a.out_w = w - 2 * a.hx;
-    a.out_h = h - 2 * t;
+    a.out_h = h - 2 * a.hy;
     if (a.out_w <= 0 || a.out_h <= 0) return false;
     a.tiles_x = edge_tiles(nx, a.out_w, p->bc == kZero ? a.hx : 0, a.edge_x);
     a.tiles_y = edge_tiles(ny, a.out_h, p->bc == kZero ? a.hy : 0, a.edge_y);
@@ -698,20 +699,22 @@ bool geo_brick(const st_plan_s* p, int vx, int t, Brick3DArgs& a) {
 // 1.23), 512^2 16 steps 0.63 (1.30), 1024^2 12 steps of two columns 0.89 (1.60),
 // 2048^2 2.36 (3.28), 4096^2 8 steps 7.5 (8.2: the rows are kept); FP32 9 points
 // 256^2 0.55 (1.94), 2048^2 2.64 (3.28).  The model is within 12 % of all of them.
+// Radius 2 fills the registers of two work-groups a CU: further ones cost about
+// half more (FP64 25 points: 1024^2 2.9 in tiles, 4.8 in rows; 3000^2 16.2 and 15.3).
 double tile_select(st_plan_s* p) {
     double best = 1e300;
     p->tile = Candidate();
     p->tile.kernel = kKernelTile2D;
     const int dw = p->dtype == kF64 ? 2 : 1, rows = tile2d_rows() / 8;
     for (int vx : {1, 2, 4}) {
-        if ((p->dtype == kBF16) != (vx == 4)) continue;
+        if ((p->dtype == kBF16) != (vx == 4) || vx < p->radius) continue;
         const double us = 2 * kUsPerInstr * (rows * vx * (p->npoints + (p->dtype == kBF16 ? 2 : 0)) +
-                                             2 * dw * (p->cls == kStar ? rows : rows + 2));
-        for (int t = 2; 2 * t < tile2d_rows(); ++t) {
+                                             2 * p->radius * dw * (p->cls == kStar ? rows : rows + 2 * p->radius));
+        for (int t = 2; 2 * p->radius * t < tile2d_rows(); ++t) {
             Tile2DArgs a;
             if (!geo_tile(p, vx, t, a)) break;
             const double groups = static_cast<double>(ceil_div(static_cast<int64_t>(a.tiles_x) * a.tiles_y, device_cus()));
-            const double pass = 2.3 + t * ((p->dtype == kF64 ? 0.21 : 0.16) + us) + (groups - 1) * (0.6 + t * us);
+            const double pass = 2.3 + t * ((p->dtype == kF64 ? 0.21 : 0.16) + us) + (groups - 1) * (0.6 + t * us * (p->radius == 2 ? 1.45 : 1.0));
             if (pass / t < best) {
                 best = pass / t;
                 p->tile.tb = t;
@@ -783,7 +786,9 @@ void model_select(st_plan_s* p, bool fixed) {
         best = step_us(p, p->cands.back());
         p->stand_in = kOneStep;
     }
-    if (const double us = p->ndim == 2 ? tile_select(p) : brick_select(p); us < 0.9 * best) p->stand_in = kTiles;
+    // (radius 2 by a wider margin: its model is less exact where both are near)
+    const double margin = p->ndim == 2 && p->radius == 2 ? 0.8 : 0.9;
+    if (const double us = p->ndim == 2 ? tile_select(p) : brick_select(p); us < margin * best) p->stand_in = kTiles;
 }
 
 // Default fused depth and lane width per family.
@@ -1139,7 +1144,7 @@ st_status launch_pass(const st_plan_s* p, const Candidate& c, const void* src, v
         a.src = src;
         a.dst = dst;
         for (int i = 0; i < p->npoints; ++i) a.w[i] = wcan[i];
-        e = launch_tile2d(p->dtype, c.k2.vx, p->cls != kStar, p->bc != kZero, a, s);
+        e = launch_tile2d(p->dtype, p->radius, c.k2.vx, p->cls != kStar, p->bc != kZero, a, s);
         if (e != hipSuccess) return hip_fail(e, "register tile launch");
         return ST_OK;
     }

@@ -1,4 +1,4 @@
-// tile2d.hip -- small 2D grids, radius 1: a work-group holds a tile in
+// tile2d.hip -- small 2D grids, radius R = 1 or 2: a work-group holds a tile in
 // registers and advances it many steps before it returns to memory.
 //
 // The row pipelines (stream2d_impl.h) carry a pass through a chain of rows, one
@@ -8,7 +8,7 @@
 // cells; every step all waves update their rows at once: x neighbours from the
 // lane's own registers or lane +-1 through DPP, y neighbours from the wave's own
 // rows and, for its first and last row, through LDS (one barrier a step, two
-// buffers alternating).  After t steps the tile is exact but for t cells a side.
+// buffers alternating).  After t steps the tile is exact but for R*t cells a side.
 //
 // Zero rule: a tile that would cross the grid's edge is moved inward to touch
 // it; there the zeros that enter through DPP and the LDS rows outside the tile
@@ -20,7 +20,9 @@
 // What bounds it: the chain of steps -- one LDS round trip, a barrier and the
 // wave's own arithmetic each, 0.45 us for FP64 5 points at one column a
 // lane, of which 0.24 is arithmetic; a pass adds 2.3 us.  512^2 FP64, 100 steps:
-// 125 us with the row pipeline, 61 us here.
+// 125 us with the row pipeline, 60 us here.  Radius 2, us a step, rows and tiles:
+// FP64 9 points 512^2 2.40 and 1.27, 25 points 3.52 and 2.20, FP32 25 points
+// 1024^2 5.15 and 2.24.
 #include "dev_common.h"
 #include "internal.h"
 
@@ -29,15 +31,16 @@ namespace t2d {
 
 constexpr int kNW = 8, kK = 8;  // waves, rows a wave
 
-template <typename TS, bool BOX, int VX, bool PER>
+template <typename TS, int R, bool BOX, int VX, bool PER>
 struct Tile {
     using S = Storage<TS>;
     using TC = typename S::TC;
     static constexpr int NW = kNW, K = kK, W = 64 * VX, H = NW * K;
-    // LDS rows of a buffer: slot 0 above the tile, 2w+1 and 2w+2 the first and
-    // last row of wave w, 2*NW+1 below the tile
-    static constexpr int SLOTS = 2 * NW + 2, BUF = SLOTS * W;
-    static constexpr int kPoints = BOX ? 9 : 5;
+    static_assert(VX >= R && K >= 2 * R, "neighbours in the next lane and the next wave");
+    // LDS rows of a buffer: R above the tile, the first and the last R of each
+    // wave, R below the tile
+    static constexpr int SLOTS = 2 * R * (NW + 1), BUF = SLOTS * W;
+    static constexpr int kPoints = BOX ? (2 * R + 1) * (2 * R + 1) : 4 * R + 1;
     static constexpr uint32_t kOut = 0x80000000u;
     static constexpr int32_t kRsrcWord3 = 0x00020000;
 
@@ -80,65 +83,72 @@ struct Tile {
 
     // a row with its x neighbours
     struct Row {
-        TC v[VX], l, r;
+        TC v[VX], l[R], r[R];
     };
     static __device__ __forceinline__ Row row(const TC (&v)[VX]) {
         Row q;
 #pragma unroll
         for (int e = 0; e < VX; ++e) q.v[e] = v[e];
-        q.l = from_lower_z(v[VX - 1]);
-        q.r = from_upper_z(v[0]);
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            q.l[j] = from_lower_z(v[VX - R + j]);
+            q.r[j] = from_upper_z(v[j]);
+        }
         return q;
     }
     static __device__ __forceinline__ TC at(const Row& q, int x) {
-        return x < 0 ? q.l : (x >= VX ? q.r : q.v[x < 0 ? 0 : (x >= VX ? 0 : x)]);
+        return x < 0 ? q.l[x < 0 ? R + x : 0] : (x >= VX ? q.r[x >= VX ? x - VX : 0] : q.v[x < 0 ? 0 : (x >= VX ? 0 : x)]);
     }
-    static __device__ __forceinline__ TC next(const TC (&w)[kPoints], const Row& a, const Row& m, const Row& b, int e) {
-        TC acc = w[0] * m.v[e];
-        if constexpr (BOX) {
-            int p = 1;
+    // row k of the wave's rows with the R above (a) and below (b)
+    static __device__ __forceinline__ const Row& pick(const Row (&q)[K], const Row (&a)[R], const Row (&b)[R], int k) {
+        return k < 0 ? a[k < 0 ? R + k : 0] : (k >= K ? b[k >= K ? k - K : 0] : q[k < 0 ? 0 : (k >= K ? 0 : k)]);
+    }
+    static __device__ __forceinline__ TC next(const TC (&w)[kPoints], const Row (&q)[K], const Row (&a)[R],
+                                              const Row (&b)[R], int k, int e) {
+        TC acc = w[0] * q[k].v[e];
+        int p = 1;
 #pragma unroll
-            for (int dx = -1; dx <= 1; ++dx) acc = fma_c(w[p++], at(a, e + dx), acc);
-            acc = fma_c(w[p++], at(m, e - 1), acc);
-            acc = fma_c(w[p++], at(m, e + 1), acc);
+        for (int dy = -R; dy <= R; ++dy) {
+            const Row& m = pick(q, a, b, k + dy);
 #pragma unroll
-            for (int dx = -1; dx <= 1; ++dx) acc = fma_c(w[p++], at(b, e + dx), acc);
-        } else {
-            acc = fma_c(w[1], a.v[e], acc);
-            acc = fma_c(w[2], at(m, e - 1), acc);
-            acc = fma_c(w[3], at(m, e + 1), acc);
-            acc = fma_c(w[4], b.v[e], acc);
+            for (int dx = -R; dx <= R; ++dx)
+                if ((dy != 0 || dx != 0) && (BOX || dy == 0 || dx == 0)) acc = fma_c(w[p++], at(m, e + dx), acc);
         }
         return S::round(acc);
     }
 
     static __device__ __forceinline__ void step(const TC (&w)[kPoints], TC (&u)[K][VX], TC* buf, int own) {
 #pragma unroll
-        for (int e = 0; e < VX; ++e) {
-            buf[own + W + e] = u[0][e];
-            buf[own + 2 * W + e] = u[K - 1][e];
-        }
-        __syncthreads();
-        TC va[VX], vb[VX];
+        for (int j = 0; j < R; ++j)
 #pragma unroll
-        for (int e = 0; e < VX; ++e) {
-            va[e] = buf[own + e];
-            vb[e] = buf[own + 3 * W + e];
-        }
+            for (int e = 0; e < VX; ++e) {
+                buf[own + (R + j) * W + e] = u[j][e];
+                buf[own + (2 * R + j) * W + e] = u[K - R + j][e];
+            }
+        __syncthreads();
+        TC va[R][VX], vb[R][VX];
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+#pragma unroll
+            for (int e = 0; e < VX; ++e) {
+                va[j][e] = buf[own + j * W + e];
+                vb[j][e] = buf[own + (3 * R + j) * W + e];
+            }
         TC n[K][VX];
-        // the rows between first, then those that wait for LDS
-        Row q[K];
+        Row q[K], a[R], b[R];
 #pragma unroll
         for (int k = 0; k < K; ++k) q[k] = row(u[k]);
 #pragma unroll
-        for (int k = 1; k < K - 1; ++k)
+        for (int j = 0; j < R; ++j) {
+            a[j] = row(va[j]);
+            b[j] = row(vb[j]);
+        }
+        // the rows between first, then those that wait for LDS
 #pragma unroll
-            for (int e = 0; e < VX; ++e) n[k][e] = next(w, q[k - 1], q[k], q[k + 1], e);
-        const Row qa = row(va), qb = row(vb);
+        for (int i = 0; i < K; ++i) {
+            const int k = i < K - 2 * R ? i + R : (i < K - R ? i - (K - 2 * R) : i);
 #pragma unroll
-        for (int e = 0; e < VX; ++e) {
-            n[0][e] = next(w, qa, q[0], q[1], e);
-            n[K - 1][e] = next(w, q[K - 2], q[K - 1], qb, e);
+            for (int e = 0; e < VX; ++e) n[k][e] = next(w, q, a, b, k, e);
         }
 #pragma unroll
         for (int k = 0; k < K; ++k)
@@ -172,15 +182,15 @@ struct Tile {
             ld(rs, off[k], u[k]);
         }
         // the rows outside the tile hold 0
-        for (int i = threadIdx.x; i < 2 * W; i += 64 * NW) {
-            TC* b = lds + (i / W) * BUF + i % W;
+        for (int i = threadIdx.x; i < 2 * R * W; i += 64 * NW) {
+            TC* b = lds + (i / (R * W)) * BUF + i % (R * W);
             b[0] = TC(0);
-            b[(SLOTS - 1) * W] = TC(0);
+            b[(SLOTS - R) * W] = TC(0);
         }
         TC w[kPoints];
 #pragma unroll
         for (int p = 0; p < kPoints; ++p) w[p] = static_cast<TC>(a.w[p]);
-        const int own = 2 * wave * W + lane * VX;
+        const int own = 2 * R * wave * W + lane * VX;
         int32_t t = a.t;
         for (; t >= 2; t -= 2) {
             step(w, u, lds, own);
@@ -194,20 +204,21 @@ struct Tile {
     }
 };
 
-template <typename TS, bool BOX, int VX, bool PER>
-__global__ __launch_bounds__(64 * kNW) void tile2d_kernel(const Tile2DArgs a) {
-    using P = Tile<TS, BOX, VX, PER>;
+// 128 registers a lane: two work-groups a CU
+template <typename TS, int R, bool BOX, int VX, bool PER>
+__global__ __launch_bounds__(64 * kNW, 4) void tile2d_kernel(const Tile2DArgs a) {
+    using P = Tile<TS, R, BOX, VX, PER>;
     __shared__ __align__(16) typename P::TC lds[2 * P::BUF];
     P::run(a, lds);
 }
 
-template <typename TS, int VX>
+template <typename TS, int R, int VX>
 hipError_t go(bool box, bool per, const Tile2DArgs& a, hipStream_t s) {
     const dim3 grid(static_cast<unsigned>(a.tiles_x) * static_cast<unsigned>(a.tiles_y)), block(64 * kNW);
-    if (box && per) hipLaunchKernelGGL((tile2d_kernel<TS, true, VX, true>), grid, block, 0, s, a);
-    else if (box) hipLaunchKernelGGL((tile2d_kernel<TS, true, VX, false>), grid, block, 0, s, a);
-    else if (per) hipLaunchKernelGGL((tile2d_kernel<TS, false, VX, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((tile2d_kernel<TS, false, VX, false>), grid, block, 0, s, a);
+    if (box && per) hipLaunchKernelGGL((tile2d_kernel<TS, R, true, VX, true>), grid, block, 0, s, a);
+    else if (box) hipLaunchKernelGGL((tile2d_kernel<TS, R, true, VX, false>), grid, block, 0, s, a);
+    else if (per) hipLaunchKernelGGL((tile2d_kernel<TS, R, false, VX, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((tile2d_kernel<TS, R, false, VX, false>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 
@@ -215,12 +226,18 @@ hipError_t go(bool box, bool per, const Tile2DArgs& a, hipStream_t s) {
 
 int tile2d_rows() { return t2d::kNW * t2d::kK; }
 
-hipError_t launch_tile2d(int dtype, int vx, bool box, bool periodic, const Tile2DArgs& a, hipStream_t s) {
-    if (dtype == kF64 && vx == 1) return t2d::go<double, 1>(box, periodic, a, s);
-    if (dtype == kF64 && vx == 2) return t2d::go<double, 2>(box, periodic, a, s);
-    if (dtype == kF32 && vx == 1) return t2d::go<float, 1>(box, periodic, a, s);
-    if (dtype == kF32 && vx == 2) return t2d::go<float, 2>(box, periodic, a, s);
-    if (dtype == kBF16 && vx == 4) return t2d::go<bf16s, 4>(box, periodic, a, s);
+hipError_t launch_tile2d(int dtype, int radius, int vx, bool box, bool periodic, const Tile2DArgs& a, hipStream_t s) {
+    if (radius == 1) {
+        if (dtype == kF64 && vx == 1) return t2d::go<double, 1, 1>(box, periodic, a, s);
+        if (dtype == kF64 && vx == 2) return t2d::go<double, 1, 2>(box, periodic, a, s);
+        if (dtype == kF32 && vx == 1) return t2d::go<float, 1, 1>(box, periodic, a, s);
+        if (dtype == kF32 && vx == 2) return t2d::go<float, 1, 2>(box, periodic, a, s);
+        if (dtype == kBF16 && vx == 4) return t2d::go<bf16s, 1, 4>(box, periodic, a, s);
+    } else if (radius == 2) {
+        if (dtype == kF64 && vx == 2) return t2d::go<double, 2, 2>(box, periodic, a, s);
+        if (dtype == kF32 && vx == 2) return t2d::go<float, 2, 2>(box, periodic, a, s);
+        if (dtype == kBF16 && vx == 4) return t2d::go<bf16s, 2, 4>(box, periodic, a, s);
+    }
     return hipErrorInvalidValue;
 }
 

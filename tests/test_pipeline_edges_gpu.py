@@ -275,3 +275,19 @@ def test_varcoef_infinite_value_inside(dtype):
     got, want = (_varcoef(u0, k, y, dtype, 2, 2, naive) for naive in (False, True))
     for i, (a, b) in enumerate(zip(got, want)):
         assert np.array_equal(a, b, equal_nan=True), f"buffer {i}"
+
+
+# the same tiles at radius 2 (two edge rows a wave, two columns from the next lane)
+@pytest.mark.parametrize("dtype", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("bc", ["zero", "periodic"])
+@pytest.mark.parametrize("pattern", ["star", "box"])
+@pytest.mark.parametrize("shape", [(64, 128), (65, 257), (66, 256), (130, 260), (256, 515)])
+def test_2d_small_grids_in_register_tiles_radius_2(dtype, bc, pattern, shape):
+    import paper_2303_08365_amd as st
+    offs = (synth.star_offsets if pattern == "star" else synth.box_offsets)(2, 2)
+    w = _weights(offs, 71, dtype)
+    u0 = synth.uniform_field(shape, seed=72)
+    plan, naive = st.Plan(offs, shape, dtype, bc), st.Plan(offs, shape, dtype, bc, naive=True)
+    for steps in (1, 2, 5, 15, 16, 31):
+        one = _against_naive(plan, naive, u0, offs, w, steps, bc, dtype, None, f"tiles r2 {dtype} {bc} {pattern} {shape}")
+    check(one, oracle_ref(u0, offs, w, steps, bc, dtype), dtype, steps, "one-step kernel")
