@@ -207,6 +207,17 @@ __device__ __forceinline__ double from_upper(double v, double old) {
                                 static_cast<uint32_t>(lo));
 }
 
+// LDS handed from lane to lane of one wave: writes before it are seen by every
+// lane's reads after it, and reads before it are done before writes after it.
+// The LDS serves a wave's accesses in order, so this costs no instruction; it
+// keeps the compiler to that order, which it may otherwise change where it can
+// prove the indices of one lane apart.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---------------------------------------------------------------------------
 // XCD-aware work-group order
 // ---------------------------------------------------------------------------

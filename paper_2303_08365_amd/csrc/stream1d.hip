@@ -66,7 +66,7 @@ struct Kern {
     // A strip between memory and the lanes' registers.  In memory order lane L
     // moves the 16-byte pieces L, 64 + L, ..., whole lines per instruction; a
     // lane's cells are CH consecutive pieces.  The two orders meet in LDS,
-    // each wave in its own 64*VX cells; piece j of lane L lies at slot
+    // each wave in its own 64*VX cells (no barrier, wave_lds_order only); piece j of lane L lies at slot
     // j ^ swz(L) of the lane's CH, so that the 16 lanes an LDS cycle serves read
     // 16 different 16-byte columns.
     static constexpr int CH = VX * static_cast<int>(sizeof(TS)) / 16;  // pieces per lane
@@ -86,6 +86,7 @@ struct Kern {
                 u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, b0 + 16u * static_cast<uint32_t>(i * 64 + lane), 0, 0));
 #pragma unroll
         for (int i = 0; i < CH; ++i) lds[slot(i * 64 + lane)] = raw[i];
+        wave_lds_order();
 #pragma unroll
         for (int j = 0; j < CH; ++j) raw[j] = lds[slot(lane * CH + j)];
         TS vals[VX];
@@ -101,8 +102,10 @@ struct Kern {
         for (int e = 0; e < VX; ++e) vals[e] = S::narrow(v[e]);
         u32x4 raw[CH];
         __builtin_memcpy(raw, vals, sizeof(raw));
+        wave_lds_order();  // load_strip's reads are done
 #pragma unroll
         for (int j = 0; j < CH; ++j) lds[slot(lane * CH + j)] = raw[j];
+        wave_lds_order();
 #pragma unroll
         for (int i = 0; i < CH; ++i) raw[i] = lds[slot(i * 64 + lane)];
 #pragma unroll

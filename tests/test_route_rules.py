@@ -1,0 +1,25 @@
+"""Host checks of what the run calls route where, and of rules that the kernels'
+sources have to keep."""
+import os
+import re
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2303_08365_amd", "csrc")
+
+
+# the 1D strips hand their pieces from lane to lane through LDS without a barrier:
+# the source orders every change between writing and reading
+def test_1d_strips_order_their_lds_accesses():
+    src = re.sub(r"//[^\n]*", "", open(os.path.join(CSRC, "stream1d.hip")).read())
+    kinds = re.findall(r"(\blds\[[^;]*?\]\s*=[^=])|(=\s*lds\[)|(wave_lds_order\(\);)|(static __device__[^;{]*?u32x4\* lds)", src)
+    ops = ["write" if w else "read" if r else "order" if o else "function" for w, r, o, _ in kinds]
+    assert ops.count("write") == 2 and ops.count("read") == 2
+    last = None  # the first access of a function follows those of whatever ran before
+    for op in ops:
+        if op == "function" and last != "start":
+            last = "start" if last is None else "before"
+        elif op in ("write", "read"):
+            assert last in ("start", "order", op), f"{op} after {last} with nothing that orders them"
+            last = op
+        elif op == "order":
+            last = "order"
