@@ -44,9 +44,12 @@
 // the zero rule a tile that would cross the grid edge is moved inward to
 // touch it, where those zeros are the ghost layer, so edge tiles are exact up
 // to the edge.  A plane outside the grid is a ghost plane: level 0 loads it
-// as 0 (empty descriptor range); a deeper level's value there is never used,
-// because the z weights that would read it are set to 0 for that iteration
-// (scalar selects, nothing per element; exact for finite states).
+// as 0 (empty descriptor range), and a deeper level's values there are masked
+// to 0, two at a time in bfloat16, where the mask rides on the rounding.
+// (Zeroing the weights that would read them instead is exact for finite states
+// only, 0 * inf being NaN, and no faster.  512^3, us a pass, weights and
+// values: FP64 470 and 469, FP32 298 and 292, bfloat16 215 and 212; FP64 with
+// the outflow 1.03 times faster, two planes a trip included.)
 //
 // Memory access: one buffer descriptor per plane (range = the plane, empty
 // for a ghost plane) and, per row, one 32-bit vector offset fixed for the
@@ -116,10 +119,9 @@ struct Pipe {
     // instead of 232.  512^3, us a pass, one plane a trip and two: FP64 520 and
     // 504, FP32 (8 rows) 320 and 304, outflow FP32 397 and 385, bfloat16 328 and
     // 317.  One where two spill: bfloat16 6 x 4 (217 and 375) and four steps of
-    // it, and where it gains nothing: the FP64 outflow twin.  A second plane
-    // prefetched fits FP64 then (228 VGPRs) and gains nothing (511).
-    static constexpr int kTrip =
-        LQ || (FLX && sizeof(TC) == 8) || (sizeof(TS) == 2 && TBMAX * K * VX > 48) ? 1 : 2;
+    // it.  A second plane prefetched fits FP64 then (228 VGPRs) and gains nothing
+    // (511).
+    static constexpr int kTrip = LQ || (sizeof(TS) == 2 && TBMAX * K * VX > 48) ? 1 : 2;
     static constexpr int LDS_BYTES = DYN_BYTES + (LQ ? Q_BYTES : 0);
     static constexpr uint32_t kOut = 0x80000000u;  // past the end of any plane (planes < 2 GiB)
     static constexpr int32_t kRsrcWord3 = 0x00020000;  // gfx9: raw 32-bit data
@@ -152,9 +154,6 @@ struct Pipe {
         int32_t k0, k1;        // the wave's rows that the tile owns: k0 <= k < k1
     };
 
-    static __device__ __forceinline__ bool zghost(int32_t z, int32_t nz) {
-        return !PER && static_cast<uint32_t>(z) >= static_cast<uint32_t>(nz);
-    }
     // All ones where 0 <= i < n, else 0.  Two planes per trip: planes outside are
     // masked, not branched around (a branch splits the loop's body, and the
     // compiler moves partial sums behind it, where their operands live longer).
@@ -162,15 +161,26 @@ struct Pipe {
         if constexpr (kTrip == 2) return ~((i | (n - 1 - i)) >> 31);
         else return static_cast<uint32_t>(i) < static_cast<uint32_t>(n) ? -1 : 0;
     }
-    // w, or 0 for a ghost plane
-    static __device__ __forceinline__ TC unless_ghost(TC w, int32_t z, int32_t nz) {
-        if constexpr (PER) return w;
-        if constexpr (kTrip == 1) return zghost(z, nz) ? TC(0) : w;
-        const int32_t keep = inside(z, nz);
-        if constexpr (sizeof(TC) == 8)
-            return __longlong_as_double(__double_as_longlong(w) & static_cast<int64_t>(keep));
-        else
-            return __int_as_float(__float_as_int(w) & keep);
+    // A level's new values of a row, rounded to the storage type; 0 on a ghost
+    // plane (keep = 0, else all ones).  bfloat16 rounds and masks two at a time.
+    static __device__ __forceinline__ void round_masked(TC (&v)[VX], int32_t keep) {
+        if constexpr (sizeof(TS) == 2 && VX % 2 == 0) {
+#pragma unroll
+            for (int e = 0; e < VX; e += 2) {
+                const uint32_t p = f32x2_to_bf16x2(v[e], v[e + 1]) & static_cast<uint32_t>(keep);
+                v[e] = __uint_as_float(p << 16);
+                v[e + 1] = __uint_as_float(p & 0xffff0000u);
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < VX; ++e) {
+                const TC x = S::round(v[e]);
+                if constexpr (PER) v[e] = x;
+                else if constexpr (sizeof(TC) == 8)
+                    v[e] = __longlong_as_double(__double_as_longlong(x) & static_cast<int64_t>(keep));
+                else v[e] = __int_as_float(__float_as_int(x) & keep);
+            }
+        }
     }
     static __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane(const Ctx& c, const TS* p, int32_t z, int32_t keep) {
         if constexpr (kTrip == 1) {
@@ -429,9 +439,8 @@ struct Pipe {
         // gain for FP32, a loss for bfloat16).
         if constexpr (sizeof(TC) == 8) __builtin_amdgcn_s_setprio(1);
         // phase A, level by level: u_{l+1}(zin-l-1) = fma(w6, u_l(zin-l),
-        // P_l(zin-l-1)) (a ghost plane zin-l, where levels >= 1 hold junk,
-        // enters with weight 0); the last level's plane is stored.  Early
-        // form: then the next partial sum of level l takes its first two
+        // P_l(zin-l-1)) (0 on a ghost plane); the last level's plane is stored.
+        // Early form: then the next partial sum of level l takes its first two
         // terms, which need no neighbour, w0 u_l(zin-l) and w1 u_l(zin-l-1),
         // and u_l(zin-l) replaces u_l(zin-l-1), so across the LDS exchange a
         // level keeps two planes.  Late form: every level's new plane is kept
@@ -440,30 +449,31 @@ struct Pipe {
         TC nw[kEarly ? 1 : TB][K][VX];
 #pragma unroll
         for (int l = 0; l < TB; ++l) {
-            const TC w6 = l > 0 ? unless_ghost(c.w[6], zin - l, c.nz) : c.w[6];
             TC nxt[K][VX];
             if (l + 1 < TB) {
 #pragma unroll
                 for (int k = 0; k < K; ++k)
 #pragma unroll
-                    for (int e = 0; e < VX; ++e) nxt[k][e] = S::round(fma_c(w6, cur[k][e], s.pend[l][k][e]));
+                    for (int e = 0; e < VX; ++e) nxt[k][e] = fma_c(c.w[6], cur[k][e], s.pend[l][k][e]);
+                const int32_t z = zin - l - 1, keep = PER ? -1 : ~((z | (c.nz - 1 - z)) >> 31);
+#pragma unroll
+                for (int k = 0; k < K; ++k) round_masked(nxt[k], keep);
             } else {
                 const __amdgpu_buffer_rsrc_t r = plane_out(c, zin - TB);
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
                     TC o[VX];
 #pragma unroll
-                    for (int e = 0; e < VX; ++e) o[e] = fma_c(w6, cur[k][e], s.pend[l][k][e]);
+                    for (int e = 0; e < VX; ++e) o[e] = fma_c(c.w[6], cur[k][e], s.pend[l][k][e]);
                     strow(r, c.so[k], o);
                 }
             }
             if constexpr (kEarly) {
-                const TC w1 = l > 0 ? unless_ghost(c.w[1], zin - l - 1, c.nz) : c.w[1];
 #pragma unroll
                 for (int k = 0; k < K; ++k)
 #pragma unroll
                     for (int e = 0; e < VX; ++e) {
-                        s.pend[l][k][e] = fma_c(w1, s.prev[l][k][e], c.w[0] * cur[k][e]);
+                        s.pend[l][k][e] = fma_c(c.w[1], s.prev[l][k][e], c.w[0] * cur[k][e]);
                         s.prev[l][k][e] = cur[k][e];
                     }
             } else {
@@ -516,14 +526,13 @@ struct Pipe {
 #pragma unroll
         for (int l = 0; l < TB; ++l) {
             const TC (&u)[K][VX] = kEarly ? s.prev[l] : nw[kEarly ? 0 : l];
-            const TC w1 = l > 0 ? unless_ghost(c.w[1], zin - l - 1, c.nz) : c.w[1];
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 const TC lft = from_lower_z(u[k][VX - 1]);
                 const TC rgt = from_upper_z(u[k][0]);
 #pragma unroll
                 for (int e = 0; e < VX; ++e) {
-                    TC acc = kEarly ? s.pend[l][k][e] : fma_c(w1, s.prev[l][k][e], c.w[0] * u[k][e]);
+                    TC acc = kEarly ? s.pend[l][k][e] : fma_c(c.w[1], s.prev[l][k][e], c.w[0] * u[k][e]);
                     acc = fma_c(c.w[2], k > 0 ? u[k > 0 ? k - 1 : 0][e] : above[l][e], acc);
                     acc = fma_c(c.w[3], e > 0 ? u[k][e > 0 ? e - 1 : 0] : lft, acc);
                     acc = fma_c(c.w[4], e + 1 < VX ? u[k][e + 1 < VX ? e + 1 : 0] : rgt, acc);
