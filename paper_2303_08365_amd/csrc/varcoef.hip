@@ -14,7 +14,10 @@
 //                         - (number of ghost faces of j) * u[j] * lambda[j] ).
 // (An inner face couples j and j+f: the term 0.5*(u_f-u_j) arises once from
 // the update of j and once, with the opposite sign of the lambda difference,
-// from the update of j+f; a ghost face contributes d kap/d k[j] = 1.)
+// from the update of j+f; a ghost face contributes d kap/d k[j] = 1.  The
+// kernels take a ghost face's -u[j] * lambda[j] in two halves: one among the
+// faces, where u and lambda of 0 on the ghost layer make it an inner face's
+// term, the other, times the number of ghost faces, at the end.)
 // Both kernels are one thread per cell; a work-group covers 256 consecutive
 // cells of one row (its row and plane come from the work-group index with
 // 32-bit scalar arithmetic, so no lane divides), neighbours come through
@@ -96,7 +99,7 @@ __global__ __launch_bounds__(256) void varcoef_adjoint_kernel(const VarcoefArgs 
     // faces z-, y-, y+, x-, x+, z+
     const int64_t dz[6] = {-1, 0, 0, 0, 0, 1}, dy[6] = {0, -1, 1, 0, 0, 0}, dx[6] = {0, 0, 0, -1, 1, 0};
     TC acc = TC(0), gacc = TC(0);
-    int ng = 0;  // ghost faces: their dL/dk terms come last, as in the other kernels
+    int ng = 0;  // ghost faces: half of their dL/dk terms comes last
 #pragma unroll
     for (int f = 0; f < 6; ++f) {
         const int64_t zz = z + dz[f], yy = y + dy[f], xx = x + dx[f];
@@ -108,10 +111,11 @@ __global__ __launch_bounds__(256) void varcoef_adjoint_kernel(const VarcoefArgs 
             gacc = fma_c(TC(0.5) * (ld1(u + j) - uc), lc - lf, gacc);
         } else {
             acc = fma_c(kc, -lc, acc);
+            gacc = fma_c(TC(-0.5) * uc, lc, gacc);
             ng += 1;
         }
     }
-    if (ng > 0) gacc = fma_c(-static_cast<TC>(ng) * uc, lc, gacc);
+    if (ng > 0) gacc = fma_c(TC(-0.5) * static_cast<TC>(ng) * uc, lc, gacc);
     st1(out + i, fma_c(alpha, acc, lc));
     if (a.grad != nullptr) st1(g + i, fma_c(alpha, gacc, ld1(g + i)));
 }

@@ -19,10 +19,10 @@
 //
 // Ghost layer: u and lambda are 0 there (loads outside the range, the zero that
 // enters the wave through DPP, zero LDS rows; planes of step 1 outside the grid
-// are set to 0).  k, and u in the adjoint, repeat the edge cell: clamped rows
-// and planes, and DPP's old operand in x; then (k + k) / 2 = k and (u - u) / 2
-// = 0 make the interior formulas the edge terms, and the adjoint adds -u *
-// lambda once per ghost face.
+// are set to 0).  k repeats the edge cell: clamped rows and planes, and DPP's old
+// operand in x; then (k + k) / 2 = k makes the interior formula the edge term.
+// In dL/dk the interior formula gives half of a ghost face's -u * lambda, and
+// the adjoint adds the other half once per ghost face.
 //
 // The y neighbours of all fields go through LDS, one barrier per plane, two
 // buffers alternating; rows outside the tile are loaded for step 1 and missing
@@ -77,9 +77,9 @@ struct Pipe {
         uint32_t plane_bytes;
         uint32_t lo[K];     // the lane's columns in the wave's rows
         uint32_t so[K];     // same for the stores; kOut outside the owned cells
-        uint32_t hz, hc;    // the wave's halo row: kOut where outside (zero fields), clamped (k, u)
+        uint32_t hz, hc;    // the wave's halo row: kOut where outside (zero fields), clamped (k)
         int hslot;          // its LDS slot
-        uint32_t ra, rb;    // adjoint: the rows above and below the wave's, clamped
+        uint32_t ra, rb;    // adjoint: the rows above and below the wave's; kOut where outside
         int lane, wave;
         T alpha;
         int ngy[K], ngx[VX];  // adjoint: ghost faces in y and x
@@ -153,13 +153,13 @@ struct Pipe {
         ld(rv, c.hz, in.hv);
         ld(rk, c.hc, in.hk);
         if constexpr (ADJ) {
-            const __amdgpu_buffer_rsrc_t ru = plane_clamp(c, c.u, z), r1 = plane_clamp(c, c.u1, z - 1);
+            const __amdgpu_buffer_rsrc_t ru = plane_zero(c, c.u, z), r1 = plane_zero(c, c.u1, z - 1);
 #pragma unroll
             for (int i = 0; i < K; ++i) {
                 ld(ru, c.lo[i], in.u[i]);
                 ld(r1, c.lo[i], in.u1[i]);
             }
-            ld(ru, c.hc, in.hu);
+            ld(ru, c.hz, in.hu);
         }
     }
 
@@ -188,8 +188,7 @@ struct Pipe {
                     const T du = T(0.5) * (u[i][e] - s.uprev[i][e]);
                     const T g = fma_c(du, -d, s.gacc[i][e]);
                     const int ng = ngz + c.ngy[i] + c.ngx[e];
-                    // (a cell without ghost faces keeps its sum, also where u is infinite)
-                    gout[i][e] = fma_c(-static_cast<T>(ng) * (ng > 0 ? s.uprev[i][e] : T(0)), s.prev[i][e], g);
+                    gout[i][e] = ng > 0 ? fma_c(T(-0.5) * static_cast<T>(ng) * s.uprev[i][e], s.prev[i][e], g) : g;
                     s.gacc[i][e] = fma_c(-du, d, T(0));
                 }
             }
@@ -250,7 +249,7 @@ struct Pipe {
             T vl, vr, kl, kr, ul = T(0), ur = T(0);
             sides<false>(s.prev[i], vl, vr);
             sides<true>(k[i], kl, kr);
-            if constexpr (ADJ) sides<true>(s.uprev[ADJ ? i : 0], ul, ur);
+            if constexpr (ADJ) sides<false>(s.uprev[ADJ ? i : 0], ul, ur);
             // faces left of column e: x+ of column e - 1 after its x-
 #pragma unroll
             for (int e = 0; e <= VX; ++e) {
@@ -302,7 +301,7 @@ struct Pipe {
             if constexpr (ADJ) put(buf + FU * FIELD + hrow, s.in.hu);
         }
         if constexpr (ADJ && (PH == kBoth || PH == kLast)) {
-            const __amdgpu_buffer_rsrc_t r1 = plane_clamp(c, c.u1, z - 1), rg = plane_own(c, c.grad, z - 2);
+            const __amdgpu_buffer_rsrc_t r1 = plane_zero(c, c.u1, z - 1), rg = plane_own(c, c.grad, z - 2);
 #pragma unroll
             for (int i = 0; i < K; ++i) ld(rg, c.so[i], gold[i]);
             if constexpr (PH == kBoth) {
@@ -456,9 +455,8 @@ struct Pipe {
             c.hz = (top || bot) && in ? static_cast<uint32_t>(hy * nx + xl) * sizeof(T) : kOut;
             c.hc = top || bot ? static_cast<uint32_t>(hyc * nx + xl) * sizeof(T) : kOut;
             if constexpr (ADJ) {
-                const int32_t ya = yw > 0 ? yw - 1 : 0, yb = yw + K < ny ? yw + K : ny - 1;
-                c.ra = static_cast<uint32_t>(ya * nx + xl) * sizeof(T);
-                c.rb = static_cast<uint32_t>(yb * nx + xl) * sizeof(T);
+                c.ra = yw > 0 ? static_cast<uint32_t>((yw - 1) * nx + xl) * sizeof(T) : kOut;
+                c.rb = yw + K < ny ? static_cast<uint32_t>((yw + K) * nx + xl) * sizeof(T) : kOut;
             }
             c.hslot = top ? 0 : (bot ? 2 * NW + 1 : 2 * NW + 2);
         }

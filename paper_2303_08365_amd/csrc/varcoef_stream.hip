@@ -13,16 +13,16 @@
 // test.  The operator (the faces visited z-, y-, y+, x-, x+, z+):
 //   u'[i] = u[i] + alpha * sum_f kap_f * (u[f] - u[i]),
 //   kap_f = (k[i] + k[f]) / 2 inside; across the grid edge kap = k[i], u = 0.
-// Fields that are 0 on the ghost layer (u in the step, lambda in the
-// adjoint) are read through buffer descriptors whose range is the row (or
-// plane): a row, plane or column outside the grid reads 0.  k is read with
-// clamped indices: the ghost neighbour of an edge cell reads that cell's own
-// k, and (k + k) / 2 = k exactly, so the interior formula gives the edge term
-// bit for bit.  In the adjoint u is read clamped too, which makes the
-// interior dL/dk term (u[f] - u[i]) / 2 * (lambda[i] - lambda[f]) vanish
-// across the edge; the edge term -u[i] * lambda[i] is added once per ghost
-// face at the end (the count of a cell's ghost faces is fixed by its
-// position).
+// u and lambda are 0 on the ghost layer: they are read through buffer
+// descriptors whose range is the row (or plane), and a row, plane or column
+// outside the grid reads 0.  k is read with clamped indices: the ghost
+// neighbour of an edge cell reads that cell's own k, and (k + k) / 2 = k
+// exactly, so the interior formula gives the edge term bit for bit.  The
+// interior dL/dk term (u[f] - u[i]) / 2 * (lambda[i] - lambda[f]) gives half of
+// a ghost face's -u[i] * lambda[i]; the other half is added at the end, once per
+// ghost face (the count of a cell's ghost faces is fixed by its position).
+// Nothing is multiplied by a 0 that stands for "no such face", so an infinite
+// u or lambda gives what it gives in the one-cell form.
 #include <utility>
 
 #include "dev_common.h"
@@ -37,7 +37,7 @@ struct Kern {
     static constexpr int F = ADJ ? 3 : 2;  // fields: 0 u, 1 k, 2 lambda
     static constexpr int32_t kRsrcWord3 = 0x00020000;  // gfx9: raw 32-bit data
     static constexpr int32_t kNT = 2;                  // non-temporal stores
-    static constexpr bool clamped(int f) { return f == 1 || (ADJ && f == 0); }
+    static constexpr bool clamped(int f) { return f == 1; }
 
     struct Ctx {
         const T* fld[F];
@@ -62,27 +62,21 @@ struct Kern {
     }
     static __device__ __forceinline__ int32_t clampi(int32_t i, int32_t n) { return i < 0 ? 0 : (i >= n ? n - 1 : i); }
 
-    // one row of field f in plane z (row y): empty range outside the grid for
-    // the zero fields, clamped indices for the others
+    // all ones where 0 <= i < n, else 0 (masks: no branch between the loads)
+    static __device__ __forceinline__ int32_t inside(int32_t i, int32_t n) { return ~((i | (n - 1 - i)) >> 31); }
+
+    // one row of field f in plane z (row y), both clamped; an empty range outside
+    // the grid for the zero fields
     static __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const Ctx& c, int f, int32_t z, int32_t y) {
-        if (clamped(f)) {
-            const T* base = c.fld[f] + static_cast<int64_t>(clampi(z, c.nz)) * c.plane_elems + clampi(y, c.ny) * c.nx;
-            return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base), 0, c.row_bytes, kRsrcWord3);
-        }
-        const bool out = outside(z, c.nz) || outside(y, c.ny);
-        const T* base = out ? c.fld[f] : c.fld[f] + static_cast<int64_t>(z) * c.plane_elems + y * c.nx;
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base), 0, out ? 0 : c.row_bytes, kRsrcWord3);
+        const T* base = c.fld[f] + static_cast<int64_t>(clampi(z, c.nz)) * c.plane_elems + clampi(y, c.ny) * c.nx;
+        const int32_t keep = clamped(f) ? -1 : inside(z, c.nz) & inside(y, c.ny);
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base), 0, c.row_bytes & keep, kRsrcWord3);
     }
     static __device__ __forceinline__ T ring_x(const Ctx& c, int f, int32_t z) {
-        if (clamped(f)) {
-            const T* base = c.fld[f] + static_cast<int64_t>(clampi(z, c.nz)) * c.plane_elems;
-            const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base), 0, c.plane_bytes, kRsrcWord3);
-            return bload1(r, c.xr_clamp);
-        }
-        const bool out = outside(z, c.nz);
-        const T* base = out ? c.fld[f] : c.fld[f] + static_cast<int64_t>(z) * c.plane_elems;
-        const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base), 0, out ? 0 : c.plane_bytes, kRsrcWord3);
-        return bload1(r, c.xr_zero);
+        const T* base = c.fld[f] + static_cast<int64_t>(clampi(z, c.nz)) * c.plane_elems;
+        const int32_t keep = clamped(f) ? -1 : inside(z, c.nz);
+        const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base), 0, c.plane_bytes & keep, kRsrcWord3);
+        return bload1(r, clamped(f) ? c.xr_clamp : c.xr_zero);
     }
     static __device__ __forceinline__ T bload1(__amdgpu_buffer_rsrc_t r, uint32_t off) {
         if constexpr (sizeof(T) == 8) return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
@@ -202,7 +196,7 @@ struct Kern {
                         gacc = fma_c(T(0.5) * (nb[fc][0] - uc), lc - nb[fc][2], gacc);
                     }
                     const int ng = ngzy + c.ngx[e];
-                    gacc = fma_c(-static_cast<T>(ng) * uc, lc, gacc);
+                    gacc = ng > 0 ? fma_c(T(-0.5) * static_cast<T>(ng) * uc, lc, gacc) : gacc;
                     o[e] = fma_c(c.alpha, acc, lc);
                     g[e] = gacc;
                 }

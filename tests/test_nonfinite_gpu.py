@@ -49,3 +49,47 @@ def test_infinite_values_at_the_faces(dtype, bc, pattern, radius, shape):
         if ref8 is None:
             ref8 = gpu_sweep(u0, offs, w, 8, bc, dtype, plan=naive)[0]
         assert np.array_equal(own, ref8, equal_nan=True), f"the plan's own choice at {at}"
+
+
+def _varcoef(u0, k, y, alpha, dtype, steps, naive):
+    """Forward with a checkpoint at the start, and both gradients."""
+    import torch
+    import paper_2303_08365_amd as st
+    t = {"f64": torch.float64, "f32": torch.float32}[dtype]
+    plan = st.varcoef_plan(u0.shape, dtype, naive=naive)
+    g, kk, lam = (torch.from_numpy(a).to("cuda", t) for a in (u0, k, y))
+    gk, ck = torch.zeros_like(g), [torch.empty_like(g)]
+    plan.run_ckpt(g, kk, alpha, steps, torch.empty_like(g), every=steps, ckpts=ck)
+    seg = torch.empty((max(steps - 1, 1),) + u0.shape, dtype=t, device="cuda")
+    plan.adjoint(lam, steps, torch.empty_like(g), k=kk, alpha=alpha, ckpts=ck, every=steps, grad_k=gk, seg=seg)
+    return [a.cpu().numpy() for a in (g, lam, gk)]
+
+
+# variable coefficients: an infinite state or cotangent on a face, edge or corner
+# or inside, through single steps (1), pairs (2) and both (3).  The other field
+# has an extremum in that cell, and the negative diffusion number keeps the
+# infinity one, so that dL/dk there is an infinity that any stray 0 * inf or inf -
+# inf would turn into NaN.
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("what", ["u", "lambda"])
+@pytest.mark.parametrize("shape", [(9, 95, 512), (7, 64, 100), (60, 96, 252)])
+def test_varcoef_infinite_values_at_the_faces(dtype, what, shape):
+    rng = np.random.default_rng(83)
+    k = 0.5 + rng.random(shape)
+    mid = tuple(n // 2 for n in shape)
+    places = [tuple(0 for _ in shape), tuple(n - 1 for n in shape), mid]
+    for d in range(3):
+        places += [mid[:d] + (0,) + mid[d + 1:], mid[:d] + (shape[d] - 1,) + mid[d + 1:]]
+    for at in places:
+        u0, y = rng.random(shape), rng.random(shape)
+        if what == "u":
+            u0[at], y[at] = np.inf, 10.0
+        else:
+            u0[at], y[at] = -10.0, np.inf
+        for steps in (1, 2, 3):
+            print(f"varcoef infinity {dtype} {what} {shape} at {at} steps {steps}", flush=True)
+            got, want = (_varcoef(u0, k, y, -0.1, dtype, steps, naive) for naive in (False, True))
+            if what == "lambda" and steps == 1:
+                assert np.isinf(want[2][at]), "the case tells nothing"
+            for i, (a, b) in enumerate(zip(got, want)):
+                assert np.array_equal(a, b, equal_nan=True), f"buffer {i}: {np.argwhere(~((a == b) | (np.isnan(a) & np.isnan(b))))[:4]}"
