@@ -18,6 +18,8 @@
 // kernels take a ghost face's -u[j] * lambda[j] in two halves: one among the
 // faces, where u and lambda of 0 on the ghost layer make it an inner face's
 // term, the other, times the number of ghost faces, at the end.)
+// A face's conductivity is a sum of halves: k[i] + k[i+f] may overflow where
+// their mean does not.
 // Both kernels are one thread per cell; a work-group covers 256 consecutive
 // cells of one row (its row and plane come from the work-group index with
 // 32-bit scalar arithmetic, so no lane divides), neighbours come through
@@ -73,7 +75,7 @@ __global__ __launch_bounds__(256) void varcoef_step_kernel(const VarcoefArgs a) 
         const int64_t zz = z + dz[f], yy = y + dy[f], xx = x + dx[f];
         if (zz >= 0 && zz < nz && yy >= 0 && yy < ny && xx >= 0 && xx < nx) {
             const int64_t j = (zz * ny + yy) * nx + xx;
-            const TC kap = TC(0.5) * (kc + ld1(k + j));
+            const TC kap = fma_c(TC(0.5), kc, TC(0.5) * ld1(k + j));
             acc = fma_c(kap, ld1(u + j) - uc, acc);
         } else {
             acc = fma_c(kc, -uc, acc);
@@ -105,7 +107,7 @@ __global__ __launch_bounds__(256) void varcoef_adjoint_kernel(const VarcoefArgs 
         const int64_t zz = z + dz[f], yy = y + dy[f], xx = x + dx[f];
         if (zz >= 0 && zz < nz && yy >= 0 && yy < ny && xx >= 0 && xx < nx) {
             const int64_t j = (zz * ny + yy) * nx + xx;
-            const TC kap = TC(0.5) * (kc + ld1(k + j));
+            const TC kap = fma_c(TC(0.5), kc, TC(0.5) * ld1(k + j));
             const TC lf = ld1(lam + j);
             acc = fma_c(kap, lf - lc, acc);
             gacc = fma_c(TC(0.5) * (ld1(u + j) - uc), lc - lf, gacc);

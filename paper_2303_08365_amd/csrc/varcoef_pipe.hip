@@ -20,7 +20,7 @@
 // Ghost layer: u and lambda are 0 there (loads outside the range, the zero that
 // enters the wave through DPP, zero LDS rows; planes of step 1 outside the grid
 // are set to 0).  k repeats the edge cell: clamped rows and planes, and DPP's old
-// operand in x; then (k + k) / 2 = k makes the interior formula the edge term.
+// operand in x; then k / 2 + k / 2 = k makes the interior formula the edge term.
 // In dL/dk the interior formula gives half of a ghost face's -u * lambda, and
 // the adjoint adds the other half once per ghost face.
 //
@@ -137,6 +137,15 @@ struct Pipe {
             for (int e = 0; e < VX; ++e) d[i][e] = s[i][e];
     }
 
+    // (opaque: fused into a face's sum, k itself would have to stay beside it)
+    static __device__ __forceinline__ void halve(T (&d)[VX], const T (&s)[VX]) {
+#pragma unroll
+        for (int e = 0; e < VX; ++e) {
+            d[e] = T(0.5) * s[e];
+            asm("" : "+v"(d[e]));
+        }
+    }
+
     // The planes one iteration takes in: step 1's state and k (and u) of plane
     // z with the wave's halo row, u^{n-1} of plane z-1.
     struct In {
@@ -228,7 +237,7 @@ struct Pipe {
             for (int e = 0; e < VX; ++e) {
                 const T v0 = i > 0 ? s.prev[i > 0 ? i - 1 : 0][e] : va[e], v1 = i < K ? s.prev[i < K ? i : 0][e] : vb[e];
                 const T k0 = i > 0 ? k[i > 0 ? i - 1 : 0][e] : ka[e], k1 = i < K ? k[i < K ? i : 0][e] : kb[e];
-                const T kap = T(0.5) * (k0 + k1), d = v1 - v0;
+                const T kap = k0 + k1, d = v1 - v0;
                 T du = T(0);
                 if constexpr (ADJ)
                     du = T(0.5) * ((i < K ? s.uprev[ADJ && i < K ? i : 0][e] : ub[e]) -
@@ -253,7 +262,7 @@ struct Pipe {
             // faces left of column e: x+ of column e - 1 after its x-
 #pragma unroll
             for (int e = 0; e <= VX; ++e) {
-                const T kap = T(0.5) * (at(k[i], kl, kr, e - 1) + at(k[i], kl, kr, e));
+                const T kap = at(k[i], kl, kr, e - 1) + at(k[i], kl, kr, e);
                 const T d = at(s.prev[i], vl, vr, e) - at(s.prev[i], vl, vr, e - 1);
                 T du = T(0);
                 if constexpr (ADJ) du = T(0.5) * (at(s.uprev[ADJ ? i : 0], ul, ur, e) - at(s.uprev[ADJ ? i : 0], ul, ur, e - 1));
@@ -277,8 +286,8 @@ struct Pipe {
     struct State {
         Level s0, s1;
         In in;
-        T k[K][VX], kz[K][VX];       // newest plane's k; its faces to the plane before
-        T ka[VX], kb[VX];            // k above and below the wave's rows, newest plane
+        T k[K][VX], kz[K][VX];       // half of the newest plane's k; its faces to the plane before
+        T ka[VX], kb[VX];            // half of k above and below the wave's rows, newest plane
         T ghold[ADJ ? K : 1][VX];    // step 1's dL/dk of the plane step 2 finishes next
     };
     enum Phase { kFirst, kStep1, kBoth, kLast };
@@ -290,13 +299,15 @@ struct Pipe {
         const int own = (2 * c.wave) * W + c.lane * VX, hrow = c.hslot * W + c.lane * VX;
         T v[K][VX], k[K][VX], u[ADJ ? K : 1][VX], u1[ADJ ? K : 1][VX], gold[ADJ ? K : 1][VX], ua[VX], ub[VX];
         copy(v, s.in.v);
-        copy(k, s.in.k);
+#pragma unroll
+        for (int i = 0; i < K; ++i) halve(k[i], s.in.k[i]);
         if constexpr (ADJ) {
             copy(u, s.in.u);
             copy(u1, s.in.u1);
         }
         if constexpr (PH == kStep1 || PH == kBoth) {
             put(buf + FV * FIELD + hrow, s.in.hv);
+            halve(s.in.hk, s.in.hk);
             put(buf + FK * FIELD + hrow, s.in.hk);
             if constexpr (ADJ) put(buf + FU * FIELD + hrow, s.in.hu);
         }
@@ -321,7 +332,7 @@ struct Pipe {
 #pragma unroll
         for (int i = 0; i < K; ++i)
 #pragma unroll
-            for (int e = 0; e < VX; ++e) kz[i][e] = T(0.5) * (k[i][e] + s.k[i][e]);
+            for (int e = 0; e < VX; ++e) kz[i][e] = k[i][e] + s.k[i][e];
         zface(c, s.s0, v, u, kz, (z - 1 == 0) + (z == c.nz), w1, g0);
         const bool ghost1 = zghost(z - 1, c.nz);
 #pragma unroll

@@ -16,7 +16,7 @@
 // u and lambda are 0 on the ghost layer: they are read through buffer
 // descriptors whose range is the row (or plane), and a row, plane or column
 // outside the grid reads 0.  k is read with clamped indices: the ghost
-// neighbour of an edge cell reads that cell's own k, and (k + k) / 2 = k
+// neighbour of an edge cell reads that cell's own k, and k / 2 + k / 2 = k
 // exactly, so the interior formula gives the edge term bit for bit.  The
 // interior dL/dk term (u[f] - u[i]) / 2 * (lambda[i] - lambda[f]) gives half of
 // a ghost face's -u[i] * lambda[i]; the other half is added at the end, once per
@@ -177,12 +177,12 @@ struct Kern {
                     nb[3][f] = e > 0 ? C.v[f][k][e > 0 ? e - 1 : 0] : lft[f];
                     nb[4][f] = e < VX - 1 ? C.v[f][k][e < VX - 1 ? e + 1 : 0] : rgt[f];
                 }
-                const T uc = C.v[0][k][e], kc = C.v[1][k][e];
+                const T uc = C.v[0][k][e], hc = T(0.5) * C.v[1][k][e];
                 T acc = T(0);
                 if constexpr (!ADJ) {
 #pragma unroll
                     for (int fc = 0; fc < 6; ++fc) {
-                        const T kap = T(0.5) * (kc + nb[fc][1]);
+                        const T kap = fma_c(T(0.5), nb[fc][1], hc);
                         acc = fma_c(kap, nb[fc][0] - uc, acc);
                     }
                     o[e] = fma_c(c.alpha, acc, uc);
@@ -191,7 +191,7 @@ struct Kern {
                     T gacc = T(0);
 #pragma unroll
                     for (int fc = 0; fc < 6; ++fc) {
-                        const T kap = T(0.5) * (kc + nb[fc][1]);
+                        const T kap = fma_c(T(0.5), nb[fc][1], hc);
                         acc = fma_c(kap, nb[fc][2] - lc, acc);
                         gacc = fma_c(T(0.5) * (nb[fc][0] - uc), lc - nb[fc][2], gacc);
                     }

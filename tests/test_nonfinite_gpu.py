@@ -93,3 +93,22 @@ def test_varcoef_infinite_values_at_the_faces(dtype, what, shape):
                 assert np.isinf(want[2][at]), "the case tells nothing"
             for i, (a, b) in enumerate(zip(got, want)):
                 assert np.array_equal(a, b, equal_nan=True), f"buffer {i}: {np.argwhere(~((a == b) | (np.isnan(a) & np.isnan(b))))[:4]}"
+
+
+# conductivities whose sum overflows where their mean does not: the same bits as
+# with k times 2^-8 and the diffusion number times 2^8, and as in the one-cell form
+@pytest.mark.parametrize("dtype,big,small", [("f64", 1023, -300), ("f32", 127, -40)])
+@pytest.mark.parametrize("shape", [(9, 95, 512), (7, 64, 100)])
+def test_varcoef_largest_conductivities(dtype, big, small, shape):
+    rng = np.random.default_rng(84)
+    k = (1.0 + 0.999 * rng.random(shape)) * 2.0 ** big  # the type's last binade
+    u0, y = rng.random(shape) * 2.0 ** small, rng.random(shape) * 2.0 ** small
+    alpha = 2.0 ** (3 - big)
+    for steps in (1, 2, 3):
+        print(f"varcoef largest k {dtype} {shape} steps {steps}", flush=True)
+        got, want = (_varcoef(u0, k, y, alpha, dtype, steps, naive) for naive in (False, True))
+        scaled = _varcoef(u0, k * 2.0 ** -8, y, alpha * 2.0 ** 8, dtype, steps, False)
+        for i in range(3):
+            assert np.array_equal(got[i], want[i]), f"buffer {i}"
+        for i in range(2):
+            assert np.isfinite(got[i]).all() and np.array_equal(got[i], scaled[i]), f"buffer {i} of the scaled problem"
