@@ -2440,6 +2440,15 @@ st_status varcoef_launch(const st_plan_s* p, bool adjoint, const void* u, const 
     return ST_OK;
 }
 
+// Whether every buffer of a call (NULL: none) is aligned to an element, which the
+// two-step kernels' buffer accesses need.
+template <typename... P>
+bool elems_aligned(const st_plan_s* p, void* const* list, int64_t n, const P*... ptrs) {
+    bool ok = (elem_aligned(ptrs, p->dtype) && ...);
+    for (int64_t i = 0; i < n && ok; ++i) ok = elem_aligned(list[i], p->dtype);
+    return ok;
+}
+
 // Launch geometry of the two-step kernels for one plan and direction; vx == 0:
 // they do not take the plan.  They take every grid their tiles fit into, but
 // for FP64 grids below 3 * 2^17 cells: a pass is a chain of at least five
@@ -2532,7 +2541,8 @@ extern "C" st_status stencil_run_ckpt(st_plan plan, void* grid, void* work, cons
     void* cur = grid;
     void* nxt = work;
     // two steps per pass; a checkpoint of the state between is stored by the pass
-    const VarcoefPairs pairs = steps > 1 ? varcoef_pairs(plan, false) : VarcoefPairs();
+    const bool elems = elems_aligned(plan, ckpts, ckpts ? ceil_div(steps, every) : 0, grid, work, k);
+    const VarcoefPairs pairs = steps > 1 && elems ? varcoef_pairs(plan, false) : VarcoefPairs();
     for (int64_t t = 0; t < steps; ++t) {
         if (ckpts && t % every == 0)
             ST_HIP(hipMemcpyAsync(ckpts[t / every], cur, bytes, hipMemcpyDeviceToDevice, s), "hipMemcpyAsync(checkpoint)");
@@ -2580,8 +2590,9 @@ extern "C" st_status stencil_adjoint_run(st_plan plan, const void* k, double alp
     void* cur = lambda;
     void* nxt = work;
     const int64_t longest = std::min(every, steps);
-    const VarcoefPairs fwd = longest > 2 ? varcoef_pairs(plan, false) : VarcoefPairs();
-    const VarcoefPairs adj = longest > 1 && grad_k ? varcoef_pairs(plan, true) : VarcoefPairs();
+    const bool elems = elems_aligned(plan, ckpts, nck, lambda, work, k, grad_k, seg);
+    const VarcoefPairs fwd = longest > 2 && elems ? varcoef_pairs(plan, false) : VarcoefPairs();
+    const VarcoefPairs adj = longest > 1 && grad_k && elems ? varcoef_pairs(plan, true) : VarcoefPairs();
     for (int64_t c = nck - 1; c >= 0; --c) {
         const int64_t n0 = c * every;
         const int64_t len = std::min(every, steps - n0);
