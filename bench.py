@@ -213,7 +213,7 @@ def heat3d(torch, st, synth, dtype, select=None, n=512, steps=100, alpha=0.15, f
         # the same sweep through stencil_run_flux: FP64 outflow of every step
         w.flux = torch.zeros(1, dtype=torch.float64, device="cuda")
         w.run = lambda: w.plan.run_flux(w.u, w.coeffs, w.steps, w.flux, work=w.work)
-    w.kernel_tb = w.plan.info()["tb"]
+    w.kernel_tb = w.plan.launches("flux" if flux else "run")["tb"]
     return w
 
 
@@ -243,7 +243,7 @@ def heat2d(torch, st, synth, dtype, select=None, n=512, steps=100, alpha=0.2):
     w.steps, w.cells, w.dtype = steps, n * n, dtype
     w.name = f"2D 5-point heat stencil, {n}^2, {steps} steps, alpha {alpha}, zero boundary"
     w.run = lambda: w.plan.run(w.u, w.coeffs, w.steps, work=w.work)
-    w.kernel_tb = w.plan.info()["tb"]
+    w.kernel_tb = w.plan.launches()["tb"]
     return w
 
 
@@ -266,7 +266,7 @@ def heat1d(torch, st, synth, dtype, select=None, n=10_000_000, steps=1000, alpha
     w.steps, w.cells, w.dtype = steps, n, dtype
     w.name = f"1D {2 * radius + 1}-point star, {n} cells, {steps} steps, zero boundary"
     w.run = lambda: w.plan.run(w.u, w.coeffs, w.steps, work=w.work)
-    w.kernel_tb = w.plan.info()["tb"]
+    w.kernel_tb = w.plan.launches()["tb"]
     return w
 
 
@@ -284,7 +284,7 @@ def box27(torch, st, synth, dtype, select=None, n=512, steps=20):
     w.steps, w.cells, w.dtype = steps, n ** 3, dtype
     w.name = f"3D 27-point box stencil, {n}^3, {steps} steps, zero boundary"
     w.run = lambda: w.plan.run(w.u, w.coeffs, w.steps, work=w.work)
-    w.kernel_tb = w.plan.info()["tb"]
+    w.kernel_tb = w.plan.launches()["tb"]
     return w
 
 
@@ -300,7 +300,7 @@ def box2d(torch, st, synth, dtype, select=None, n=8192, steps=1000):
     w.steps, w.cells, w.dtype = steps, n * n, dtype
     w.name = f"2D 9-point box stencil (weights 1/9), {n}^2, {steps} steps, periodic"
     w.run = lambda: w.plan.run(w.u, w.coeffs, w.steps, work=w.work)
-    w.kernel_tb = w.plan.info()["tb"]
+    w.kernel_tb = w.plan.launches()["tb"]
     return w
 
 
@@ -318,7 +318,7 @@ def box2d25(torch, st, synth, dtype, select=None, n=8192, steps=100):
     w.steps, w.cells, w.dtype = steps, n * n, dtype
     w.name = f"2D 25-point box stencil (weights 1/25), {n}^2, {steps} steps, zero boundary"
     w.run = lambda: w.plan.run(w.u, w.coeffs, w.steps, work=w.work)
-    w.kernel_tb = w.plan.info()["tb"]
+    w.kernel_tb = w.plan.launches()["tb"]
     return w
 
 
@@ -334,7 +334,7 @@ def star25(torch, st, synth, dtype, select=None, n=512, steps=50):
     w.steps, w.cells, w.dtype = steps, n ** 3, dtype
     w.name = f"3D order-4 25-point star stencil, {n}^3, {steps} steps, periodic"
     w.run = lambda: w.plan.run(w.u, w.coeffs, w.steps, work=w.work)
-    w.kernel_tb = w.plan.info()["tb"]
+    w.kernel_tb = w.plan.launches()["tb"]
     return w
 
 
@@ -359,7 +359,7 @@ def batch(torch, st, synth, dtype, select=None, ngrids=64, steps=500):
     w.name = (f"{ngrids} 2D 5-point heat grids, sides log-uniform [256, 4096] (seed 0), "
               f"alpha U[0.05, 0.24], {steps} steps, zero boundary")
     w.run = lambda: w.plan.run(w.grids, w.works, w.coeffs, [steps] * ngrids)
-    w.kernel_tb = w.plan.info()["tb"]
+    w.kernel_tb = w.plan.launches()["tb"]
     return w
 
 
@@ -463,7 +463,7 @@ DEFAULT_DTYPE = {"varcoef": "f32", "heat3d": "f64", "heat2d": "f64", "box2d": "f
                  "star25": "f32", "batch": "f32",
                  "heat1d": "f64", "star1d5": "f64", "box27": "f64"}
 KERNEL_NAMES = {0: "naive_kernel", 1: "stream2d_kernel", 2: "stream3d_kernel", 3: "varcoef3d_kernel",
-                4: "stream1d_kernel", 5: "box3d_kernel"}
+                4: "stream1d_kernel", 5: "box3d_kernel", 6: "tile2d_kernel", 7: "brick3d_kernel"}
 
 
 def measure(torch, w, steps, warmup):
@@ -540,7 +540,7 @@ def main():
         w = heat3d(torch, st, synth, dtype, _select(args), flux=True)
     else:
         w = WORKLOADS[args.workload](torch, st, synth, dtype, _select(args))
-    info = w.plan.info()
+    info = w.plan.launches("flux" if args.flux else "run")
     log(f"plan: {info}")
     tkey = [args.workload, dtype, info["kernel"], info["tb"], info["tile_x"], info["tile_y"], info["tile_z"],
             info["block"], info["workgroups"], info.get("pipeline", 0)] + \
@@ -572,7 +572,7 @@ def main():
                    "parallelism": "single GPU"},
         "roofline": {"bound": "hbm",
                      "kernel": ("boxpipe3d_kernel" if info.get("pipeline") and info["kernel"] == 5 else
-                                "pipe3d_kernel" if info.get("pipeline") else
+                                "pipe3d_kernel" if info.get("pipeline") and info["kernel"] == 2 else
                                 "stream2d_kernel + tess2d_band_kernel" if info.get("tessellated") else
                                 KERNEL_NAMES[info["kernel"]]),
                      "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",

@@ -91,6 +91,8 @@ typedef struct st_plan_s* st_plan;
 #define ST_KERNEL_VARCOEF3D 3  /* 3D variable-coefficient heat                 */
 #define ST_KERNEL_STREAM1D 4   /* 1D star, a wave's strip of cells in registers */
 #define ST_KERNEL_BOX3D 5      /* 3D radius-1 box, planes streamed, 1-2 steps    */
+#define ST_KERNEL_TILE2D 6     /* 2D star/box, small grids: tiles in registers   */
+#define ST_KERNEL_BRICK3D 7    /* 3D 7-point star, small grids: bricks in registers */
 
 typedef struct {
     int32_t kernel;           /* ST_KERNEL_*                                    */
@@ -172,12 +174,30 @@ st_status stencil_autotune_cache(const char* path);
 st_status stencil_plan_destroy(st_plan plan);
 
 /*
- * Describe the plan's current choice.  A plan whose choice is its own (no
- * ST_PLAN_AUTOTUNE, no stencil_plan_select) may still run a grid that is too
- * small to fill the device with tiles one step per launch, or a small grid in
- * register tiles with several steps per launch, with the same bits.
+ * Describe the plan's current choice among its candidates.  What a run call
+ * launches may differ, with the same bits: see stencil_plan_launches.
  */
 st_status stencil_plan_info(st_plan plan, st_plan_info* info);
+
+/*
+ * stencil_plan_launches -- describe what a run call on this plan launches, on
+ * buffers aligned to 16 bytes (st_plan_info as for stencil_plan_info; `variant` is
+ * -1 for a kernel that is in no candidate list).  It differs from the current
+ * choice where a small grid runs in register tiles or bricks, several steps per
+ * launch, or one step per launch; where a grid does not take the chosen
+ * pipeline; and where an outflow run takes another depth.  `pipeline` holds the
+ * columns a lane for ST_KERNEL_TILE2D, ST_KERNEL_BRICK3D and the two-step
+ * passes (tb == 2) of ST_KERNEL_VARCOEF3D, which calls of one step do not use.
+ *   call    ST_CALL_RUN      stencil_run, stencil_run_noalloc, stencil_run_ckpt,
+ *                            stencil_batch_run
+ *           ST_CALL_FLUX     stencil_run_flux, stencil_batch_run_flux
+ *           ST_CALL_ADJOINT  stencil_adjoint_run
+ * Errors: ST_ERR_ARG; ST_ERR_MISMATCH when the plan has no such call.
+ */
+#define ST_CALL_RUN 0
+#define ST_CALL_FLUX 1
+#define ST_CALL_ADJOINT 2
+st_status stencil_plan_launches(st_plan plan, int32_t call, st_plan_info* info);
 
 /*
  * stencil_plan_candidate -- describe tiling candidate `index` of the plan
@@ -189,8 +209,12 @@ st_status stencil_plan_candidate(st_plan plan, int32_t index, st_plan_info* info
  * stencil_plan_select -- force a kernel family, fused depth and tiling
  * candidate (used by the autotuner and by tests that compare candidates).
  * kernel = -1 keeps the family; tb <= 0 keeps the depth; variant < 0 keeps
- * the candidate.  Returns ST_ERR_UNSUPPORTED when the combination cannot run
- * this plan.
+ * the candidate.  ST_KERNEL_TILE2D and ST_KERNEL_BRICK3D are in no candidate
+ * list and are selected by name only: variant is their columns a lane (1, 2 or
+ * 4), and tb <= 0, variant < 0 take the fastest by the library's time model; the
+ * candidate selected before stays for the calls they do not take (outflow
+ * runs, buffers off an element's alignment).  Returns ST_ERR_UNSUPPORTED when
+ * the combination cannot run this plan.
  */
 st_status stencil_plan_select(st_plan plan, int32_t kernel, int32_t tb, int32_t variant);
 

@@ -19,7 +19,7 @@ __all__ = [
     "StencilError", "Plan", "BatchPlan", "run", "library", "library_path", "build",
     "F64", "F32", "BF16", "BC_ZERO", "BC_PERIODIC", "PLAN_AUTOTUNE", "PLAN_NAIVE",
     "PLAN_VARCOEF", "PLAN_GRAPH", "PLAN_OWN_WORK", "KERNEL_NAIVE", "KERNEL_STREAM2D", "KERNEL_STREAM3D", "KERNEL_VARCOEF3D",
-    "KERNEL_STREAM1D", "KERNEL_BOX3D",
+    "KERNEL_STREAM1D", "KERNEL_BOX3D", "KERNEL_TILE2D", "KERNEL_BRICK3D",
     "STATUS", "StencilFn", "varcoef_plan", "copy", "autotune_cache", "batch_run",
 ]
 
@@ -30,6 +30,8 @@ F64, F32, BF16 = 0, 1, 2
 BC_ZERO, BC_PERIODIC = 0, 1
 PLAN_AUTOTUNE, PLAN_NAIVE, PLAN_VARCOEF, PLAN_GRAPH, PLAN_OWN_WORK = 0x1, 0x2, 0x4, 0x8, 0x10
 KERNEL_NAIVE, KERNEL_STREAM2D, KERNEL_STREAM3D, KERNEL_VARCOEF3D, KERNEL_STREAM1D, KERNEL_BOX3D = 0, 1, 2, 3, 4, 5
+KERNEL_TILE2D, KERNEL_BRICK3D = 6, 7
+_CALLS = {"run": 0, "flux": 1, "adjoint": 2}
 STATUS = {0: "ST_OK", -1: "ST_ERR_ARG", -2: "ST_ERR_UNSUPPORTED", -3: "ST_ERR_MISMATCH",
           -4: "ST_ERR_NOMEM", -5: "ST_ERR_HIP", -6: "ST_ERR_CAPTURE"}
 _DTYPES = {"f64": F64, "f32": F32, "bf16": BF16, F64: F64, F32: F32, BF16: BF16}
@@ -100,6 +102,7 @@ def library():
             "stencil_plan_info": [P, ctypes.POINTER(PlanInfo)],
             "stencil_plan_candidate": [P, i32, ctypes.POINTER(PlanInfo)],
             "stencil_plan_select": [P, i32, i32, i32],
+            "stencil_plan_launches": [P, i32, ctypes.POINTER(PlanInfo)],
             "stencil_run": [P, P, P, p_dbl, p_i64, i64, i32, P],
             "stencil_run_flux": [P, P, P, p_dbl, p_i64, i64, i32, P, P],
             "stencil_run_noalloc": [P, P, p_dbl, p_i64, i64, i32, P],
@@ -214,6 +217,12 @@ class Plan:
     def info(self) -> dict:
         i = PlanInfo()
         _check(library().stencil_plan_info(self._h, ctypes.byref(i)))
+        return i.as_dict()
+
+    def launches(self, call: str = "run") -> dict:
+        """``stencil_plan_launches``: what "run", "flux" or "adjoint" launches."""
+        i = PlanInfo()
+        _check(library().stencil_plan_launches(self._h, _CALLS[call], ctypes.byref(i)))
         return i.as_dict()
 
     def candidates(self) -> List[dict]:
@@ -405,6 +414,12 @@ class BatchPlan:
     def info(self) -> dict:
         i = PlanInfo()
         _check(library().stencil_plan_info(self._h, ctypes.byref(i)))
+        return i.as_dict()
+
+    def launches(self, call: str = "run") -> dict:
+        """``stencil_plan_launches``: what "run", "flux" or "adjoint" launches."""
+        i = PlanInfo()
+        _check(library().stencil_plan_launches(self._h, _CALLS[call], ctypes.byref(i)))
         return i.as_dict()
 
     def select(self, kernel: int = -1, tb: int = 0, variant: int = -1):

@@ -197,6 +197,9 @@ hipError_t go(bool per, const Brick3DArgs& a, hipStream_t s) {
 }  // namespace b3
 
 int brick3d_edge() { return b3::kEdge; }
+int brick3d_lds_bytes(int dtype, int vx) {
+    return dtype == kF64 ? b3::Brick<double, 1, false>::LDS_BYTES * vx : b3::Brick<float, 1, false>::LDS_BYTES * vx;
+}
 
 hipError_t launch_brick3d(int dtype, int vx, bool periodic, const Brick3DArgs& a, hipStream_t s) {
     if (dtype == kF64 && vx == 1) return b3::go<double, 1>(periodic, a, s);

@@ -92,6 +92,7 @@ struct Tile2DArgs {
     double w[25];
 };
 int tile2d_rows();
+int tile2d_lds_bytes(int dtype, int radius, int vx);
 // vx: FP64 and FP32 1 (radius 1) or 2, bfloat16 4
 hipError_t launch_tile2d(int dtype, int radius, int vx, bool box, bool periodic, const Tile2DArgs& a, hipStream_t s);
 
@@ -109,6 +110,7 @@ struct Brick3DArgs {
     double w[7];
 };
 int brick3d_edge();
+int brick3d_lds_bytes(int dtype, int vx);
 // vx: FP64 1, FP32 1 or 2
 hipError_t launch_brick3d(int dtype, int vx, bool periodic, const Brick3DArgs& a, hipStream_t s);
 
@@ -221,7 +223,7 @@ int varcoef_stream_occupancy(int dtype, bool adjoint);  // work-groups per CU, 0
 // 2 GiB; the adjoint also nx % vx == 0 and a grad buffer.  4 planes re-streamed
 // per chunk.  vx: FP64 2 or 1, FP32 4 or 1.
 struct VarcoefPipeShape {
-    int w, h, out_w, out_h, wgs_per_cu;
+    int w, h, out_w, out_h, wgs_per_cu, lds_bytes;
 };
 VarcoefPipeShape varcoef_pipe_shape(int dtype, int vx, bool adjoint);
 hipError_t launch_varcoef_pipe(int dtype, int vx, bool adjoint, const VarcoefArgs& a, hipStream_t s);

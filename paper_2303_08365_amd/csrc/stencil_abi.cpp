@@ -147,8 +147,6 @@ int elem_bytes(int dtype) { return dtype == kF64 ? 8 : (dtype == kF32 ? 4 : 2); 
 // ---------------------------------------------------------------------------
 namespace {
 
-// a Candidate's kernel: register tiles and bricks, in no plan's list
-constexpr int32_t kKernelTile2D = 100, kKernelBrick3D = 101;
 enum StandIn { kNoStandIn, kOneStep, kTiles };
 
 // One tiling candidate of a plan.
@@ -184,11 +182,13 @@ struct st_plan_s {
     std::vector<Candidate> cands;
     int32_t sel = 0;
     // the selection is the time model's own (not the caller's, the
-    // autotuner's or the environment's), and it puts one step per launch
-    // before the selected tiling: the grid is too small for tiles
+    // autotuner's or the environment's)
     bool modelled = false;
-    int stand_in = kNoStandIn;  // what runs instead of a modelled plan's candidate
-    Candidate tile;             // kTiles: its depth and columns a lane
+    // what runs instead of the selected candidate: one step per launch where the
+    // model finds the grid too small for the list's tilings, register tiles or
+    // bricks (in no plan's list) where the model or the caller puts them first
+    int stand_in = kNoStandIn;
+    Candidate tile;  // kTiles: its kernel, depth and columns a lane (k2.vx)
     // Device memory a plan owns is allocated when the plan is made (see
     // plan_buffers), never by a run call.
     void* owned_work = nullptr;   // ST_PLAN_OWN_WORK
@@ -701,24 +701,25 @@ bool geo_brick(const st_plan_s* p, int vx, int t, Brick3DArgs& a) {
 // 256^2 0.55 (1.94), 2048^2 2.64 (3.28).  The model is within 12 % of all of them.
 // Radius 2 fills the registers of two work-groups a CU: further ones cost about
 // half more (FP64 25 points: 1024^2 2.9 in tiles, 4.8 in rows; 3000^2 16.2 and 15.3).
-double tile_select(st_plan_s* p) {
+// `tile` gets them; only_vx, only_t > 0: those columns a lane, that depth.
+double tile_select(const st_plan_s* p, Candidate& tile, int only_vx = 0, int only_t = 0) {
     double best = 1e300;
-    p->tile = Candidate();
-    p->tile.kernel = kKernelTile2D;
+    tile = Candidate();
+    tile.kernel = ST_KERNEL_TILE2D;
     const int dw = p->dtype == kF64 ? 2 : 1, rows = tile2d_rows() / 8;
     for (int vx : {1, 2, 4}) {
-        if ((p->dtype == kBF16) != (vx == 4) || vx < p->radius) continue;
+        if ((p->dtype == kBF16) != (vx == 4) || vx < p->radius || (only_vx > 0 && vx != only_vx)) continue;
         const double us = 2 * kUsPerInstr * (rows * vx * (p->npoints + (p->dtype == kBF16 ? 2 : 0)) +
                                              2 * p->radius * dw * (p->cls == kStar ? rows : rows + 2 * p->radius));
-        for (int t = 2; 2 * p->radius * t < tile2d_rows(); ++t) {
+        for (int t = only_t > 0 ? only_t : 2; 2 * p->radius * t < tile2d_rows() && (only_t <= 0 || t == only_t); ++t) {
             Tile2DArgs a;
             if (!geo_tile(p, vx, t, a)) break;
             const double groups = static_cast<double>(ceil_div(static_cast<int64_t>(a.tiles_x) * a.tiles_y, device_cus()));
             const double pass = 2.3 + t * ((p->dtype == kF64 ? 0.21 : 0.16) + us) + (groups - 1) * (0.6 + t * us * (p->radius == 2 ? 1.45 : 1.0));
             if (pass / t < best) {
                 best = pass / t;
-                p->tile.tb = t;
-                p->tile.k2.vx = vx;
+                tile.tb = t;
+                tile.k2.vx = vx;
             }
         }
     }
@@ -731,16 +732,17 @@ double tile_select(st_plan_s* p) {
 // pass 2.5 (3.8), 89 x 97 x 101 3 steps 3.45 (7.5), 96^3 4 steps 3.0 (5.8), 128^3 4
 // steps of two columns 4.2 (9.1), 192^3 2 steps 11.2 (10.5: planes); FP64 96^3 4.1
 // (6.0), 128^3 7.7 (5.5: planes).
-double brick_select(st_plan_s* p) {
+double brick_select(const st_plan_s* p, Candidate& tile, int only_vx = 0, int only_t = 0) {
     double best = 1e300;
-    p->tile = Candidate();
-    p->tile.kernel = kKernelBrick3D;
+    tile = Candidate();
+    tile.kernel = ST_KERNEL_BRICK3D;
     const bool wide = p->dtype == kF64;
     const int cells = brick3d_edge() * brick3d_edge() / 16;  // a lane's rows
     for (int vx = 1; vx <= (wide ? 1 : 2); ++vx) {
+        if (only_vx > 0 && vx != only_vx) continue;
         const double us = 4 * kUsPerInstr * (cells * vx * 8 + cells * (wide ? 4 : 2)) +
                           2.0 * cells * 16 * 64 * vx * elem_bytes(p->dtype) / 128 / 2400 + (wide ? 0.25 : 0.1);
-        for (int t = 1; 2 * t < brick3d_edge(); ++t) {
+        for (int t = only_t > 0 ? only_t : 1; 2 * t < brick3d_edge() && (only_t <= 0 || t == only_t); ++t) {
             Brick3DArgs a;
             if (!geo_brick(p, vx, t, a)) break;
             const int64_t bricks = static_cast<int64_t>(a.tiles[0]) * a.tiles[1] * a.tiles[2];
@@ -748,12 +750,17 @@ double brick_select(st_plan_s* p) {
                                 static_cast<double>(ceil_div(bricks, device_cus()) - 1) * (2.9 + 1.15 * t * us);
             if (pass / t < best) {
                 best = pass / t;
-                p->tile.tb = t;
-                p->tile.k2.vx = vx;
+                tile.tb = t;
+                tile.k2.vx = vx;
             }
         }
     }
     return best;
+}
+
+double register_select(const st_plan_s* p, Candidate& tile, int only_vx = 0, int only_t = 0) {
+    if (p->flags & (ST_PLAN_NAIVE | ST_PLAN_VARCOEF)) return 1e300;
+    return p->ndim == 2 ? tile_select(p, tile, only_vx, only_t) : brick_select(p, tile, only_vx, only_t);
 }
 
 // Selection of a plan that is not autotuned: the family's fastest candidate
@@ -788,7 +795,7 @@ void model_select(st_plan_s* p, bool fixed) {
     }
     // (radius 2 by a wider margin: its model is less exact where both are near)
     const double margin = p->ndim == 2 && p->radius == 2 ? 0.8 : 0.9;
-    if (const double us = p->ndim == 2 ? tile_select(p) : brick_select(p); us < margin * best) p->stand_in = kTiles;
+    if (register_select(p, p->tile) < margin * best) p->stand_in = kTiles;
 }
 
 // Default fused depth and lane width per family.
@@ -1128,7 +1135,7 @@ st_status launch_pass(const st_plan_s* p, const Candidate& c, const void* src, v
                       const double* wcan, int tb, hipStream_t s, double* fpart = nullptr) {
     hipError_t e = hipSuccess;
     const bool elems = elem_aligned(src, p->dtype) && elem_aligned(dst, p->dtype);
-    if (c.kernel == kKernelBrick3D) {
+    if (c.kernel == ST_KERNEL_BRICK3D) {
         Brick3DArgs a;
         if (!geo_brick(p, c.k2.vx, tb, a)) return fail(ST_ERR_UNSUPPORTED, "tiling infeasible");
         a.src = src;
@@ -1138,7 +1145,7 @@ st_status launch_pass(const st_plan_s* p, const Candidate& c, const void* src, v
         if (e != hipSuccess) return hip_fail(e, "register brick launch");
         return ST_OK;
     }
-    if (c.kernel == kKernelTile2D) {
+    if (c.kernel == ST_KERNEL_TILE2D) {
         Tile2DArgs a;
         if (!geo_tile(p, c.k2.vx, tb, a)) return fail(ST_ERR_UNSUPPORTED, "tiling infeasible");
         a.src = src;
@@ -1364,28 +1371,27 @@ st_status check_flux_parts(const st_plan_s* p, int64_t need) {
     return ST_OK;
 }
 
+// What a run with candidate c_sel between these buffers launches.  A selection
+// may stand for one step per launch or for the register tiles (no outflow form).
+// The pipeline has whole-vector rows only: on a grid that does not take them
+// (too small) the run uses the plan's first other candidate, with its own depth
+// (every candidate gives the same bits; the list always ends with the one-step
+// kernel).
+const Candidate& run_pick(const st_plan_s* p, const Candidate& c_sel, const void* grid, const void* work, bool flux,
+                          int stand_in) {
+    if (stand_in == kOneStep) return p->cands.back();
+    if (stand_in == kTiles && !flux && elem_aligned(grid, p->dtype) && elem_aligned(work, p->dtype)) return p->tile;
+    if (c_sel.kernel == ST_KERNEL_STREAM3D && c_sel.k3.pipe && !fast3(p, c_sel, c_sel.tb, grid, work))
+        for (const Candidate& o : p->cands)
+            if (!(o.kernel == ST_KERNEL_STREAM3D && o.k3.pipe)) return o;
+    return c_sel;
+}
+
 // Run `steps` steps with candidate c: grid -> work -> grid ...  With `flux`
 // (zero rule only), the outflow of every step is also added to flux[0].
 st_status run_steps(st_plan_s* p, const Candidate& c_sel, void* grid, void* work, const double* wcan,
                     int64_t steps, hipStream_t s, double* flux = nullptr, int stand_in = kNoStandIn) {
-    // A selection of the time model may stand for one step per launch or for
-    // the register tiles (no outflow form).  The pipeline has whole-vector rows only: on a grid that does not take
-    // them (too small) the run uses the plan's first other
-    // candidate, with its own depth (every candidate gives the same bits; the
-    // list always ends with the one-step kernel).
-    const Candidate* pick = &c_sel;
-    if (stand_in == kOneStep) pick = &p->cands.back();
-    else if (stand_in == kTiles && !flux && elem_aligned(grid, p->dtype) && elem_aligned(work, p->dtype)) pick = &p->tile;
-    else if (c_sel.kernel == ST_KERNEL_STREAM3D && c_sel.k3.pipe) {
-        if (!fast3(p, c_sel, c_sel.tb, grid, work)) {
-            for (const Candidate& o : p->cands)
-                if (!(o.kernel == ST_KERNEL_STREAM3D && o.k3.pipe)) {
-                    pick = &o;
-                    break;
-                }
-        }
-    }
-    const Candidate& c_in = *pick;
+    const Candidate& c_in = run_pick(p, c_sel, grid, work, flux != nullptr, stand_in);
     const bool elems = elem_aligned(grid, p->dtype) && elem_aligned(work, p->dtype);
     // the pipeline's outflow twin has whole-vector rows only
     const bool fused = flux && flux_fused(p, c_in) &&
@@ -1482,6 +1488,26 @@ void describe(const st_plan_s* p, const Candidate& c, int index, st_plan_info* i
         info->tile_y = info->tile_z = 1;
         info->block = 256;
         info->workgroups = ceil_div(g.strips, 4);
+    } else if (c.kernel == ST_KERNEL_TILE2D) {
+        Tile2DArgs a;
+        geo_tile(p, c.k2.vx, c.tb, a);
+        info->tile_x = a.out_w;
+        info->tile_y = a.out_h;
+        info->tile_z = 1;
+        info->block = 8 * tile2d_rows();  // 8 rows a wave
+        info->workgroups = static_cast<int64_t>(a.tiles_x) * a.tiles_y;
+        info->lds_bytes = tile2d_lds_bytes(p->dtype, p->radius, c.k2.vx);
+        info->pipeline = c.k2.vx;
+    } else if (c.kernel == ST_KERNEL_BRICK3D) {
+        Brick3DArgs a;
+        geo_brick(p, c.k2.vx, c.tb, a);
+        info->tile_x = a.own[2];
+        info->tile_y = a.own[1];
+        info->tile_z = a.own[0];
+        info->block = 1024;
+        info->workgroups = static_cast<int64_t>(a.tiles[0]) * a.tiles[1] * a.tiles[2];
+        info->lds_bytes = brick3d_lds_bytes(p->dtype, c.k2.vx);
+        info->pipeline = c.k2.vx;
     } else if (c.kernel == ST_KERNEL_VARCOEF3D) {
         info->tile_x = info->tile_y = info->tile_z = 1;
         info->block = 256;
@@ -1597,6 +1623,36 @@ st_status autotune(st_plan_s* p) {
     return ST_OK;
 }
 
+// The candidate of an outflow run; stand_in gets what runs instead of it.
+const Candidate& flux_choice(const st_plan_s* plan, int& stand_in) {
+    const Candidate* cand = &plan->cands[plan->sel];
+    stand_in = plan->stand_in == kOneStep ? kOneStep : kNoStandIn;
+    if (plan->modelled && plan->bc == kZero) {
+        // a launch more per pass where the kernel sums the outflow, two more
+        // per step where it does not (about 4 us each): the fastest of the
+        // model's candidates under that account
+        const auto account = [&](const Candidate& c, bool alone) {
+            if (alone || !flux_fused(plan, c)) return (alone ? step_us(plan, plan->cands.back()) : step_us(plan, c) * c.tb) + 8.0;
+            return step_us(plan, c) + 4.0 / c.tb;
+        };
+        double best = account(*cand, stand_in == kOneStep);
+        for (const Candidate& c : plan->cands)
+            if (c.chunk == plan->cands[0].chunk && c.kernel != ST_KERNEL_NAIVE && flux_fused(plan, c))
+                if (const double us = account(c, false); us < 0.97 * best) {
+                    best = us;
+                    cand = &c;
+                    stand_in = kNoStandIn;
+                }
+    }
+    // a fused candidate of the same depth with an outflow-summing twin
+    // stands in for one without (same states bit for bit: every tiling of a
+    // plan gives the same grid)
+    if (stand_in == kNoStandIn && cand->kernel == ST_KERNEL_STREAM3D && !flux_fused(plan, *cand))
+        for (const Candidate& c : plan->cands)
+            if (c.kernel == cand->kernel && c.tb == cand->tb && flux_fused(plan, c)) return c;
+    return *cand;
+}
+
 // Key of a run: every argument that ends up inside the launches.
 void key_push(std::vector<uint64_t>& k, const void* p) { k.push_back(reinterpret_cast<uintptr_t>(p)); }
 void key_push(std::vector<uint64_t>& k, int64_t v) { k.push_back(static_cast<uint64_t>(v)); }
@@ -1699,6 +1755,7 @@ const char* stencil_version(void) { return "paper_2303_08365_amd stencil 0.1 (gf
 
 namespace {
 st_status plan_buffers(st_plan_s* p);
+void describe_varcoef(const st_plan_s* p, bool adjoint, st_plan_info* info);
 
 // stencil_plan without the device buffers and the mirror (the mirror plan of
 // a constant-weight adjoint is made this way, host memory only).
@@ -1784,9 +1841,42 @@ st_status stencil_plan_candidate(st_plan plan, int32_t index, st_plan_info* info
     return ST_OK;
 }
 
+st_status stencil_plan_launches(st_plan plan, int32_t call, st_plan_info* info) {
+    if (!plan || !info) return fail(ST_ERR_ARG, "plan or info is NULL");
+    if (call != ST_CALL_RUN && call != ST_CALL_FLUX && call != ST_CALL_ADJOINT) return fail(ST_ERR_ARG, "call %d not in 0..2", call);
+    if (plan->flags & ST_PLAN_VARCOEF) {
+        if (call == ST_CALL_FLUX) return fail(ST_ERR_MISMATCH, "a variable-coefficient plan has no outflow run");
+        describe_varcoef(plan, call == ST_CALL_ADJOINT, info);
+        return ST_OK;
+    }
+    if (call == ST_CALL_ADJOINT) {
+        if (plan->batch || !plan->mirror) return fail(ST_ERR_MISMATCH, "the plan has no transposed sweep");
+        return stencil_plan_launches(plan->mirror, ST_CALL_RUN, info);
+    }
+    const Candidate* c = &plan->cands[plan->sel];
+    if (!plan->batch) {
+        const bool flux = call == ST_CALL_FLUX && plan->bc == kZero;
+        int stand_in = plan->stand_in;
+        if (call == ST_CALL_FLUX) c = &flux_choice(plan, stand_in);
+        c = &run_pick(plan, *c, nullptr, nullptr, flux, stand_in);
+    }
+    const int index = c == &plan->tile ? -1 : static_cast<int>(c - plan->cands.data());
+    describe(plan, *c, index, info);
+    return ST_OK;
+}
+
 st_status stencil_plan_select(st_plan plan, int32_t kernel, int32_t tb, int32_t variant) {
     if (!plan) return fail(ST_ERR_ARG, "plan is NULL");
     const int n = static_cast<int>(plan->cands.size());
+    if (kernel == ST_KERNEL_TILE2D || kernel == ST_KERNEL_BRICK3D) {
+        Candidate tile;
+        if (register_select(plan, tile, std::max(variant, 0), std::max(tb, 0)) >= 1e300 || tile.kernel != kernel)
+            return fail(ST_ERR_UNSUPPORTED, "no register tiles of kernel %d, depth %d and %d columns a lane", kernel, tb,
+                        variant);
+        plan->tile = tile;
+        plan->stand_in = kTiles;
+        return ST_OK;
+    }
     if (variant >= 0) {
         if (variant >= n) return fail(ST_ERR_UNSUPPORTED, "candidate %d not in 0..%d", variant, n - 1);
         const Candidate& c = plan->cands[variant];
@@ -1822,6 +1912,7 @@ st_status stencil_run(st_plan plan, void* grid, void* work, const double* coeffs
         key_push(key, work);
         key_push(key, steps);
         key_push(key, static_cast<int64_t>(plan->sel) * 3 + plan->stand_in);
+        key_push(key, static_cast<int64_t>(plan->tile.tb) * 8 + plan->tile.k2.vx);
         for (int i = 0; i < plan->npoints; ++i) key_push(key, wcan[i]);
     }
     const Candidate cand = plan->cands[plan->sel];
@@ -1857,36 +1948,10 @@ st_status stencil_run_flux(st_plan plan, void* grid, void* work, const double* c
     bool nothing = false;
     if (st_status r = prepare_run(plan, grid, work, coeffs, shape, steps, bc, s, wcan, nothing); r != ST_OK || nothing)
         return r;
-    // a fused candidate of the same depth with an outflow-summing twin
-    // stands in for one without (same states bit for bit: every tiling of a
-    // plan gives the same grid)
-    Candidate cand = plan->cands[plan->sel];
-    bool one_step = plan->stand_in == kOneStep;
-    if (plan->modelled && plan->bc == kZero) {
-        // a launch more per pass where the kernel sums the outflow, two more
-        // per step where it does not (about 4 us each): the fastest of the
-        // model's candidates under that account
-        const auto account = [&](const Candidate& c, bool alone) {
-            if (alone || !flux_fused(plan, c)) return (alone ? step_us(plan, plan->cands.back()) : step_us(plan, c) * c.tb) + 8.0;
-            return step_us(plan, c) + 4.0 / c.tb;
-        };
-        double best = account(cand, one_step);
-        for (const Candidate& c : plan->cands)
-            if (c.chunk == plan->cands[0].chunk && c.kernel != ST_KERNEL_NAIVE && flux_fused(plan, c))
-                if (const double us = account(c, false); us < 0.97 * best) {
-                    best = us;
-                    cand = c;
-                    one_step = false;
-                }
-    }
-    if (!one_step && cand.kernel == ST_KERNEL_STREAM3D && !flux_fused(plan, cand))
-        for (const Candidate& c : plan->cands)
-            if (c.kernel == cand.kernel && c.tb == cand.tb && flux_fused(plan, c)) {
-                cand = c;
-                break;
-            }
+    int stand_in = kNoStandIn;
+    const Candidate& cand = flux_choice(plan, stand_in);
     // a periodic grid has no boundary: nothing leaves
-    return run_steps(plan, cand, grid, work, wcan, steps, s, plan->bc == kZero ? flux : nullptr, one_step ? kOneStep : kNoStandIn);
+    return run_steps(plan, cand, grid, work, wcan, steps, s, plan->bc == kZero ? flux : nullptr, stand_in);
 }
 
 }  // extern "C"
@@ -2499,6 +2564,21 @@ VarcoefPairs varcoef_pairs(const st_plan_s* p, bool adjoint) {
         }
     }
     return best;
+}
+
+void describe_varcoef(const st_plan_s* p, bool adjoint, st_plan_info* info) {
+    describe(p, p->cands[p->sel], p->sel, info);
+    const VarcoefPairs g = varcoef_pairs(p, adjoint);
+    if (g.vx == 0) return;
+    const VarcoefPipeShape sh = varcoef_pipe_shape(p->dtype, g.vx, adjoint);
+    info->tb = 2;
+    info->tile_x = sh.out_w;
+    info->tile_y = sh.out_h;
+    info->tile_z = g.a.chunk_z;
+    info->block = 512;
+    info->workgroups = static_cast<int64_t>(g.a.tiles_x) * g.a.tiles_y * g.a.chunks_z;
+    info->lds_bytes = sh.lds_bytes;
+    info->pipeline = g.vx;
 }
 
 // Two steps: forward (u1 null) u -> mid (may be null) -> out; adjoint (u, u1 the

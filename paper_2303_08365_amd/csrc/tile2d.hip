@@ -225,6 +225,9 @@ hipError_t go(bool box, bool per, const Tile2DArgs& a, hipStream_t s) {
 }  // namespace t2d
 
 int tile2d_rows() { return t2d::kNW * t2d::kK; }
+int tile2d_lds_bytes(int dtype, int radius, int vx) {
+    return 2 * 2 * radius * (t2d::kNW + 1) * 64 * vx * (dtype == kF64 ? 8 : 4);  // two buffers of Tile::SLOTS rows
+}
 
 hipError_t launch_tile2d(int dtype, int radius, int vx, bool box, bool periodic, const Tile2DArgs& a, hipStream_t s) {
     if (radius == 1) {

@@ -549,7 +549,9 @@ void pick(bool adjoint, const VarcoefArgs& a, hipStream_t s) {
 
 VarcoefPipeShape varcoef_pipe_shape(int dtype, int vx, bool adjoint) {
     const int hx = (2 + vx - 1) / vx * vx, h = vcp::kNW * (adjoint ? vcp::kKA : vcp::kKF);
-    return VarcoefPipeShape{64 * vx, h, 64 * vx - 2 * hx, h - 2, vcp::wgs_per_cu(vx * (dtype == kF64 ? 8 : 4))};
+    const int esz = dtype == kF64 ? 8 : 4, fields = adjoint ? 4 : 3;
+    return VarcoefPipeShape{64 * vx, h, 64 * vx - 2 * hx, h - 2, vcp::wgs_per_cu(vx * esz),
+                            2 * fields * (2 * vcp::kNW + 3) * 64 * vx * esz};
 }
 
 hipError_t launch_varcoef_pipe(int dtype, int vx, bool adjoint, const VarcoefArgs& a, hipStream_t s) {
