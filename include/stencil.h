@@ -141,8 +141,9 @@ typedef struct {
  *   storage  ST_F64 computes in FP64; ST_F32 and ST_BF16 compute in FP32
  *            (ST_BF16 rounds every step's result to bfloat16, ties to even).
  *   flags    ST_PLAN_* bits.  With ST_PLAN_AUTOTUNE the call allocates two
- *            scratch grids, times every candidate on the current device and
- *            keeps the fastest; without it a fixed heuristic is used.  With
+ *            scratch grids, times every candidate on the current device, and
+ *            register tiles or bricks where the grid takes them, and keeps the
+ *            fastest; without it a time model chooses.  With
  *            ST_PLAN_GRAPH, stencil_run captures its passes into a HIP graph
  *            (on a plan-owned stream) the first time it sees a set of
  *            arguments (grid, work, steps, weights, candidate) and afterwards
@@ -162,7 +163,9 @@ st_status stencil_plan(st_plan* out, const st_pattern* pattern, const int64_t* s
  * shape or shapes, point offsets -- and takes the stored candidate without
  * timing anything; otherwise it times the candidates and stores its choice.
  * The in-memory table lives as long as the library.
- *   path  text file, one "key<TAB>candidate<TAB>candidates" line per plan:
+ *   path  text file, one "key<TAB>candidate<TAB>candidates" line per plan (the
+ *         key of a plan that runs in register tiles ends in " tile", their
+ *         columns a lane and depth):
  *         read now when it exists (its entries join the table) and rewritten
  *         after every new tuning (a file that cannot be written is left as
  *         it is: the cache is advisory).  NULL stops writing a file.

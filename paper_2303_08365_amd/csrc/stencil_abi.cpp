@@ -1553,21 +1553,41 @@ std::string tune_key(const st_plan_s* p) {
     return k;
 }
 
+// Register tiles that won are named by the end of the key, " tile COLUMNS DEPTH";
+// the candidate of such a line is the best of the list.
+constexpr char kTuneTile[] = " tile ";
+
 bool tune_lookup(st_plan_s* p, const std::string& key) {
     std::lock_guard<std::mutex> lock(g_tune_mu);
     auto it = g_tune.find(key);
-    if (it == g_tune.end()) return false;
+    Candidate tile;
+    if (it == g_tune.end()) {
+        const std::string start = key + kTuneTile;
+        it = g_tune.lower_bound(start);
+        int vx = 0, t = 0;
+        if (it == g_tune.end() || it->first.compare(0, start.size(), start) != 0 ||
+            std::sscanf(it->first.c_str() + start.size(), "%d %d", &vx, &t) != 2 || vx < 1 || t < 1 ||
+            register_select(p, tile, vx, t) >= 1e300)
+            return false;
+    }
     const int idx = it->second.first, n = it->second.second;
     if (n != static_cast<int>(p->cands.size()) || idx < 0 || idx >= n) return false;
     p->sel = idx;
     p->modelled = false;
-    p->stand_in = kNoStandIn;
+    p->stand_in = tile.k2.vx > 0 ? kTiles : kNoStandIn;
+    p->tile = tile;
     return true;
 }
 
-void tune_store(const std::string& key, int idx, int n) {
+void tune_store(const std::string& key, const st_plan_s* p) {
     std::lock_guard<std::mutex> lock(g_tune_mu);
-    g_tune[key] = {idx, n};
+    const std::string start = key + kTuneTile;
+    g_tune.erase(key);
+    for (auto it = g_tune.lower_bound(start); it != g_tune.end() && it->first.compare(0, start.size(), start) == 0;)
+        it = g_tune.erase(it);
+    const std::string full =
+        p->stand_in == kTiles ? start + std::to_string(p->tile.k2.vx) + " " + std::to_string(p->tile.tb) : key;
+    g_tune[full] = {p->sel, static_cast<int>(p->cands.size())};
     if (g_tune_path.empty()) return;
     // the cache is advisory: a file that cannot be written is left as it is
     FILE* f = std::fopen(g_tune_path.c_str(), "w");
@@ -1596,20 +1616,39 @@ st_status autotune(st_plan_s* p) {
     hipEventCreate(&e1);
     double best = 1e300;
     int best_i = p->sel;
-    for (size_t i = 0; i < p->cands.size(); ++i) {
-        const Candidate& c = p->cands[i];
+    // ms a step of candidate c
+    const auto measure = [&](const Candidate& c) {
         const int64_t steps = std::max<int64_t>(8, 4 * c.tb);
-        if (run_steps(p, c, a, b, w, steps, nullptr) != ST_OK) continue;  // warm-up
+        if (run_steps(p, c, a, b, w, steps, nullptr) != ST_OK) return 1e300;  // warm-up
         hipEventRecord(e0, nullptr);
         st_status r = ST_OK;
         for (int rep = 0; rep < 3 && r == ST_OK; ++rep) r = run_steps(p, c, a, b, w, steps, nullptr);
         hipEventRecord(e1, nullptr);
         hipEventSynchronize(e1);
-        if (r != ST_OK) continue;
+        if (r != ST_OK) return 1e300;
         float ms = 0.f;
         hipEventElapsedTime(&ms, e0, e1);
-        const double per_step = ms / (3.0 * steps);
-        if (per_step < best) { best = per_step; best_i = static_cast<int>(i); }
+        return ms / (3.0 * steps);
+    };
+    for (size_t i = 0; i < p->cands.size(); ++i)
+        if (const double ms = measure(p->cands[i]); ms < best) {
+            best = ms;
+            best_i = static_cast<int>(i);
+        }
+    // Register tiles and bricks, where their model comes within twice that: for
+    // each lane width its depth and those around (the model is 12 % off at most).
+    bool tiles = false;
+    for (int vx : {1, 2, 4}) {
+        Candidate c;
+        if (register_select(p, c, vx) >= 2e3 * best) continue;
+        const int model_t = c.tb;
+        for (int t = std::max(1, model_t - 4); t <= model_t + 4; ++t)
+            if (register_select(p, c, vx, t) < 1e300)
+                if (const double ms = measure(c); ms < best) {
+                    best = ms;
+                    p->tile = c;
+                    tiles = true;
+                }
     }
     hipEventDestroy(e0);
     hipEventDestroy(e1);
@@ -1617,8 +1656,8 @@ st_status autotune(st_plan_s* p) {
     hipFree(b);
     p->sel = best_i;
     p->modelled = false;
-    p->stand_in = kNoStandIn;
-    tune_store(tkey, best_i, static_cast<int>(p->cands.size()));
+    p->stand_in = tiles ? kTiles : kNoStandIn;
+    tune_store(tkey, p);
     g_last_error.clear();
     return ST_OK;
 }
@@ -2422,7 +2461,7 @@ st_status batch_autotune(st_plan_s* p) {
         p->stand_in = kNoStandIn;
         p->table_shadow.clear();
         p->flags = flags;
-        tune_store(tkey, best_i, static_cast<int>(p->cands.size()));
+        tune_store(tkey, p);
         g_last_error.clear();
     }
     hipDeviceSynchronize();

@@ -157,3 +157,61 @@ def test_small_grids_run_in_register_tiles(dtype):
             for bc in ("zero", "periodic"):
                 ran = st.Plan(synth.star_offsets(3, 1), shape, dtype, bc).launches()
                 assert ran["kernel"] == st.KERNEL_BRICK3D, (shape, bc, ran)
+
+
+# asking for autotuning must not give less than not asking: small grids keep the
+# register tiles (twice the speed of the next tiling here), in the cache file too
+@pytest.mark.parametrize("shape,kernel", [((512, 512), 6), ((64, 64, 64), 7)])
+def test_autotuning_knows_the_register_tiles(tmp_path, shape, kernel):
+    import paper_2303_08365_amd as st
+    path = tmp_path / "tune.txt"
+    offs, w, u0 = synth.star_offsets(len(shape), 1), synth.heat_weights(len(shape), 0.15, "f32"), synth.uniform_field(shape, seed=97)
+    st.autotune_cache(str(path))
+    try:
+        tuned = st.Plan(offs, shape, "f32", autotune=True)
+        print(f"autotuned {shape}: {tuned.launches()}", flush=True)
+        assert tuned.launches()["kernel"] == kernel
+        where = " grid " + "x".join(str(n) for n in (1,) * (3 - len(shape)) + shape) + " "
+        line, = [ln for ln in path.read_text().splitlines() if where in ln and " t1 " in ln]
+        key, idx, n = line.split("\t")
+        base, tile = key.split(" tile ")
+        assert [int(v) for v in tile.split()] == [tuned.launches()["pipeline"], tuned.launches()["tb"]]
+        again = st.Plan(offs, shape, "f32", autotune=True)
+        assert again.launches() == tuned.launches() and again.info() == tuned.info()
+        naive = st.Plan(offs, shape, "f32", naive=True)
+        want, _ = gpu_sweep(u0, offs, w, 25, "zero", "f32", plan=naive)
+        for plan in (tuned, again):
+            got, _ = gpu_sweep(u0, offs, w, 25, "zero", "f32", plan=plan)
+            assert np.array_equal(got, want)
+    finally:
+        st.autotune_cache(None)
+
+
+# stored choices of register tiles are taken as they are; ones that no instance
+# can run are tuned anew
+def test_autotune_cache_names_register_tiles(tmp_path):
+    import paper_2303_08365_amd as st
+    path, offs, shape = tmp_path / "tune.txt", synth.star_offsets(2, 1), (130, 257)
+    st.autotune_cache(str(path))
+    try:
+        st.Plan(offs, shape, "f32", autotune=True)
+        line, = [ln for ln in path.read_text().splitlines() if " grid 1x130x257 " in ln and " t1 " in ln]
+        base, n = line.split("\t")[0].split(" tile ")[0], line.split("\t")[2]
+        path.write_text(f"{base} tile 1 7\t2\t{n}\n")
+        # a fresh table: what this process has tuned would come first
+        import subprocess
+        import sys
+        code = (f"import sys; sys.path[:0] = {sys.path!r}\nimport synth, paper_2303_08365_amd as st\nst.autotune_cache({str(path)!r})\n"
+                f"p = st.Plan(synth.star_offsets(2, 1), {shape}, 'f32', autotune=True); r = p.launches()\n"
+                "print(r['kernel'], r['pipeline'], r['tb'], p.info()['variant'])")
+        got = []
+        for entry in ("tile 1 7", "tile 1 99", "tile 3 7", "tile x"):
+            path.write_text(f"{base} {entry}\t2\t{n}\n")
+            out = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=100)
+            assert out.returncode == 0, out.stderr[-2000:]
+            got.append(out.stdout.split()[-4:])
+        print(f"from the file: {got}", flush=True)
+        assert got[0] == ["6", "1", "7", "2"]
+        assert all(g[:1] == ["6"] and g[1] in ("1", "2") and int(g[2]) < 32 for g in got[1:])
+    finally:
+        st.autotune_cache(None)
