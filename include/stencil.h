@@ -158,9 +158,9 @@ st_status stencil_plan(st_plan* out, const st_pattern* pattern, const int64_t* s
 /*
  * stencil_autotune_cache -- remember autotuning results (paper Sec. 5.2: the
  * scheduler's choice comes from a profile of the problem, taken once).  Every
- * ST_PLAN_AUTOTUNE plan (single or batch) first looks its key up -- device
- * (architecture and compute-unit count), dimensions, storage type, boundary,
- * shape or shapes, point offsets -- and takes the stored candidate without
+ * ST_PLAN_AUTOTUNE plan (single or batch) first looks its key up -- candidate
+ * list, device (architecture and compute-unit count), dimensions, storage type,
+ * boundary, shape or shapes, point offsets -- and takes the stored candidate without
  * timing anything; otherwise it times the candidates and stores its choice.
  * The in-memory table lives as long as the library.
  *   path  text file, one "key<TAB>candidate<TAB>candidates" line per plan (the

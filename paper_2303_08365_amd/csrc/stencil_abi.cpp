@@ -1533,13 +1533,29 @@ std::mutex g_tune_mu;
 std::map<std::string, std::pair<int, int>> g_tune;
 std::string g_tune_path;
 
+// A candidate's number means something within one list only: the key names the
+// list (a hash of its tilings in order, FNV-1a), so that a file written by a
+// library with another one is not taken for this one's.
+std::string list_name(const st_plan_s* p) {
+    uint64_t h = 14695981039346656037ull;
+    const auto add = [&](int32_t v) { h = (h ^ static_cast<uint32_t>(v)) * 1099511628211ull; };
+    for (const Candidate& c : p->cands) {
+        for (int32_t v : {c.kernel, c.tb, c.chunk, c.bpipe, c.k2.tbmax, c.k2.vx, c.k2.tess, c.k3.tbmax, c.k3.vx, c.k3.k,
+                          c.k3.nw, c.k3.late, c.k3.ylds, c.k3.pipe})
+            add(v);
+    }
+    char buf[20];
+    std::snprintf(buf, sizeof(buf), "%016llx", static_cast<unsigned long long>(h));
+    return buf;
+}
+
 std::string tune_key(const st_plan_s* p) {
     int dev = 0;
     hipDeviceProp_t prop;
     std::string devname = "?";
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
         devname = std::string(prop.gcnArchName) + ":" + std::to_string(prop.multiProcessorCount);
-    std::string k = "v1 " + devname + " nd" + std::to_string(p->ndim) + " t" + std::to_string(p->dtype) + " bc" +
+    std::string k = "v2 " + list_name(p) + " " + devname + " nd" + std::to_string(p->ndim) + " t" + std::to_string(p->dtype) + " bc" +
                     std::to_string(p->bc) + (p->batch ? " batch" : " grid");
     if (p->batch) {
         for (const BatchGrid& g : p->grids) k += " " + std::to_string(g.ny) + "x" + std::to_string(g.nx);

@@ -215,3 +215,31 @@ def test_autotune_cache_names_register_tiles(tmp_path):
         assert all(g[:1] == ["6"] and g[1] in ("1", "2") and int(g[2]) < 32 for g in got[1:])
     finally:
         st.autotune_cache(None)
+
+
+# a number from another library's candidate list means another tiling: lines of
+# the format before, and of another list with as many entries, are not taken
+def test_autotune_cache_of_another_list_is_not_taken(tmp_path):
+    import paper_2303_08365_amd as st
+    path, offs, shape = tmp_path / "tune.txt", synth.star_offsets(1, 1), (30011,)
+    st.autotune_cache(str(path))
+    try:
+        tuned = st.Plan(offs, shape, "f64", autotune=True)
+        line, = [ln for ln in path.read_text().splitlines() if " grid 1x1x30011 " in ln]
+        key, idx, n = line.split("\t")
+        version, listed, rest = key.split(" ", 2)
+        assert version == "v2" and len(listed) == 16 and int(n) == tuned.info()["ncandidates"]
+        st.Plan(offs, (30012,), "f64", autotune=True)  # the same list: the same name
+        assert any(ln.startswith(f"v2 {listed} ") and " grid 1x1x30012 " in ln for ln in path.read_text().splitlines())
+        # shape 30013 is not in the table: only what the file says could be taken
+        other = rest.replace("1x1x30011", "1x1x30013")
+        wrong = int(n) - 1  # one step per launch: the slowest by far
+        path.write_text(f"v1 {other}\t{wrong}\t{n}\nv2 {listed[::-1]} {other}\t{wrong}\t{n}\n")
+        st.autotune_cache(str(path))
+        assert st.Plan(offs, (30013,), "f64", autotune=True).info()["kernel"] == st.KERNEL_STREAM1D
+        other = rest.replace("1x1x30011", "1x1x30014")
+        path.write_text(f"v2 {listed} {other}\t{wrong}\t{n}\n")
+        st.autotune_cache(str(path))
+        assert st.Plan(offs, (30014,), "f64", autotune=True).info()["variant"] == wrong
+    finally:
+        st.autotune_cache(None)
