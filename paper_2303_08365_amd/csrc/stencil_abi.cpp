@@ -147,8 +147,6 @@ int elem_bytes(int dtype) { return dtype == kF64 ? 8 : (dtype == kF32 ? 4 : 2); 
 // ---------------------------------------------------------------------------
 namespace {
 
-enum StandIn { kNoStandIn, kOneStep, kTiles };
-
 // One tiling candidate of a plan.
 struct Candidate {
     int32_t kernel = ST_KERNEL_NAIVE;
@@ -185,10 +183,11 @@ struct st_plan_s {
     // autotuner's or the environment's)
     bool modelled = false;
     // what runs instead of the selected candidate: one step per launch where the
-    // model finds the grid too small for the list's tilings, register tiles or
-    // bricks (in no plan's list) where the model or the caller puts them first
-    int stand_in = kNoStandIn;
-    Candidate tile;  // kTiles: its kernel, depth and columns a lane (k2.vx)
+    // model finds the grid too small for the list's tilings; before both, in the
+    // calls that they take, register tiles or bricks (in no plan's list) where
+    // the model, the autotuner or the caller puts them first
+    bool one_step = false, tiles = false;
+    Candidate tile;  // tiles: their kernel, depth and columns a lane (k2.vx)
     // Device memory a plan owns is allocated when the plan is made (see
     // plan_buffers), never by a run call.
     void* owned_work = nullptr;   // ST_PLAN_OWN_WORK
@@ -767,8 +766,7 @@ double register_select(const st_plan_s* p, Candidate& tile, int only_vx = 0, int
 // with a model chunk, and whether one step per launch or tiles in registers beat it.
 void model_select(st_plan_s* p, bool fixed) {
     p->sel = 0;
-    p->modelled = false;
-    p->stand_in = kNoStandIn;
+    p->modelled = p->one_step = p->tiles = false;
     if (fixed || p->cands.size() <= 1) return;
     p->modelled = true;
     double best = 1e300;
@@ -791,15 +789,21 @@ void model_select(st_plan_s* p, bool fixed) {
     if (p->batch) return;
     if (step_us(p, p->cands.back()) < 0.9 * best) {
         best = step_us(p, p->cands.back());
-        p->stand_in = kOneStep;
+        p->one_step = true;
     }
     // (radius 2 by a wider margin: its model is less exact where both are near)
     const double margin = p->ndim == 2 && p->radius == 2 ? 0.8 : 0.9;
-    if (register_select(p, p->tile) < margin * best) p->stand_in = kTiles;
+    p->tiles = register_select(p, p->tile) < margin * best;
 }
 
 // Default fused depth and lane width per family.
 int default_vx2(int dtype) { return dtype == kF64 ? 2 : 4; }
+
+// Candidate i, by the caller's, the autotuner's or the environment's choice.
+void select_listed(st_plan_s* p, int i) {
+    p->sel = i;
+    p->modelled = p->one_step = p->tiles = false;
+}
 
 void build_candidates(st_plan_s* p) {
     p->cands.clear();
@@ -995,18 +999,12 @@ void build_candidates(st_plan_s* p) {
     // environment overrides (testing and tuning): STENCIL_TB, STENCIL_VARIANT
     if (const char* v = std::getenv("STENCIL_VARIANT")) {
         const int i = std::atoi(v);
-        if (i >= 0 && i < static_cast<int>(p->cands.size())) {
-            p->sel = i;
-            p->modelled = false;
-            p->stand_in = kNoStandIn;
-        }
+        if (i >= 0 && i < static_cast<int>(p->cands.size())) select_listed(p, i);
     } else if (const char* t = std::getenv("STENCIL_TB")) {
         const int tb = std::atoi(t);
         for (size_t i = 0; i < p->cands.size(); ++i)
             if (p->cands[i].tb == tb) {
-                p->sel = static_cast<int>(i);
-                p->modelled = false;
-                p->stand_in = kNoStandIn;
+                select_listed(p, static_cast<int>(i));
                 break;
             }
     }
@@ -1371,16 +1369,15 @@ st_status check_flux_parts(const st_plan_s* p, int64_t need) {
     return ST_OK;
 }
 
-// What a run with candidate c_sel between these buffers launches.  A selection
-// may stand for one step per launch or for the register tiles (no outflow form).
-// The pipeline has whole-vector rows only: on a grid that does not take them
+// What a run with candidate c_sel between these buffers launches: register tiles
+// (no outflow form), one step per launch, or c_sel.  The pipeline has whole-vector rows only: on a grid that does not take them
 // (too small) the run uses the plan's first other candidate, with its own depth
 // (every candidate gives the same bits; the list always ends with the one-step
 // kernel).
-const Candidate& run_pick(const st_plan_s* p, const Candidate& c_sel, const void* grid, const void* work, bool flux,
-                          int stand_in) {
-    if (stand_in == kOneStep) return p->cands.back();
-    if (stand_in == kTiles && !flux && elem_aligned(grid, p->dtype) && elem_aligned(work, p->dtype)) return p->tile;
+const Candidate& run_pick(const st_plan_s* p, const Candidate& c_sel, const void* grid, const void* work, bool tiles,
+                          bool one_step) {
+    if (tiles && elem_aligned(grid, p->dtype) && elem_aligned(work, p->dtype)) return p->tile;
+    if (one_step) return p->cands.back();
     if (c_sel.kernel == ST_KERNEL_STREAM3D && c_sel.k3.pipe && !fast3(p, c_sel, c_sel.tb, grid, work))
         for (const Candidate& o : p->cands)
             if (!(o.kernel == ST_KERNEL_STREAM3D && o.k3.pipe)) return o;
@@ -1390,8 +1387,8 @@ const Candidate& run_pick(const st_plan_s* p, const Candidate& c_sel, const void
 // Run `steps` steps with candidate c: grid -> work -> grid ...  With `flux`
 // (zero rule only), the outflow of every step is also added to flux[0].
 st_status run_steps(st_plan_s* p, const Candidate& c_sel, void* grid, void* work, const double* wcan,
-                    int64_t steps, hipStream_t s, double* flux = nullptr, int stand_in = kNoStandIn) {
-    const Candidate& c_in = run_pick(p, c_sel, grid, work, flux != nullptr, stand_in);
+                    int64_t steps, hipStream_t s, double* flux = nullptr, bool tiles = false, bool one_step = false) {
+    const Candidate& c_in = run_pick(p, c_sel, grid, work, tiles, one_step);
     const bool elems = elem_aligned(grid, p->dtype) && elem_aligned(work, p->dtype);
     // the pipeline's outflow twin has whole-vector rows only
     const bool fused = flux && flux_fused(p, c_in) &&
@@ -1588,9 +1585,8 @@ bool tune_lookup(st_plan_s* p, const std::string& key) {
     }
     const int idx = it->second.first, n = it->second.second;
     if (n != static_cast<int>(p->cands.size()) || idx < 0 || idx >= n) return false;
-    p->sel = idx;
-    p->modelled = false;
-    p->stand_in = tile.k2.vx > 0 ? kTiles : kNoStandIn;
+    select_listed(p, idx);
+    p->tiles = tile.k2.vx > 0;
     p->tile = tile;
     return true;
 }
@@ -1602,7 +1598,7 @@ void tune_store(const std::string& key, const st_plan_s* p) {
     for (auto it = g_tune.lower_bound(start); it != g_tune.end() && it->first.compare(0, start.size(), start) == 0;)
         it = g_tune.erase(it);
     const std::string full =
-        p->stand_in == kTiles ? start + std::to_string(p->tile.k2.vx) + " " + std::to_string(p->tile.tb) : key;
+        p->tiles ? start + std::to_string(p->tile.k2.vx) + " " + std::to_string(p->tile.tb) : key;
     g_tune[full] = {p->sel, static_cast<int>(p->cands.size())};
     if (g_tune_path.empty()) return;
     // the cache is advisory: a file that cannot be written is left as it is
@@ -1670,19 +1666,18 @@ st_status autotune(st_plan_s* p) {
     hipEventDestroy(e1);
     hipFree(a);
     hipFree(b);
-    p->sel = best_i;
-    p->modelled = false;
-    p->stand_in = tiles ? kTiles : kNoStandIn;
+    select_listed(p, best_i);
+    p->tiles = tiles;
     tune_store(tkey, p);
     g_last_error.clear();
     return ST_OK;
 }
 
-// The candidate of an outflow run; stand_in gets what runs instead of it.
-const Candidate& flux_choice(const st_plan_s* plan, int& stand_in) {
+// The candidate of a zero-rule outflow run; one_step: one step per launch instead of it.
+const Candidate& flux_choice(const st_plan_s* plan, bool& one_step) {
     const Candidate* cand = &plan->cands[plan->sel];
-    stand_in = plan->stand_in == kOneStep ? kOneStep : kNoStandIn;
-    if (plan->modelled && plan->bc == kZero) {
+    one_step = plan->one_step;
+    if (plan->modelled) {
         // a launch more per pass where the kernel sums the outflow, two more
         // per step where it does not (about 4 us each): the fastest of the
         // model's candidates under that account
@@ -1690,19 +1685,19 @@ const Candidate& flux_choice(const st_plan_s* plan, int& stand_in) {
             if (alone || !flux_fused(plan, c)) return (alone ? step_us(plan, plan->cands.back()) : step_us(plan, c) * c.tb) + 8.0;
             return step_us(plan, c) + 4.0 / c.tb;
         };
-        double best = account(*cand, stand_in == kOneStep);
+        double best = account(*cand, one_step);
         for (const Candidate& c : plan->cands)
             if (c.chunk == plan->cands[0].chunk && c.kernel != ST_KERNEL_NAIVE && flux_fused(plan, c))
                 if (const double us = account(c, false); us < 0.97 * best) {
                     best = us;
                     cand = &c;
-                    stand_in = kNoStandIn;
+                    one_step = false;
                 }
     }
     // a fused candidate of the same depth with an outflow-summing twin
     // stands in for one without (same states bit for bit: every tiling of a
     // plan gives the same grid)
-    if (stand_in == kNoStandIn && cand->kernel == ST_KERNEL_STREAM3D && !flux_fused(plan, *cand))
+    if (!one_step && cand->kernel == ST_KERNEL_STREAM3D && !flux_fused(plan, *cand))
         for (const Candidate& c : plan->cands)
             if (c.kernel == cand->kernel && c.tb == cand->tb && flux_fused(plan, c)) return c;
     return *cand;
@@ -1910,10 +1905,10 @@ st_status stencil_plan_launches(st_plan plan, int32_t call, st_plan_info* info) 
     }
     const Candidate* c = &plan->cands[plan->sel];
     if (!plan->batch) {
+        bool one_step = plan->one_step;
         const bool flux = call == ST_CALL_FLUX && plan->bc == kZero;
-        int stand_in = plan->stand_in;
-        if (call == ST_CALL_FLUX) c = &flux_choice(plan, stand_in);
-        c = &run_pick(plan, *c, nullptr, nullptr, flux, stand_in);
+        if (flux) c = &flux_choice(plan, one_step);
+        c = &run_pick(plan, *c, nullptr, nullptr, !flux && plan->tiles, one_step);
     }
     const int index = c == &plan->tile ? -1 : static_cast<int>(c - plan->cands.data());
     describe(plan, *c, index, info);
@@ -1929,7 +1924,7 @@ st_status stencil_plan_select(st_plan plan, int32_t kernel, int32_t tb, int32_t 
             return fail(ST_ERR_UNSUPPORTED, "no register tiles of kernel %d, depth %d and %d columns a lane", kernel, tb,
                         variant);
         plan->tile = tile;
-        plan->stand_in = kTiles;
+        plan->tiles = true;
         return ST_OK;
     }
     if (variant >= 0) {
@@ -1937,17 +1932,13 @@ st_status stencil_plan_select(st_plan plan, int32_t kernel, int32_t tb, int32_t 
         const Candidate& c = plan->cands[variant];
         if ((kernel >= 0 && c.kernel != kernel) || (tb > 0 && c.tb != tb))
             return fail(ST_ERR_UNSUPPORTED, "candidate %d is kernel %d depth %d", variant, c.kernel, c.tb);
-        plan->sel = variant;
-        plan->modelled = false;
-        plan->stand_in = kNoStandIn;
+        select_listed(plan, variant);
         return ST_OK;
     }
     for (int i = 0; i < n; ++i) {
         const Candidate& c = plan->cands[i];
         if ((kernel < 0 || c.kernel == kernel) && (tb <= 0 || c.tb == tb)) {
-            plan->sel = i;
-            plan->modelled = false;
-            plan->stand_in = kNoStandIn;
+            select_listed(plan, i);
             return ST_OK;
         }
     }
@@ -1966,13 +1957,13 @@ st_status stencil_run(st_plan plan, void* grid, void* work, const double* coeffs
         key_push(key, grid);
         key_push(key, work);
         key_push(key, steps);
-        key_push(key, static_cast<int64_t>(plan->sel) * 3 + plan->stand_in);
+        key_push(key, static_cast<int64_t>(plan->sel) * 4 + plan->one_step * 2 + plan->tiles);
         key_push(key, static_cast<int64_t>(plan->tile.tb) * 8 + plan->tile.k2.vx);
         for (int i = 0; i < plan->npoints; ++i) key_push(key, wcan[i]);
     }
     const Candidate cand = plan->cands[plan->sel];
     return run_graphed(plan, key, s, [&](hipStream_t st) {
-        return run_steps(plan, cand, grid, work, wcan, steps, st, nullptr, plan->stand_in);
+        return run_steps(plan, cand, grid, work, wcan, steps, st, nullptr, plan->tiles, plan->one_step);
     });
 }
 
@@ -1992,7 +1983,7 @@ st_status stencil_run_noalloc(st_plan plan, void* grid, const double* coeffs, co
         return r;
     // eager launches whatever the plan's flags (no graph is instantiated
     // here); inside a caller's capture they are recorded into its graph
-    return run_steps(plan, plan->cands[plan->sel], grid, work, wcan, steps, s, nullptr, plan->stand_in);
+    return run_steps(plan, plan->cands[plan->sel], grid, work, wcan, steps, s, nullptr, plan->tiles, plan->one_step);
 }
 
 st_status stencil_run_flux(st_plan plan, void* grid, void* work, const double* coeffs, const int64_t* shape,
@@ -2003,10 +1994,12 @@ st_status stencil_run_flux(st_plan plan, void* grid, void* work, const double* c
     bool nothing = false;
     if (st_status r = prepare_run(plan, grid, work, coeffs, shape, steps, bc, s, wcan, nothing); r != ST_OK || nothing)
         return r;
-    int stand_in = kNoStandIn;
-    const Candidate& cand = flux_choice(plan, stand_in);
     // a periodic grid has no boundary: nothing leaves
-    return run_steps(plan, cand, grid, work, wcan, steps, s, plan->bc == kZero ? flux : nullptr, stand_in);
+    if (plan->bc != kZero)
+        return run_steps(plan, plan->cands[plan->sel], grid, work, wcan, steps, s, nullptr, plan->tiles, plan->one_step);
+    bool one_step = false;
+    const Candidate& cand = flux_choice(plan, one_step);
+    return run_steps(plan, cand, grid, work, wcan, steps, s, flux, false, one_step);
 }
 
 }  // extern "C"
@@ -2472,9 +2465,7 @@ st_status batch_autotune(st_plan_s* p) {
         }
         hipEventDestroy(e0);
         hipEventDestroy(e1);
-        p->sel = best_i;
-        p->modelled = false;
-        p->stand_in = kNoStandIn;
+        select_listed(p, best_i);
         p->table_shadow.clear();
         p->flags = flags;
         tune_store(tkey, p);

@@ -3,6 +3,11 @@ sources have to keep."""
 import os
 import re
 
+import pytest
+
+import paper_2303_08365_amd as st
+import synth
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2303_08365_amd", "csrc")
 
@@ -23,3 +28,16 @@ def test_1d_strips_order_their_lds_accesses():
             last = op
         elif op == "order":
             last = "order"
+
+
+# no heat leaves a periodic grid: an outflow run launches what a plain run does,
+# register tiles and bricks and one step per launch included
+@pytest.mark.parametrize("dtype", ["f64", "f32", "bf16"])
+@pytest.mark.parametrize("pattern,shape", [(synth.star_offsets, (100, 256)), (synth.box_offsets, (66, 64)), (synth.star_offsets, (9, 9)),
+                                           (synth.star_offsets, (32, 32, 64)), (synth.star_offsets, (12, 13, 14)),
+                                           (synth.star_offsets, (89, 97, 101)), (synth.star_offsets, (512, 512, 512))])
+def test_periodic_outflow_runs_launch_what_plain_runs_do(dtype, pattern, shape):
+    plan = st.Plan(pattern(len(shape), 1), shape, dtype, "periodic")
+    assert plan.launches("flux") == plan.launches("run")
+    plan.select(variant=1)
+    assert plan.launches("flux") == plan.launches("run")
