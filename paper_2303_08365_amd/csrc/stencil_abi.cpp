@@ -988,14 +988,15 @@ void build_candidates(st_plan_s* p) {
         }
     }
     // STENCIL_CHUNK: fixed chunk length along the streamed axis (tuning)
-    if (const char* ch = std::getenv("STENCIL_CHUNK")) {
-        const int v = std::atoi(ch);
-        if (v > 0)
-            for (Candidate& c : fast) c.chunk = v;
-    }
+    int chunk = 0;
+    if (const char* ch = std::getenv("STENCIL_CHUNK")) chunk = std::atoi(ch);
+    if (chunk > 0)
+        for (Candidate& c : fast) c.chunk = chunk;
     p->cands = fast;
     p->cands.push_back(naive);
     model_select(p, force_naive);
+    // (the streaming kernels are asked for: no others instead of them)
+    if (chunk > 0) p->one_step = p->tiles = false;
     // environment overrides (testing and tuning): STENCIL_TB, STENCIL_VARIANT
     if (const char* v = std::getenv("STENCIL_VARIANT")) {
         const int i = std::atoi(v);

@@ -41,3 +41,13 @@ def test_periodic_outflow_runs_launch_what_plain_runs_do(dtype, pattern, shape):
     assert plan.launches("flux") == plan.launches("run")
     plan.select(variant=1)
     assert plan.launches("flux") == plan.launches("run")
+
+
+# a chunk length asked for by the environment is what runs, on small grids too
+@pytest.mark.parametrize("shape,kernel,axis", [((512, 512), st.KERNEL_STREAM2D, "tile_y"), ((64, 64, 64), st.KERNEL_STREAM3D, "tile_z"),
+                                               ((20, 40, 70), st.KERNEL_STREAM3D, "tile_z")])
+def test_chunk_length_from_the_environment_runs(monkeypatch, shape, kernel, axis):
+    monkeypatch.setenv("STENCIL_CHUNK", "16")
+    for dtype in ("f64", "f32", "bf16"):
+        ran = st.Plan(synth.star_offsets(len(shape), 1), shape, dtype).launches()
+        assert ran["kernel"] == kernel and ran[axis] == 16, (dtype, ran)
