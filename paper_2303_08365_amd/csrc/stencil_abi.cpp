@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <array>
 #include <chrono>
 #include <cmath>
@@ -12,6 +13,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -157,7 +159,11 @@ struct Candidate {
     int32_t occ = 0;    // resident work-groups per CU (0 = unknown: assume 2)
     int32_t bpipe = 0;  // ST_KERNEL_BOX3D, two steps: 0 = box3d_kernel, v + 1 = boxpipe3d variant v
     int32_t auto_chunk = 0;  // the time model's chunk at depth tb (chunk == 0; 0: not asked yet)
+    // the same for passes of other depths, [1 .. kDepths]: asked by the first run
+    // that needs it (0: not yet) and kept by the plan
+    std::atomic<int32_t>* tails = nullptr;
 };
+constexpr int kDepths = 8;
 
 struct BatchGrid {
     int64_t ny, nx;
@@ -188,6 +194,7 @@ struct st_plan_s {
     // the model, the autotuner or the caller puts them first
     bool one_step = false, tiles = false;
     Candidate tile;  // tiles: their kernel, depth and columns a lane (k2.vx)
+    std::unique_ptr<std::atomic<int32_t>[]> tails;  // the candidates' `tails`
     // Device memory a plan owns is allocated when the plan is made (see
     // plan_buffers), never by a run call.
     void* owned_work = nullptr;   // ST_PLAN_OWN_WORK
@@ -195,6 +202,7 @@ struct st_plan_s {
     // work-group), sized for the largest pass of any candidate
     double* flux_part = nullptr;
     int64_t flux_cap = 0;
+    int32_t flux_shortest = 0;  // the shortest chunks that flux_cap allows for
     // tessellated 2D candidates: the band scratch, sized for the largest pass
     void* tess_buf = nullptr;
     int64_t tess_cap = 0;
@@ -288,8 +296,18 @@ double bytes_us(double bytes, double tbs, double enough, double power, double gr
 // Where the two come near each other both are felt.
 double both_us(double a, double b) { return std::sqrt(std::sqrt(a * a * a * a + b * b * b * b)); }
 
+// A pass: `launch`, and the walk's and the bytes' times together; no better than
+// `limit` (then 1e300) already where the walk alone, or the bytes at full
+// bandwidth, reach it: most chunk lengths of a search need no power or root.
+template <typename F>
+double pass_us(double launch, double walk, double bytes, double tbs, double limit, const F& loaded) {
+    if (launch + walk >= limit || launch + bytes / (tbs * 1e6) >= limit) return 1e300;
+    return launch + both_us(walk, loaded());
+}
+
 // The chunk length (extent n, at least `least`) that the model finds fastest; a
 // shorter one has to be 2 % better (well inside the model's error).
+// us(chunk, limit): the model's time, or 1e300 where it is at least limit.
 template <typename F>
 int64_t best_chunk(int64_t n, int64_t least, const F& us) {
     int64_t best = n, last = 0;
@@ -299,7 +317,7 @@ int64_t best_chunk(int64_t n, int64_t least, const F& us) {
         if (chunk < least && c > 1) break;
         if (chunk == last) continue;
         last = chunk;
-        const double v = us(chunk);
+        const double v = us(chunk, best_us * 0.98);
         if (v < best_us * 0.98) {
             best_us = v;
             best = chunk;
@@ -308,24 +326,39 @@ int64_t best_chunk(int64_t n, int64_t least, const F& us) {
     return best;
 }
 
+// The model's chunk length for a pass of depth tb != c.tb; `keep`: of the tiling
+// that passes between element-aligned buffers have.
+template <typename F>
+int64_t depth_chunk(const Candidate& c, int tb, bool keep, const F& search) {
+    std::atomic<int32_t>* kept = keep && c.tails && tb >= 1 && tb <= kDepths ? &c.tails[tb] : nullptr;
+    if (kept)
+        if (const int32_t v = kept->load(std::memory_order_relaxed); v > 0) return v;
+    const int64_t v = search();
+    if (kept) kept->store(static_cast<int32_t>(v), std::memory_order_relaxed);
+    return v;
+}
+
 // 2D rows (4 waves a work-group, one per SIMD): `items` strips x chunks of at
 // most `nit` rows, `streamed` cells read and `cells` written.
-double rows_us(const Candidate& c, int tb, int64_t items, int64_t nit, double streamed, double cells) {
+double rows_us(const Candidate& c, int tb, int64_t items, int64_t nit, double streamed, double cells, double limit = 1e300) {
     const int vx = c.k2.vx, R = c.k2.radius, dw = c.k2.dtype == kF64 ? 2 : 1;
     const int points = c.k2.cls == kStar ? 4 * R + 1 : (2 * R + 1) * (2 * R + 1);
     const double us = kUsPerInstr * (tb * (vx * points + 2 * R * dw) + 12);
     const double rnd = c.k2.dtype == kBF16 ? kUsPerInstr * tb * 2 * vx : 0.0;  // bfloat16 rounds every level
     const double groups = static_cast<double>(ceil_div(items, 4));
     const int occ = c.occ > 0 ? c.occ : 2;
-    return 4.0 + both_us(walk_us(groups, occ, static_cast<double>(nit), 0.075 + 1.18 * (us + 2 * rnd), 1.08 * (us + rnd)),
-                         bytes_us(elem_bytes(c.k2.dtype) * (streamed + cells), 5.2, 3.0, 0.3, groups, occ, 4));
+    const double bytes = elem_bytes(c.k2.dtype) * (streamed + cells);
+    return pass_us(4.0, walk_us(groups, occ, static_cast<double>(nit), 0.075 + 1.18 * (us + 2 * rnd), 1.08 * (us + rnd)), bytes, 5.2,
+                   limit, [&] { return bytes_us(bytes, 5.2, 3.0, 0.3, groups, occ, 4); });
 }
 
 // 3D planes: a pass over `grid` bytes in chunks of `chunk` planes, `nit` with
 // the halo (the tiles' xy halos come from L2).
 double planes_us(double launch, double tbs, double groups, int occ, int waves, double nit, double chunk, double lat, double thr,
-                 double grid) {
-    return launch + both_us(walk_us(groups, occ, nit, lat, thr), bytes_us(grid * (nit / chunk + 1.0), tbs, 2.0, 0.2, groups, occ, waves));
+                 double grid, double limit) {
+    const double bytes = grid * (nit / chunk + 1.0);
+    return pass_us(launch, walk_us(groups, occ, nit, lat, thr), bytes, tbs, limit,
+                   [&] { return bytes_us(bytes, tbs, 2.0, 0.2, groups, occ, waves); });
 }
 
 // Geometry of one 2D pass for a grid.
@@ -352,10 +385,11 @@ int32_t wrap_strip(int64_t nx, int32_t out_w, int32_t hxa, int vx) {
     return 0;
 }
 
-double rows2_us(const Candidate& c, int64_t ny, int64_t nx, int tb, int64_t tiles_x, int64_t chunk) {
+double rows2_us(const Candidate& c, int64_t ny, int64_t nx, int tb, int64_t tiles_x, int64_t chunk, double limit = 1e300) {
     const int64_t chunks = ceil_div(ny, chunk), halo = 2 * static_cast<int64_t>(c.k2.radius) * tb;
     return rows_us(c, tb, tiles_x * chunks, std::min(chunk, ny) + halo,
-                   static_cast<double>(nx) * static_cast<double>(ny + chunks * halo), static_cast<double>(nx) * static_cast<double>(ny));
+                   static_cast<double>(nx) * static_cast<double>(ny + chunks * halo), static_cast<double>(nx) * static_cast<double>(ny),
+                   limit);
 }
 
 // Tiles along an axis of n cells, `out` owned each.  Under the zero rule the
@@ -430,7 +464,9 @@ bool geo2(const Candidate& c, int64_t ny, int64_t nx, int tb, Geo2& g, int64_t c
     int64_t chunk = chunk_override > 0 ? chunk_override : c.chunk;
     if (chunk <= 0 && tb == c.tb) chunk = c.auto_chunk;
     if (chunk <= 0)
-        chunk = best_chunk(ny, 4, [&](int64_t len) { return rows2_us(c, ny, nx, tb, g.tiles_x, len); });
+        chunk = depth_chunk(c, tb, elems, [&] {
+            return best_chunk(ny, 4, [&](int64_t len, double limit) { return rows2_us(c, ny, nx, tb, g.tiles_x, len, limit); });
+        });
     chunk = std::min<int64_t>(chunk, ny);
     g.chunk_y = static_cast<int32_t>(chunk);
     g.chunks_y = static_cast<int32_t>(ceil_div(ny, chunk));
@@ -470,7 +506,7 @@ struct GeoB {
     bool vec;       // the tiles allow whole-vector rows (element-aligned buffers)
 };
 
-double box_us(const st_plan_s* p, const Candidate& c, int tb, int64_t per_plane, int64_t chunk) {
+double box_us(const st_plan_s* p, const Candidate& c, int tb, int64_t per_plane, int64_t chunk, double limit = 1e300) {
     const int64_t chunks = ceil_div(p->n[0], chunk);
     const double groups = static_cast<double>(per_plane) * static_cast<double>(chunks);
     const int dw = p->dtype == kF64 ? 2 : 1, esz = elem_bytes(p->dtype);
@@ -479,7 +515,7 @@ double box_us(const st_plan_s* p, const Candidate& c, int tb, int64_t per_plane,
         const BoxPipeShape sh = boxpipe3d_shape(p->dtype, c.bpipe - 1);
         const double us = kUsPerInstr * (2 * sh.k * sh.vx * (27 + (p->dtype == kBF16 ? 2 : 0)) + 4 * (sh.k + 2) * 2 * dw);
         return planes_us(3.7, 4.8, groups, 1, sh.block / 64, len + 5, len,
-                         (0.8 + (p->dtype == kF64 && sh.k == 4 ? 2.2 : 1.83) * us) * (p->dtype == kF64 ? 1.0 : 1.1), 0.0, grid);
+                         (0.8 + (p->dtype == kF64 && sh.k == 4 ? 2.2 : 1.83) * us) * (p->dtype == kF64 ? 1.0 : 1.1), 0.0, grid, limit);
     }
     const Box3DShape sh = box3d_shape(p->dtype, tb);
     const int waves = sh.block / 64, k = sh.h / waves;
@@ -488,7 +524,7 @@ double box_us(const st_plan_s* p, const Candidate& c, int tb, int64_t per_plane,
     // (two steps measured over the fit of one, FP64 well over it: registers)
     const double us = kUsPerInstr * (rows * sh.vx * (27 + (p->dtype == kBF16 ? 2 : 0)) + 6 * (k + 2 * tb) * dw * tb) *
                       (tb == 1 ? 1.0 : (p->dtype == kF64 ? 1.7 : 1.12));
-    return planes_us(7.0, 5.5, groups, tb == 1 ? 2 : 1, waves, len + 2 * tb, len, 0.54 + 1.42 * us, 1.22 * us * waves / 4, grid);
+    return planes_us(7.0, 5.5, groups, tb == 1 ? 2 : 1, waves, len + 2 * tb, len, 0.54 + 1.42 * us, 1.22 * us * waves / 4, grid, limit);
 }
 
 // 3D boxes: tiles of out_w x h owned cells (the register tile is 64*VX wide;
@@ -512,7 +548,7 @@ bool geob(const st_plan_s* p, const Candidate& c, int tb, GeoB& g) {
         const int64_t per_plane = static_cast<int64_t>(g.tiles_x) * g.tiles_y;
         int64_t chunk = c.chunk;
         if (chunk <= 0) chunk = c.auto_chunk;
-        if (chunk <= 0) chunk = best_chunk(n[0], 4, [&](int64_t len) { return box_us(p, c, tb, per_plane, len); });
+        if (chunk <= 0) chunk = best_chunk(n[0], 4, [&](int64_t len, double limit) { return box_us(p, c, tb, per_plane, len, limit); });
         chunk = std::min<int64_t>(chunk, n[0]);
         g.chunk_z = static_cast<int32_t>(chunk);
         g.chunks_z = static_cast<int32_t>(ceil_div(n[0], chunk));
@@ -534,14 +570,17 @@ bool geob(const st_plan_s* p, const Candidate& c, int tb, GeoB& g) {
     const int64_t per_plane = static_cast<int64_t>(g.tiles_x) * g.tiles_y;
     int64_t chunk = c.chunk;
     if (chunk <= 0 && tb == c.tb && c.bpipe == 0) chunk = c.auto_chunk;
-    if (chunk <= 0) chunk = best_chunk(n[0], 4, [&](int64_t len) { return box_us(p, c, tb, per_plane, len); });
+    if (chunk <= 0)
+        chunk = depth_chunk(c, tb, true, [&] {
+            return best_chunk(n[0], 4, [&](int64_t len, double limit) { return box_us(p, c, tb, per_plane, len, limit); });
+        });
     chunk = std::min<int64_t>(chunk, n[0]);
     g.chunk_z = static_cast<int32_t>(chunk);
     g.chunks_z = static_cast<int32_t>(ceil_div(n[0], chunk));
     return per_plane * g.chunks_z < (int64_t(1) << 31);
 }
 
-double star3_us(const Candidate& c, const int64_t n[3], int tb, int64_t per_plane, int64_t chunk, bool vec) {
+double star3_us(const Candidate& c, const int64_t n[3], int tb, int64_t per_plane, int64_t chunk, bool vec, double limit = 1e300) {
     const int R = c.k3.radius, K = c.k3.k, vx = c.k3.vx, dw = c.k3.dtype == kF64 ? 2 : 1, esz = elem_bytes(c.k3.dtype);
     const double groups = static_cast<double>(per_plane) * static_cast<double>(ceil_div(n[0], chunk));
     const double len = static_cast<double>(std::min(chunk, n[0])), nit = len + 2 * R * tb;
@@ -556,14 +595,14 @@ double star3_us(const Candidate& c, const int64_t n[3], int tb, int64_t per_plan
         double plane = 0.8 + 1.88 * us;
         if (c.k3.dtype == kF32 && vx == 4) plane = 0.3 + 2.4 * us;
         if (c.k3.dtype == kBF16 && K == 4 && c.k3.tbmax == 3) plane = (tb == 2 ? 0.45 : 0.2) + 2.1 * us;
-        return planes_us(3.9, 4.8, groups, 1, c.k3.nw, nit, len, plane, 0.0, grid);
+        return planes_us(3.9, 4.8, groups, 1, c.k3.nw, nit, len, plane, 0.0, grid, limit);
     }
     if (R > 1) {  // one step; the loads of the halo rows set the pace
         const double lat = c.k3.dtype == kF64 ? 1.85 : (c.k3.dtype == kF32 ? 1.5 : 1.35);
-        return planes_us(4.0, 5.4, groups, 1, c.k3.nw, nit, len, lat * (vec ? 1.0 : 1.2), 0.0, grid);
+        return planes_us(4.0, 5.4, groups, 1, c.k3.nw, nit, len, lat * (vec ? 1.0 : 1.2), 0.0, grid, limit);
     }
     return planes_us(7.7, 5.4, groups, c.occ > 0 ? c.occ : 1, c.k3.nw, nit, len, (0.8 + 1.6 * us) * (vec ? 1.0 : 1.2),
-                     2.46 * us * c.k3.nw / 4, grid);
+                     2.46 * us * c.k3.nw / 4, grid, limit);
 }
 
 struct Geo3 {
@@ -601,7 +640,10 @@ bool geo3(const Candidate& c, const int64_t n[3], int tb, Geo3& g, bool elems = 
     int64_t chunk = c.chunk;
     const int64_t per_plane = static_cast<int64_t>(g.tiles_x) * g.tiles_y;
     if (chunk <= 0 && tb == c.tb) chunk = c.auto_chunk;
-    if (chunk <= 0) chunk = best_chunk(n[0], 4, [&](int64_t len) { return star3_us(c, n, tb, per_plane, len, g.vec); });
+    if (chunk <= 0)
+        chunk = depth_chunk(c, tb, elems, [&] {
+            return best_chunk(n[0], 4, [&](int64_t len, double limit) { return star3_us(c, n, tb, per_plane, len, g.vec, limit); });
+        });
     chunk = std::min<int64_t>(chunk, n[0]);
     g.chunk_z = static_cast<int32_t>(chunk);
     g.chunks_z = static_cast<int32_t>(ceil_div(n[0], chunk));
@@ -805,6 +847,14 @@ void select_listed(st_plan_s* p, int i) {
     p->modelled = p->one_step = p->tiles = false;
 }
 
+// The plan's own places for what its candidates learn (see Candidate::tails).
+void own_tails(st_plan_s* p) {
+    const size_t n = p->cands.size() * (kDepths + 1);
+    p->tails.reset(new std::atomic<int32_t>[n]);
+    for (size_t i = 0; i < n; ++i) p->tails[i].store(0, std::memory_order_relaxed);
+    for (size_t i = 0; i < p->cands.size(); ++i) p->cands[i].tails = &p->tails[i * (kDepths + 1)];
+}
+
 void build_candidates(st_plan_s* p) {
     p->cands.clear();
     Candidate naive;
@@ -992,8 +1042,9 @@ void build_candidates(st_plan_s* p) {
     if (const char* ch = std::getenv("STENCIL_CHUNK")) chunk = std::atoi(ch);
     if (chunk > 0)
         for (Candidate& c : fast) c.chunk = chunk;
-    p->cands = fast;
+    p->cands = std::move(fast);
     p->cands.push_back(naive);
+    own_tails(p);
     model_select(p, force_naive);
     // (the streaming kernels are asked for: no others instead of them)
     if (chunk > 0) p->one_step = p->tiles = false;
@@ -1360,6 +1411,17 @@ int64_t flux_parts(const st_plan_s* p, const Candidate& c, bool fused, int tb, b
     return static_cast<int64_t>(g.tiles_x) * g.tiles_y * g.chunks_z * c.k3.nw;
 }
 
+// Candidate c for a pass of depth tb of a fused outflow run: with chunks no shorter
+// than the partial sums were sized for.
+Candidate flux_pass(const st_plan_s* p, Candidate c, int tb, bool elems) {
+    if (c.chunk > 0) return c;
+    Geo2 g2;
+    Geo3 g3;
+    if (c.kernel == ST_KERNEL_STREAM2D ? geo2(c, p->n[1], p->n[2], tb, g2, 0, elems) : geo3(c, p->n, tb, g3, elems))
+        c.chunk = std::max(c.kernel == ST_KERNEL_STREAM2D ? g2.chunk_y : g3.chunk_z, p->flux_shortest);
+    return c;
+}
+
 // The partial sums were sized when the plan was made (plan_buffers): a run
 // never allocates.
 st_status check_flux_parts(const st_plan_s* p, int64_t need) {
@@ -1406,7 +1468,7 @@ st_status run_steps(st_plan_s* p, const Candidate& c_sel, void* grid, void* work
     if (flux) {
         int64_t need = 0;
         for (int t : passes) {
-            const int64_t n = flux_parts(p, c, fused, t, elems);
+            const int64_t n = flux_parts(p, fused ? flux_pass(p, c, t, elems) : c, fused, t, elems);
             if (n < 0) return fail(ST_ERR_UNSUPPORTED, "tiling infeasible");
             need = std::max(need, n);
         }
@@ -1428,10 +1490,11 @@ st_status run_steps(st_plan_s* p, const Candidate& c_sel, void* grid, void* work
             if (hipError_t e = launch_flux_band(p->dtype, fb, p->flux_part, kFluxBandBlocks, s); e != hipSuccess)
                 return hip_fail(e, "outflow band launch");
         }
-        st_status r = launch_pass(p, c, src, dst, wcan, t, s, fused ? p->flux_part : nullptr);
+        const Candidate ct = fused ? flux_pass(p, c, t, elems) : c;
+        st_status r = launch_pass(p, ct, src, dst, wcan, t, s, fused ? p->flux_part : nullptr);
         if (r != ST_OK) return r;
         if (flux) {
-            if (hipError_t e = launch_flux_reduce(p->flux_part, flux_parts(p, c, fused, t, elems), flux, s); e != hipSuccess)
+            if (hipError_t e = launch_flux_reduce(p->flux_part, flux_parts(p, ct, fused, t, elems), flux, s); e != hipSuccess)
                 return hip_fail(e, "outflow reduce launch");
         }
         std::swap(src, dst);
@@ -1811,7 +1874,7 @@ void describe_varcoef(const st_plan_s* p, bool adjoint, st_plan_info* info);
 // stencil_plan without the device buffers and the mirror (the mirror plan of
 // a constant-weight adjoint is made this way, host memory only).
 st_status make_plan(st_plan_s** out, const st_pattern* pattern, const int64_t* shape, st_dtype storage,
-                    st_boundary bc, uint32_t flags, bool full) {
+                    st_boundary bc, uint32_t flags, bool full, const st_plan_s* like = nullptr) {
     *out = nullptr;
     if (st_status r = check_pattern(pattern); r != ST_OK) return r;
     if (!shape) return fail(ST_ERR_ARG, "shape is NULL");
@@ -1827,14 +1890,24 @@ st_status make_plan(st_plan_s** out, const st_pattern* pattern, const int64_t* s
         p->shape[d] = shape[d];
         p->n[3 - p->ndim + d] = shape[d];
     }
-    build_candidates(p);
+    if (like && like->cls == p->cls && like->radius == p->radius && like->npoints == p->npoints) {
+        p->cands = like->cands;
+        p->sel = like->sel;
+        p->modelled = like->modelled;
+        p->one_step = like->one_step;
+        p->tiles = like->tiles;
+        p->tile = like->tile;
+        own_tails(p);
+    } else {
+        build_candidates(p);
+    }
     if (full) {
-        st_status r = plan_buffers(p);
-        if (r == ST_OK && (flags & ST_PLAN_AUTOTUNE)) r = autotune(p);
-        if (r == ST_OK && !(flags & ST_PLAN_VARCOEF)) {
+        st_status r = ST_OK;
+        if (!(flags & ST_PLAN_VARCOEF)) {
             // the adjoint of a constant-weight sweep is the sweep with every
             // offset negated (same boundary): planned now, so the adjoint
-            // call allocates nothing
+            // call allocates nothing; its tilings, and the model's choice,
+            // depend on nothing that the negation changes
             std::vector<int32_t> off(static_cast<size_t>(p->npoints) * p->ndim);
             for (int i = 0; i < p->npoints; ++i) {
                 const int src = p->perm[i];  // caller's index of canonical point i
@@ -1842,8 +1915,10 @@ st_status make_plan(st_plan_s** out, const st_pattern* pattern, const int64_t* s
                     off[static_cast<size_t>(src) * p->ndim + d] = -p->off[i][3 - p->ndim + d];
             }
             const st_pattern mp{p->ndim, p->npoints, off.data()};
-            r = make_plan(&p->mirror, &mp, p->shape, storage, bc, flags & ST_PLAN_NAIVE, false);
+            r = make_plan(&p->mirror, &mp, p->shape, storage, bc, flags & ST_PLAN_NAIVE, false, p);
         }
+        if (r == ST_OK) r = plan_buffers(p);
+        if (r == ST_OK && (flags & ST_PLAN_AUTOTUNE)) r = autotune(p);
         if (r != ST_OK) {
             stencil_plan_destroy(p);
             return r;
@@ -2079,21 +2154,35 @@ int64_t batch_chunk(const st_plan_s* p, const Candidate& c, double* us_out) {
         maxny = std::max(maxny, g.ny);
         cells += static_cast<double>(g.ny) * static_cast<double>(g.nx);
     }
+    // strips of every grid: the same at every chunk length
+    struct Strips {
+        int64_t ny;
+        int32_t tiles;
+        double nx;
+    };
+    std::vector<Strips> grids;
+    grids.reserve(p->grids.size());
+    for (const BatchGrid& g : p->grids) {
+        Geo2 geo;
+        if (!geo2(c, g.ny, g.nx, c.tb, geo, maxny)) return 0;
+        grids.push_back({g.ny, geo.tiles_x, static_cast<double>(g.nx)});
+    }
+    const bool narrow = maxny < (int64_t(1) << 30);  // 32-bit divisions: a third of the time
     double best = 1e300;
     int64_t best_len = maxny, last = 0;
     for (double lf = 4; lf <= static_cast<double>(maxny) * 1.08; lf *= 1.08) {
         const int64_t len = std::min<int64_t>(static_cast<int64_t>(lf), maxny);
         if (len == last) continue;
         last = len;
+        const uint32_t len32 = static_cast<uint32_t>(len);
         int64_t items = 0;
         double streamed = 0;
-        for (const BatchGrid& bg : p->grids) {
-            Geo2 geo;
-            if (!geo2(c, bg.ny, bg.nx, c.tb, geo, len)) return 0;
-            items += geo.items;
-            streamed += static_cast<double>(bg.nx) * static_cast<double>(bg.ny + geo.chunks_y * halo);
+        for (const Strips& g : grids) {
+            const int64_t chunks = narrow ? (static_cast<uint32_t>(g.ny) + len32 - 1) / len32 : ceil_div(g.ny, len);
+            items += g.tiles * chunks;
+            streamed += g.nx * static_cast<double>(g.ny + chunks * halo);
         }
-        const double us = rows_us(c, c.tb, items, len + halo, streamed, cells);
+        const double us = rows_us(c, c.tb, items, len + halo, streamed, cells, best);
         if (us < best) {
             best = us;
             best_len = len;
@@ -2313,18 +2402,29 @@ st_status batch_run_impl(st_plan_s* plan, int32_t n, void* const* grids, void* c
 
 namespace {
 
-// Outflow partial sums a plan must hold: the most any pass of any candidate
+// Outflow partial sums a plan must hold: no fewer than any pass of any candidate
 // writes (the fused twins write one per wave or work item, the band kernel
-// kFluxBandBlocks); none for periodic and variable-coefficient plans.
-int64_t flux_need(const st_plan_s* p) {
+// kFluxBandBlocks); none for periodic and variable-coefficient plans.  Each tiling
+// of the list is asked once, with the shortest chunks of all (flux_pass keeps to
+// them at other depths).
+int64_t flux_need(st_plan_s* p) {
     if (p->bc != kZero || (p->flags & ST_PLAN_VARCOEF)) return 0;
     int64_t need = kFluxBandBlocks;
+    int32_t shortest = 0;
     for (const Candidate& c : p->cands) {
         if (p->batch) {
             if (c.kernel == ST_KERNEL_STREAM2D) need = std::max(need, batch_items(p, c));
-            continue;
+        } else if (c.kernel == ST_KERNEL_STREAM2D || c.kernel == ST_KERNEL_STREAM3D) {
+            const int32_t len = c.chunk > 0 ? c.chunk : c.auto_chunk;
+            if (len > 0 && (shortest == 0 || len < shortest)) shortest = len;
         }
-        if (!flux_fused(p, c)) continue;
+    }
+    if (p->batch) return need;
+    p->flux_shortest = shortest;
+    for (const Candidate& listed : p->cands) {
+        if (listed.chunk != p->cands[0].chunk || !flux_fused(p, listed)) continue;
+        Candidate c = listed;
+        c.chunk = shortest;
         for (int t = 1; t <= c.tb; ++t) need = std::max({need, flux_parts(p, c, true, t, true), flux_parts(p, c, true, t, false)});
     }
     return need;

@@ -2,6 +2,7 @@
 sources have to keep."""
 import os
 import re
+import time
 
 import pytest
 
@@ -51,3 +52,35 @@ def test_chunk_length_from_the_environment_runs(monkeypatch, shape, kernel, axis
     for dtype in ("f64", "f32", "bf16"):
         ran = st.Plan(synth.star_offsets(len(shape), 1), shape, dtype).launches()
         assert ran["kernel"] == kernel and ran[axis] == 16, (dtype, ran)
+
+
+# making a plan searches a chunk length per tiling: against a plan that has nothing
+# to search (one step per launch), 8 to 9 times the time where it was 19 to 24 with
+# every trial length priced in full, for the transposed sweep's plan once more
+@pytest.mark.parametrize("shape", [(512, 512, 512), (251, 319, 377)])
+def test_a_plan_costs_a_bounded_search(shape):
+    def least(**kw):
+        best = float("inf")
+        for _ in range(60):
+            t = time.perf_counter()
+            plan = st.Plan(synth.star_offsets(3, 1), shape, "f64", **kw)
+            best = min(best, time.perf_counter() - t)
+            plan.close()
+        return best
+    ratios = []
+    for _ in range(5):  # a loaded machine: the least of a few
+        ratios.append(least() / least(naive=True))
+        if ratios[-1] < 14:
+            return
+    raise AssertionError(f"times a plan without a search: {ratios}")
+
+
+# the transposed sweep takes the tilings that the plan's own choice takes, whatever
+# the caller or the autotuner selects afterwards
+def test_the_transposed_sweep_keeps_the_models_choice():
+    for offs, shape in [(synth.star_offsets(3, 1), (96, 97, 98)), (synth.box_offsets(2, 2), (300, 900)), ([(0, 0), (0, 1), (-2, 0)], (50, 50))]:
+        plan = st.Plan(offs, shape, "f32", "periodic")
+        own = plan.launches()
+        assert plan.launches("adjoint") == own
+        plan.select(variant=len(plan.candidates()) - 1)
+        assert plan.launches("adjoint") == own
