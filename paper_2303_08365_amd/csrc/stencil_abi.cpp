@@ -2695,10 +2695,10 @@ VarcoefPairs varcoef_pairs(const st_plan_s* p, bool adjoint) {
         // FP32: 724 us an adjoint step with 3 tiles of 256 columns, 839 with 9
         // of 64; 512^3 FP64: 1365 with 5 of 128, 1560 with 9 of 64)
         const double plane = sh.wgs_per_cu * vx * (vx == widest ? 1.0 : 1.5);
-        for (int64_t chunk = nz, last = 0; chunk >= 1; --chunk) {
-            const int64_t chunks = ceil_div(nz, chunk);
-            if (chunks == last || per_plane * chunks >= (int64_t(1) << 31)) continue;
-            last = chunks;
+        // the longest chunks of each count: at most 2 sqrt(nz) of them
+        for (int64_t chunk = nz, chunks; chunk >= 1; chunk = ceil_div(nz, chunks) - 1) {
+            chunks = ceil_div(nz, chunk);
+            if (per_plane * chunks >= (int64_t(1) << 31)) break;
             const double cost = static_cast<double>(ceil_div(per_plane * chunks, cap)) * static_cast<double>(chunk + 4) *
                                 plane;
             if (best.vx == 0 || cost < least) {

@@ -84,3 +84,23 @@ def test_the_transposed_sweep_keeps_the_models_choice():
         assert plan.launches("adjoint") == own
         plan.select(variant=len(plan.candidates()) - 1)
         assert plan.launches("adjoint") == own
+
+
+# the two-step variable-coefficient passes try each count of chunks once: a call
+# on a long grid spends microseconds there, not a division per plane (half a
+# second at 10^8 planes)
+def test_variable_coefficient_chunks_of_a_long_grid():
+    plan = st.varcoef_plan((10 ** 8, 32, 64), "f32")
+    best = float("inf")
+    for _ in range(3):
+        t = time.perf_counter()
+        ran = plan.launches()
+        best = min(best, time.perf_counter() - t)
+    assert ran["tb"] == 2 and best < 0.02, best
+    # every length that a search over all of them takes
+    for nz in (1, 2, 7, 63, 64, 100, 257, 1000, 4099):
+        for ny, nx in ((32, 64), (95, 512), (300, 1000)):
+            got = {c: st.varcoef_plan((nz, ny, nx), "f32").launches(c)["tile_z"] for c in ("run", "adjoint")}
+            for call, z in got.items():
+                chunks = -(-nz // z)
+                assert z == nz or -(-nz // (z + 1)) < chunks, (nz, call, z)  # the longest with that count
