@@ -195,6 +195,9 @@ struct st_plan_s {
     bool one_step = false, tiles = false;
     Candidate tile;  // tiles: their kernel, depth and columns a lane (k2.vx)
     std::unique_ptr<std::atomic<int32_t>[]> tails;  // the candidates' `tails`
+    // what outflow runs take (flux_choice), asked by the first one after a
+    // selection: candidate * 2 + one step per launch; -1: not yet
+    mutable std::atomic<int32_t> flux_kept{-1};
     // Device memory a plan owns is allocated when the plan is made (see
     // plan_buffers), never by a run call.
     void* owned_work = nullptr;   // ST_PLAN_OWN_WORK
@@ -809,6 +812,7 @@ double register_select(const st_plan_s* p, Candidate& tile, int only_vx = 0, int
 void model_select(st_plan_s* p, bool fixed) {
     p->sel = 0;
     p->modelled = p->one_step = p->tiles = false;
+    p->flux_kept.store(-1, std::memory_order_relaxed);
     if (fixed || p->cands.size() <= 1) return;
     p->modelled = true;
     double best = 1e300;
@@ -845,6 +849,7 @@ int default_vx2(int dtype) { return dtype == kF64 ? 2 : 4; }
 void select_listed(st_plan_s* p, int i) {
     p->sel = i;
     p->modelled = p->one_step = p->tiles = false;
+    p->flux_kept.store(-1, std::memory_order_relaxed);
 }
 
 // The plan's own places for what its candidates learn (see Candidate::tails).
@@ -1738,7 +1743,7 @@ st_status autotune(st_plan_s* p) {
 }
 
 // The candidate of a zero-rule outflow run; one_step: one step per launch instead of it.
-const Candidate& flux_choice(const st_plan_s* plan, bool& one_step) {
+const Candidate& search_flux(const st_plan_s* plan, bool& one_step) {
     const Candidate* cand = &plan->cands[plan->sel];
     one_step = plan->one_step;
     if (plan->modelled) {
@@ -1765,6 +1770,19 @@ const Candidate& flux_choice(const st_plan_s* plan, bool& one_step) {
         for (const Candidate& c : plan->cands)
             if (c.kernel == cand->kernel && c.tb == cand->tb && flux_fused(plan, c)) return c;
     return *cand;
+}
+
+// The same, searched once per selection: pricing the list takes longer than a
+// small run's launches.
+const Candidate& flux_choice(const st_plan_s* plan, bool& one_step) {
+    int32_t kept = plan->flux_kept.load(std::memory_order_relaxed);
+    if (kept < 0) {
+        const Candidate& c = search_flux(plan, one_step);
+        kept = static_cast<int32_t>(&c - plan->cands.data()) * 2 + (one_step ? 1 : 0);
+        plan->flux_kept.store(kept, std::memory_order_relaxed);
+    }
+    one_step = (kept & 1) != 0;
+    return plan->cands[kept / 2];
 }
 
 // Key of a run: every argument that ends up inside the launches.

@@ -104,3 +104,29 @@ def test_variable_coefficient_chunks_of_a_long_grid():
             for call, z in got.items():
                 chunks = -(-nz // z)
                 assert z == nz or -(-nz // (z + 1)) < chunks, (nz, call, z)  # the longest with that count
+
+
+# what an outflow run takes is searched once per selection, not by every call: the
+# question costs what it does for a plain run (several times that, searched)
+@pytest.mark.parametrize("shape", [(512, 512), (64, 64, 64), (251, 319, 377)])
+def test_outflow_runs_do_not_search_on_every_call(shape):
+    plan = st.Plan(synth.star_offsets(len(shape), 1), shape, "f32")
+
+    def least(call):
+        best = float("inf")
+        for _ in range(300):
+            t = time.perf_counter()
+            plan.launches(call)
+            best = min(best, time.perf_counter() - t)
+        return best
+    before = plan.launches("flux")
+    ratios = []
+    for _ in range(5):  # a loaded machine: the least of a few
+        ratios.append(least("flux") / least("run"))
+        if ratios[-1] < 2.5:
+            break
+    else:
+        raise AssertionError(ratios)
+    plan.select(variant=5)
+    assert plan.launches("flux") != before  # a selection is looked at again
+    assert plan.launches("flux")["tb"] == plan.candidates()[5]["tb"]
