@@ -1716,12 +1716,12 @@ st_status autotune(st_plan_s* p) {
             best = ms;
             best_i = static_cast<int>(i);
         }
-    // Register tiles and bricks, where their model comes within twice that: for
+    // Register tiles and bricks, where their model comes within half more than that: for
     // each lane width its depth and those around (the model is 12 % off at most).
     bool tiles = false;
     for (int vx : {1, 2, 4}) {
         Candidate c;
-        if (register_select(p, c, vx) >= 2e3 * best) continue;
+        if (register_select(p, c, vx) >= 1.5e3 * best) continue;
         const int model_t = c.tb;
         for (int t = std::max(1, model_t - 4); t <= model_t + 4; ++t)
             if (register_select(p, c, vx, t) < 1e300)

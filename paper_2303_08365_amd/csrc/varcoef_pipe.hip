@@ -31,11 +31,13 @@
 //
 // What bounds it: the bytes, with the vector units close behind.  A forward
 // pair moves 12 bytes a FP32 cell instead of 24 (16 where the state between is
-// stored too), an adjoint pair 28 instead of 48; at 256^3 FP32 a pair takes 46
-// us (56 with the state between), two single steps 90, and an adjoint pair 94
-// instead of 172: 4.4 to 5.0 TB/s, where a copy reaches 5.2 to 5.9.  FP64 256^3:
-// 47 us a step instead of 82.  Taking a face's conductivity once for both cells
-// brings a step from 25 to 16 operations a cell.  8 waves of 4 rows (2 in the
+// stored too), an adjoint pair 28 instead of 48; at 256^3 FP32 a pair takes 43
+// us (55 with the state between), two single steps 90, and an adjoint pair 94
+// instead of 172: 4.4 to 5.0 TB/s, where a copy reaches 5.2 to 5.9 (44 and 57 us
+// before planes of k were halved as they arrive, which leaves a face's
+// conductivity one addition).  FP64 256^3: 47 us a step instead of 82.  Taking a
+// face's conductivity once for both cells brings a step from 25 to 16 operations
+// a cell.  8 waves of 4 rows (2 in the
 // adjoint, whose fields need the registers) are one work-group a CU: the
 // rows re-read in y fall to 1/15 (1/7).
 #include "dev_common.h"
